@@ -8,6 +8,7 @@
 // by segmented prefixes.
 #include <hip/hip_runtime.h>
 
+#include "flr_avg.hpp"
 #include "flr_box.hpp"
 #include "flr_launch.hpp"
 #include "flr_prefix.hpp"
@@ -152,6 +153,49 @@ hipError_t launch_mean_planes64(const double* src, double* dst, int planes, int 
   a.W = W;
   a.r = r;
   return box_launch(a, planes, s);
+}
+
+// The coefficient average (it needs no per-(Q, C) code, so it is built here
+// once, beside the other window sums).
+template <int RAD, int TH, bool BATCH>
+__global__ void __launch_bounds__(kThreads, 2) apply_avg_kernel(LaunchArgs ain) {
+  int bid = blockIdx.x;
+  const LaunchArgs a = BATCH ? batch_frame(ain, &bid) : ain;
+  const int n = a.tiles_x * a.n_seg * a.nc;
+  const int t = avg_group_xcd(bid, n);
+  if (t >= n) return;  // padding
+  if constexpr (TH == 0)  // frames of a batch may differ in tile height
+    avg_group<RAD>(a, t);
+  else
+    avg_group_th<TH, RAD>(a, t);
+}
+
+template <int RAD>
+static void avg_dispatch(const LaunchArgs& a, bool batch, int blocks, hipStream_t s) {
+  const size_t l = avg_lds_bytes(batch ? kAvgTileRows : a.seg_rows);
+  if (batch)
+    hipLaunchKernelGGL((apply_avg_kernel<RAD, 0, true>), dim3(blocks), dim3(kThreads), l, s, a);
+  else if (a.seg_rows > 4)
+    hipLaunchKernelGGL((apply_avg_kernel<RAD, 8, false>), dim3(blocks), dim3(kThreads), l, s, a);
+  else if (a.seg_rows > 2)
+    hipLaunchKernelGGL((apply_avg_kernel<RAD, 4, false>), dim3(blocks), dim3(kThreads), l, s, a);
+  else
+    hipLaunchKernelGGL((apply_avg_kernel<RAD, 2, false>), dim3(blocks), dim3(kThreads), l, s, a);
+}
+
+hipError_t launch_avg(const LaunchArgs& a, bool batch, hipStream_t s) {
+  if (a.r < 0 || a.r > 32) return hipErrorInvalidValue;
+  // taller tiles load four columns at a time (plan_avg)
+  if (!batch && (a.seg_rows < 1 || a.seg_rows > kAvgTileRows || a.nc < 1 ||
+                 (a.seg_rows > 2 && a.W < 4)))
+    return hipErrorInvalidValue;
+  const int blocks = batch ? a.batch_blocks : avg_groups(a.tiles_x * a.n_seg, a.nc);
+  switch (avg_variant(a.r)) {
+    case AVG_R8: avg_dispatch<AVG_R8>(a, batch, blocks, s); break;
+    case AVG_R64: avg_dispatch<AVG_R64>(a, batch, blocks, s); break;
+    default: avg_dispatch<AVG_R16>(a, batch, blocks, s); break;
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_pair_sum(const double* src, int n, double* dst, hipStream_t s) {

@@ -36,6 +36,8 @@ LaunchArgs base_args(const flr_params* p) {
   a.H = p->height;
   a.W = p->width;
   a.r = p->radius;
+  a.nq = p->num_guides;
+  a.nc = p->num_channels;
   a.eps = p->eps;
   a.eps_mul = p->eps_mul;
   a.eps_dev = p->eps_device;
@@ -45,6 +47,11 @@ LaunchArgs base_args(const flr_params* p) {
 }
 
 void plan(const flr_params* p, int kind, LaunchArgs* a) {
+  if (kind == flr::K_APPLY_AVG) {
+    flr::plan_avg(p->height, p->width, p->radius, p->num_channels, p->tile_rows, &a->tiles_x,
+                  &a->n_seg, &a->seg_rows);
+    return;
+  }
   flr::plan_walk(kind, p->height, p->width, p->radius, p->tile_rows, &a->tiles_x, &a->n_seg,
                  &a->seg_rows);
   const int Q = p->num_guides, C = p->num_channels, r = p->radius;
@@ -57,6 +64,9 @@ void plan(const flr_params* p, int kind, LaunchArgs* a) {
 flr_status dispatch(int Q, int C, int kind, const LaunchArgs& a, void* stream) {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipError_t e;
+  if (kind == flr::K_APPLY_AVG || kind == flr::K_APPLY_AVG_BATCH)
+    return flr::launch_avg(a, kind == flr::K_APPLY_AVG_BATCH, s) == hipSuccess ? FLR_OK
+                                                                               : FLR_ERR_HIP;
   switch (Q) {
     case 1: e = flr::launch_q1(C, kind, a, s); break;
     case 2: e = flr::launch_q2(C, kind, a, s); break;
@@ -705,7 +715,7 @@ flr_status flr_batch_plan(const flr_params* p, const flr_frame* frames, int32_t 
       a.coef_lo = 1;
       plan(&q, flr::K_APPLY_AVG, &a);
       apply[np] = a;
-      ws_apply[np + 1] = ws_apply[np] + flr::avg_groups(a.tiles_x * a.n_seg);
+      ws_apply[np + 1] = ws_apply[np] + flr::avg_groups(a.tiles_x * a.n_seg, C);
       ++np;
     } else {
       a.fin = reinterpret_cast<const double*>(ws + L.mean[i]);
@@ -805,7 +815,7 @@ flr_status flr_batch_plan(const flr_params* p, const flr_frame* frames, int32_t 
     const LaunchArgs& a = apply[i];
     const LaunchArgs& w = walk_sorted[inv[i]];
     largs[nl] = a;
-    stage(flr::BI_AVG, nl++, a.tiles_x * a.n_seg, 0, walk_ctr[inv[i]], w.tiles_x, -1,
+    stage(flr::BI_AVG, nl++, flr::avg_workgroups(a.tiles_x * a.n_seg, C), 0, walk_ctr[inv[i]], w.tiles_x, -1,
           w.seg_rows, w.n_seg);
   }
   for (int j = 0; j < nj; ++j) {

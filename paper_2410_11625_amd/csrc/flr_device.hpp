@@ -45,12 +45,6 @@ __host__ __device__ constexpr int tri(int p, int q) {
   return p * Q - p * (p - 1) / 2 + (q - p);
 }
 
-__device__ __forceinline__ int win_count(int i, int n, int r) {
-  const int lo = i - r < 0 ? 0 : i - r;
-  const int hi = i + r > n - 1 ? n - 1 : i + r;
-  return hi - lo + 1;
-}
-
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
 __device__ __forceinline__ float rsqrt_t(float x) { return rsqrtf(x); }
@@ -63,14 +57,6 @@ __device__ __forceinline__ double rsqrt_t(double x) {
   const double e = fma(-x * y, y, 1.0);
   return fma(0.5 * y, e, y);
 }
-// 1/n for a window count n >= 1, refined the same way.
-__device__ __forceinline__ float recip_count(int n, float) { return 1.f / (float)n; }
-__device__ __forceinline__ double recip_count(int n, double) {
-  const double d = (double)n;
-  const double y = (double)(1.f / (float)n);
-  return fma(y, fma(-d, y, 1.0), y);
-}
-
 // max(x, 0) that lets NaN through.
 template <typename T>
 __device__ __forceinline__ T clamp_nonneg(T x) {
@@ -255,31 +241,6 @@ __device__ __forceinline__ void hbox(const E* __restrict__ src, E* __restrict__ 
       acc1 += x1[jj] - s1[jj - 1];
       d1[jj] = acc1;
     }
-  }
-}
-
-// Buffer descriptor of one FP32 plane of `bytes` bytes (raw: stride 0,
-// GFX9 dword-3 format word), and a dword load at vector offset `vo` plus
-// scalar offset `so`.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const float* base, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), (short)0, bytes, 0x00020000);
-}
-__device__ __forceinline__ float plane_load(__amdgpu_buffer_rsrc_t rs, int vo, int so) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, vo, so, 0));
-}
-
-// Rows y0 .. y0 + NV - 1 of one column of an FP32 plane (byte offset xb of
-// the column; zero outside the image or where !xin).
-template <int NV>
-__device__ __forceinline__ void column_block(const float* plane, int bytes, int xb, int y0, int H,
-                                             int W, bool xin, float (&v)[NV]) {
-  const __amdgpu_buffer_rsrc_t rs = plane_rsrc(plane, bytes);
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int y = y0 + i;
-    const float t = plane_load(rs, xb, min(max(y, 0), H - 1) * W * 4);
-    const unsigned keep = (xin && y >= 0 && y < H) ? 0xffffffffu : 0u;
-    v[i] = __uint_as_float(__float_as_uint(t) & keep);
   }
 }
 
@@ -557,16 +518,6 @@ enum WalkMode : int { W_MOMENTS = 0, W_FUSED0 = 1, W_FUSED1 = 2, W_COEFFS = 3, W
 // POFF, PCNT: the slice of product channels this walker carries (all by
 // default); W_MOMENTS over a slice writes that slice's planes (and, for the
 // first slice, n and the means).
-// The frame and local workgroup index of a batched launch (frames are few:
-// a scan of the workgroup offsets, uniform across the workgroup).
-__device__ __forceinline__ const LaunchArgs& batch_frame(const LaunchArgs& ain, int* bid) {
-  const int b = blockIdx.x;
-  int f = 0;
-  while (f + 1 < ain.nframes && ain.wg_start[f + 1] <= b) ++f;
-  *bid = b - ain.wg_start[f];
-  return ain.frames[f];
-}
-
 // One workgroup's tile (strip sx = bid % tiles_x, segment bid / tiles_x) of
 // frame a.
 template <int Q, int C, int MODE, bool WIDE, int POFF = 0, int PCNT = -1>
@@ -1031,248 +982,10 @@ __global__ void __launch_bounds__(256) apply_point_kernel(LaunchArgs a) {
   }
 }
 
-// flr_apply with averaging (Sec. 3.1: each pixel's output uses the mean of
-// the coefficients of the windows that contain it). A workgroup owns a tile
-// of th <= kAvgTileRows output rows by 256 - 2r output columns; lane l owns
-// input column X0 - r + l. The coefficient planes are taken one at a time:
-// the lane streams its column's th + 2r rows of the plane once, forms the
-// vertical window sums of the tile's rows by sliding (FP64), and the
-// horizontal sums come from DPP segment prefixes staged in LDS, as in the
-// moment walkers. Each output lane accumulates
-//   out_c = (sum b_c + sum_q g_q * sum a_qc) / n
-// for all C channels of its th pixels in FP64 registers. Planes alternate
-// between two LDS buffers, one barrier each.
-// Variants of the averaging kernel: the column walk streams its rows for any
-// radius (AV_STREAM16: 16-lane prefix segments, r <= 8; AV_STREAM64:
-// wavefront segments, r > 8), or, for r = 8 and up to three channels (the
-// register budget of two workgroups per CU), loads each plane's column
-// block once and slides with compile-time offsets (AV_BLOCK8).
-enum AvgVariant : int { AV_STREAM16 = 0, AV_STREAM64 = 1, AV_BLOCK8 = 2 };
-__host__ __device__ constexpr int avg_variant(int r, int C) {
-  return (r == 8 && C <= 3) ? AV_BLOCK8 : (wide_segments(r) ? AV_STREAM64 : AV_STREAM16);
-}
-
-template <int Q, int C, int AV, bool LO>
-__device__ __forceinline__ void apply_avg_tile(const LaunchArgs a, const int sx, const int sy) {
-  using T = solve_t;
-  constexpr bool WIDE = AV == AV_STREAM64;
-  constexpr int TH = kAvgTileRows;
-  extern __shared__ float lds[];
-  T* P0 = reinterpret_cast<T*>(lds);
-  T* P1 = P0 + TH * kLdsStride;
-  const int tid = threadIdx.x;
-  const int r = a.r;
-  const int H = a.H;
-  const int W = a.W;
-  const int64_t pl = (int64_t)H * W;
-  const int tout = kThreads - 2 * r;
-  const int X0 = sx * tout;
-  const int Y0 = sy * a.seg_rows;
-  const int th = min(a.seg_rows, H - Y0);
-  const int xcol = X0 - r + tid;
-  const bool xin = xcol >= 0 && xcol < W;
-  const int xo = X0 + tid;
-  const bool active = tid < tout && xo < W;
-  const HWin hw = hwin<WIDE>(tid, r);
-  if (tid < 2 * TH) (tid < TH ? P0 : P1)[(tid % TH) * kLdsStride + kThreads] = T(0);
-
-  T acc[TH][C];
-#pragma unroll
-  for (int k = 0; k < TH; ++k)
-#pragma unroll
-    for (int c = 0; c < C; ++c) acc[k][c] = T(0);
-
-  // Loads use clamped, always valid addresses (a plane base pointer plus a
-  // 32-bit offset) and zero what lies outside the image by selection, so
-  // that no load needs a branch.
-  // Raw buffer loads: a descriptor per plane, the lane's column byte offset
-  // (vector) and the row's byte offset (scalar; rows are clamped into the
-  // image, so every access is in range; planes hold at most 2^28 pixels, so
-  // offsets fit in 32 bits).
-  const int xcb = min(max(xcol, 0), W - 1) * 4;
-  const int xob = min(xo, W - 1) * 4;
-  const int pbytes = (int)(pl * 4 <= 0x7fffffff ? pl * 4 : 0x7fffffff);
-  auto at = [&](const float* base, int y, int xb) {
-    const int so = min(max(y, 0), H - 1) * W * 4;
-    return plane_load(plane_rsrc(base, pbytes), xb, so);
-  };
-  // Window sums of the tile's rows from the prefixes in P, batched four
-  // rows (twelve reads) at a time, accumulated into channel c's sums.
-  auto consume = [&](const T* P, int c, bool plain, const float (&gf)[TH]) {
-    constexpr int B = 4;
-#pragma unroll
-    for (int k0 = 0; k0 < TH; k0 += B) {
-      T rb[B], ra[B], rt[B];
-#pragma unroll
-      for (int i = 0; i < B; ++i) {
-        if (k0 + i < TH) {
-          const T* row = P + (k0 + i) * kLdsStride;
-          rb[i] = row[hw.ib];
-          ra[i] = row[hw.ia];
-          rt[i] = row[hw.it];
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < B; ++i) {
-        if (k0 + i < TH) {
-          const T v = (rb[i] - ra[i]) + rt[i];
-#pragma unroll
-          for (int cc = 0; cc < C; ++cc)
-            if (cc == c)
-              acc[k0 + i][cc] = plain ? acc[k0 + i][cc] + v : fma_t((T)gf[k0 + i], v, acc[k0 + i][cc]);
-        }
-      }
-    }
-  };
-  // DPP segment prefixes of the tile's vertical sums into LDS buffer P
-  auto stage = [&](T* P, const T (&vs)[TH]) {
-    constexpr int IL = 4;
-#pragma unroll
-    for (int k0 = 0; k0 < TH; k0 += IL) {
-      T x[IL];
-#pragma unroll
-      for (int i = 0; i < IL; ++i) x[i] = k0 + i < TH ? vs[k0 + i] : T(0);
-      seg_prefix_n<WIDE>(x);
-#pragma unroll
-      for (int i = 0; i < IL; ++i)
-        if (k0 + i < TH) P[(k0 + i) * kLdsStride + tid] = x[i];
-    }
-  };
-  auto load_gf = [&](int q, float (&gf)[TH]) {
-    const float* g = a.guides + (int64_t)q * pl;
-#pragma unroll
-    for (int k = 0; k < TH; ++k) gf[k] = at(g, Y0 + k, xob);
-  };
-
-  // planes: b (C), a (Q C), then with LO the intercepts' lo parts (C),
-  // taken as a pass q = Q that adds like the intercepts
-  constexpr int qend = LO ? Q + 1 : Q;
-  constexpr int nplanes = (qend + 1) * C;
-  int buf = 0;
-  if constexpr (AV == AV_BLOCK8) {
-    // r = 8: the lane loads its column's rows Y0 - 8 .. Y0 + TH + 7 of a
-    // plane as one block (zero outside the image), issued while the plane
-    // before it is staged and consumed.
-    constexpr int NV = TH + 16;
-    auto load_block = [&](int f, float (&v)[NV]) {
-      column_block<NV>(a.planes + (int64_t)f * pl, pbytes, xcb, Y0 - 8, H, W, xin, v);
-    };
-    // vertical window sums of rows Y0 + k: rows Y0 + k - R .. Y0 + k + R
-    auto slide = [&](auto RC, const float (&v)[NV], T (&vs)[TH]) {
-      constexpr int R = decltype(RC)::value;
-      T sum = T(0);
-#pragma unroll
-      for (int i = 8 - R; i <= 8 + R; ++i) sum += (T)v[i];
-      vs[0] = sum;
-#pragma unroll
-      for (int k = 1; k < TH; ++k) {
-        sum += (T)v[k + 8 + R] - (T)v[k + 7 - R];
-        vs[k] = sum;
-      }
-    };
-    float cur[NV];
-    load_block(0, cur);
-    float gf[TH];
-    for (int q = -1; q < qend; ++q) {
-      if (q >= 0 && q < Q) load_gf(q, gf);
-#pragma unroll
-      for (int c = 0; c < C; ++c) {
-        const int f = (q + 1) * C + c;
-        T vs[TH];
-        slide(std::integral_constant<int, 8>{}, cur, vs);
-        // the next plane's block streams in during staging and consumption
-        if (f + 1 < nplanes) load_block(f + 1, cur);
-        T* P = buf ? P1 : P0;
-        buf ^= 1;
-        stage(P, vs);
-        __syncthreads();
-        if (active) consume(P, c, q < 0 || q == Q, gf);
-      }
-    }
-  } else {
-    // any r: the window of the tile's first row is summed by a running
-    // loop; rows entering and leaving are loaded for each later row.
-    float gf[TH];
-    for (int q = -1; q < qend; ++q) {
-      if (q >= 0 && q < Q) load_gf(q, gf);
-#pragma unroll
-      for (int c = 0; c < C; ++c) {
-        const float* src = a.planes + (int64_t)((q + 1) * C + c) * pl;
-        T sum = T(0);
-        for (int y = max(Y0 - r, 0); y <= min(Y0 + r, H - 1); ++y) sum += (T)at(src, y, xcb);
-        if (!xin) sum = T(0);
-        T vs[TH];
-        vs[0] = sum;
-#pragma unroll
-        for (int k = 1; k < TH; ++k) {
-          const int ye = Y0 + r + k, yl = Y0 - r - 1 + k;
-          const float ve = at(src, ye, xcb), vl = at(src, yl, xcb);
-          const float e = (xin && k < th && ye < H) ? ve : 0.f;
-          const float l = (xin && k < th && yl >= 0) ? vl : 0.f;
-          sum += (T)e - (T)l;
-          vs[k] = sum;
-        }
-        T* P = buf ? P1 : P0;
-        buf ^= 1;
-        stage(P, vs);
-        __syncthreads();
-        if (active) consume(P, c, q < 0 || q == Q, gf);
-      }
-    }
-  }
-  if (active) {
-#pragma unroll
-    for (int k = 0; k < TH; ++k) {
-      if (k < th) {
-        const int y = Y0 + k;
-        const T inv = recip_count(win_count(y, H, r) * win_count(xo, W, r), T(0));
-        float* o = a.out + (int64_t)y * W + xo;
-#pragma unroll
-        for (int c = 0; c < C; ++c) o[c * pl] = (float)(acc[k][c] * inv);
-      }
-    }
-  }
-}
-
-template <int Q, int C, int AV>
-__device__ __forceinline__ void apply_avg_tile_any(const LaunchArgs& a, const int sx,
-                                                   const int sy) {
-  if (a.coef_lo)
-    apply_avg_tile<Q, C, AV, true>(a, sx, sy);
-  else
-    apply_avg_tile<Q, C, AV, false>(a, sx, sy);
-}
-
-// Tile of averaging workgroup b of a frame's launch range. Workgroups are
-// dealt to the XCDs round-robin, and a frame's range starts at a multiple
-// of kXcds and has avg_groups(tiles) workgroups, so XCD k runs the frame's
-// workgroups k, k + kXcds, ... in order; it gets the k-th run of
-// ceil(tiles / kXcds) tiles in strip-major order. Vertically adjacent tiles
-// of a strip share 2r rows of every coefficient plane, which then stay in
-// that XCD's L2. False for the padding workgroups.
-__device__ __forceinline__ bool avg_tile_xcd(int b, int tiles_x, int n_seg, int* sx, int* sy) {
-  const int tiles = tiles_x * n_seg;
-  const int m = (tiles + kXcds - 1) / kXcds;
-  const int t = (b % kXcds) * m + b / kXcds;
-  if (t >= tiles) return false;
-  *sx = t / n_seg;
-  *sy = t - *sx * n_seg;
-  return true;
-}
-
-template <int Q, int C, int AV, bool BATCH = false>
-__global__ void __launch_bounds__(kThreads, kAvgPerCU) apply_avg_kernel(LaunchArgs ain) {
-  int bid = blockIdx.x;
-  const LaunchArgs a = BATCH ? batch_frame(ain, &bid) : ain;
-  int sx, sy;
-  if (!avg_tile_xcd(bid, a.tiles_x, a.n_seg, &sx, &sy)) return;  // padding
-  apply_avg_tile_any<Q, C, AV>(a, sx, sy);
-}
-
 }  // namespace flr
 
 #include "flr_adjoint.hpp"
+#include "flr_avg.hpp"
 #include "flr_box.hpp"
 #include "flr_lowres.hpp"
 
@@ -1316,7 +1029,7 @@ __global__ void __launch_bounds__(kThreads, 1) batch_kernel(LaunchArgs ain) {
         bool ok = true;
         if (S.kind == BI_AVG) {
           const LaunchArgs& f = P->largs[S.arg];
-          const int y0 = (b / f.tiles_x) * f.seg_rows;
+          const int y0 = b / f.nc % f.n_seg * f.seg_rows;
           const int y1 = min(y0 + f.seg_rows, f.H);
           const int s0 = max(y0 - f.r, 0) / S.seg_rows;
           const int s1 = min((min(y1 + f.r, f.H) - 1) / S.seg_rows, S.nseg - 1);
@@ -1350,8 +1063,7 @@ __global__ void __launch_bounds__(kThreads, 1) batch_kernel(LaunchArgs ain) {
         box_tile_any<BOX_MEAN64, WIDE>(P->bargs[S.arg], b % S.nx, b / S.nx);
         break;
       case BI_AVG:
-        apply_avg_tile_any<Q, C, AV>(P->largs[S.arg], b % P->largs[S.arg].tiles_x,
-                                     b / P->largs[S.arg].tiles_x);
+        avg_group<AV>(P->largs[S.arg], b);
         break;
       default:
         up_apply_item<Q, C>(P->largs[S.arg], b);
@@ -1442,20 +1154,6 @@ hipError_t launch_qc(int kind, const LaunchArgs& a, hipStream_t s) {
                                       wblocks, l2, a, s);
       }
       return hipErrorInvalidValue;
-    case K_APPLY_AVG:
-      switch (avg_variant(a.r, C)) {
-        case AV_BLOCK8:
-          if constexpr (C <= 3)
-            return launch_with_lds(apply_avg_kernel<Q, C, AV_BLOCK8>, avg_groups(wblocks), lds, a,
-                                   s);
-          return hipErrorInvalidValue;
-        case AV_STREAM64:
-          return launch_with_lds(apply_avg_kernel<Q, C, AV_STREAM64>, avg_groups(wblocks), lds, a,
-                                 s);
-        default:
-          return launch_with_lds(apply_avg_kernel<Q, C, AV_STREAM16>, avg_groups(wblocks), lds, a,
-                                 s);
-      }
     case K_SOLVE:
       hipLaunchKernelGGL((solve_kernel<Q, C>), dim3(pblocks), dim3(256), 0, s, a);
       return hipGetLastError();
@@ -1489,35 +1187,18 @@ hipError_t launch_qc(int kind, const LaunchArgs& a, hipStream_t s) {
                                       a.batch_blocks, lds_of(K_COEFFS), a, s);
       }
       return hipErrorInvalidValue;
-    case K_APPLY_AVG_BATCH:
-      switch (avg_variant(a.r, C)) {
-        case AV_BLOCK8:
-          if constexpr (C <= 3)
-            return launch_with_lds(apply_avg_kernel<Q, C, AV_BLOCK8, true>, a.batch_blocks,
-                                   lds_of(K_APPLY_AVG), a, s);
-          return hipErrorInvalidValue;
-        case AV_STREAM64:
-          return launch_with_lds(apply_avg_kernel<Q, C, AV_STREAM64, true>, a.batch_blocks,
-                                 lds_of(K_APPLY_AVG), a, s);
-        default:
-          return launch_with_lds(apply_avg_kernel<Q, C, AV_STREAM16, true>, a.batch_blocks,
-                                 lds_of(K_APPLY_AVG), a, s);
-      }
     case K_UP_APPLY_BATCH:
       hipLaunchKernelGGL((up_apply_kernel<Q, C, true>), dim3(a.batch_blocks), dim3(256), 0, s, a);
       return hipGetLastError();
     case K_BATCH_PERSISTENT:
       if constexpr (!split_walk(Q, C)) {
         const size_t l = batch_lds_bytes(Q, C);
-        const int av = avg_variant(a.r, C);
-        if (av == AV_BLOCK8) {
-          if constexpr (C <= 3) return launch_with_lds(batch_kernel<Q, C, false, AV_BLOCK8>,
-                                                       a.batch_blocks, l, a, s);
-          return hipErrorInvalidValue;
-        }
-        if (av == AV_STREAM64)
-          return launch_with_lds(batch_kernel<Q, C, true, AV_STREAM64>, a.batch_blocks, l, a, s);
-        return launch_with_lds(batch_kernel<Q, C, false, AV_STREAM16>, a.batch_blocks, l, a, s);
+        const int av = avg_variant(a.r);
+        if (av == AVG_R8)
+          return launch_with_lds(batch_kernel<Q, C, false, AVG_R8>, a.batch_blocks, l, a, s);
+        if (av == AVG_R64)
+          return launch_with_lds(batch_kernel<Q, C, true, AVG_R64>, a.batch_blocks, l, a, s);
+        return launch_with_lds(batch_kernel<Q, C, false, AVG_R16>, a.batch_blocks, l, a, s);
       }
       return hipErrorInvalidValue;
     case K_LR_APPLY:

@@ -181,6 +181,7 @@ struct LaunchArgs {
   float* out;            // moments / coefficients / output image
   void* ring;            // K_FUSED1 workspace (ring_t elements)
   int H, W, r;
+  int nq, nc;  // guides and channels
   int seg_rows, tiles_x, n_seg;
   int hchunk_m, hchunk_a;  // horizontal-pass chunk lengths (moments, averaging)
   float eps, eps_mul;
@@ -275,6 +276,9 @@ hipError_t launch_box_avgfields(const float* guides, const float* gout, int Q, i
 // dst[0..1] = sums over n entries of the interleaved pairs src[2i], src[2i+1]
 // (fixed order; one workgroup).
 hipError_t launch_pair_sum(const double* src, int n, double* dst, hipStream_t s);
+// Window average of the coefficient planes and reconstruction (a.planes ->
+// a.out, tiles of plan_avg), of one frame or (batch) of a.frames.
+hipError_t launch_avg(const LaunchArgs& a, bool batch, hipStream_t s);
 
 __host__ __device__ constexpr int num_sums(int Q, int C) {
   return Q + C + Q * (Q + 1) / 2 + Q * C;
@@ -283,67 +287,65 @@ __host__ __device__ constexpr int num_sums(int Q, int C) {
 // Output columns per strip for a walker kernel.
 inline int strip_out_cols(int kind, int r) {
   if (kind == K_FUSED1) return kThreads - 4 * r;
-  return kThreads - 2 * r;  // K_MOMENTS, K_FUSED0, K_APPLY_AVG
+  return kThreads - 2 * r;  // K_MOMENTS, K_FUSED0, K_COEFFS
 }
 
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-// Output rows per tile of the coefficient-averaging kernel (sizes its
-// per-lane register arrays and its LDS), and the workgroups of it that
-// registers and LDS let a CU hold.
-#ifndef FLR_AVG_TILE_ROWS
-#define FLR_AVG_TILE_ROWS 17
-#endif
-constexpr int kAvgTileRows = FLR_AVG_TILE_ROWS;
-constexpr int kAvgPerCU = kAvgTileRows <= 8 ? 4 : (kAvgTileRows <= 12 ? 3 : 2);
+// The coefficient-averaging kernel (flr_avg.hpp): wavefronts per workgroup,
+// rows a wavefront exchanges through LDS at a time, the output columns of a
+// tile (256 input columns, four per lane, less the window's 2r, in whole
+// lanes) and the largest tile height.
+// Prefix segments of 16 lanes (or columns) serve windows up to 2r + 1 = 17
+// columns wide.
+__host__ __device__ constexpr bool wide_segments(int r) { return r > 8; }
+constexpr int kAvgWaves = 4;
+constexpr int kAvgRowBatch = 2;
+constexpr int kAvgTileRows = 8;
+__host__ __device__ constexpr int avg_cols(int r) { return (256 - 2 * r) & ~3; }
+// First output column of strip sx: its input columns start r to the left, at
+// a multiple of 4 (strip 0's first outputs may lie left of the image).
+__host__ __device__ constexpr int avg_col0(int sx, int r) {
+  return sx * avg_cols(r) + r - ((r + 3) & ~3);
+}
+// LDS of a workgroup with tiles of `rows` rows: the wavefronts' exchange
+// rows, reused for their closing sums of `rows` rows.
+inline size_t avg_lds_bytes(int rows) {
+  return (size_t)kAvgWaves * (rows > 4 ? 8 : (rows > 2 ? 4 : 2)) * 256 * sizeof(double);
+}
+// Its forms by radius: r = 8 keeps a plane's rows of the tile in registers;
+// other radii load the rows entering and leaving the window; r > 8 needs
+// prefix segments of 64 columns.
+enum AvgVariant : int { AVG_R16 = 0, AVG_R64 = 1, AVG_R8 = 2 };
+__host__ __device__ constexpr int avg_variant(int r) {
+  return r == 8 ? AVG_R8 : (wide_segments(r) ? AVG_R64 : AVG_R16);
+}
 
-// XCDs of the GPU (workgroups are dealt to them round-robin), and the
-// workgroups of an averaging launch over `tiles` tiles: whole rounds of the
-// XCDs, so that each XCD runs a contiguous run of tiles (apply_avg_kernel).
+// XCDs of the GPU (workgroups are dealt to them round-robin), the averaging
+// workgroups of `tiles` tiles of C channels, and their launch range: whole
+// rounds of the XCDs, so that each XCD runs a contiguous run of them.
 constexpr int kXcds = 8;
-inline int avg_groups(int tiles) { return (tiles + kXcds - 1) / kXcds * kXcds; }
-
-// Workgroups of a walker kernel resident per CU (the coefficient-averaging
-// kernel's kAvgPerCU, one for the others).
-inline int workgroups_per_cu(int kind) { return kind == K_APPLY_AVG ? kAvgPerCU : 1; }
+inline int avg_workgroups(int tiles, int C) { return tiles * C; }
+inline int avg_groups(int tiles, int C) {
+  return (avg_workgroups(tiles, C) + kXcds - 1) / kXcds * kXcds;
+}
 
 // Rows of coefficient halo a walker recomputes above and below its segment.
 inline int row_halo(int kind, int r) { return kind == K_FUSED1 ? r : 0; }
 
 // Pick tiles and segments. With tile_rows > 0 the caller fixes the segment
 // length; otherwise minimise (workgroup waves) x (rows walked per segment).
-// K_MOMENTS, K_FUSED0, K_COEFFS and K_APPLY_AVG have no coefficient-row halo.
+// K_MOMENTS, K_FUSED0 and K_COEFFS have no coefficient-row halo.
 inline void plan_walk(int kind, int H, int W, int r, int tile_rows, int* tiles_x, int* n_seg,
                       int* seg_rows) {
   const int tout = strip_out_cols(kind, r);
   *tiles_x = ceil_div(W, tout);
-  const int rmax = kind == K_APPLY_AVG ? kAvgTileRows : H;
   if (tile_rows > 0) {
-    int t = tile_rows < H ? tile_rows : H;
-    *seg_rows = t < rmax ? t : rmax;
+    *seg_rows = tile_rows < H ? tile_rows : H;
     *n_seg = ceil_div(H, *seg_rows);
     return;
   }
-  if (kind == K_APPLY_AVG) {
-    // every tile reads its rows plus 2r halo rows of each coefficient plane
-    double best = 1e300;
-    int best_n = ceil_div(H, rmax);
-    for (int n = best_n; n <= H; ++n) {
-      const int R = ceil_div(H, n);
-      if (n > best_n && ceil_div(H, n - 1) == R) continue;
-      const double waves = (double)ceil_div(*tiles_x * n, kCUs * workgroups_per_cu(kind));
-      const double cost = waves * (double)(R + 2 * r) + 1e-3 * n;
-      if (cost < best) {
-        best = cost;
-        best_n = n;
-      }
-    }
-    *n_seg = best_n;
-    *seg_rows = ceil_div(H, best_n);
-    return;
-  }
   const int hc = row_halo(kind, r);
-  const int per_cu = workgroups_per_cu(kind);
   double best = 1e300;
   int best_n = 1;
   const int nmax = H < 4096 ? H : 4096;
@@ -351,7 +353,7 @@ inline void plan_walk(int kind, int H, int W, int r, int tile_rows, int* tiles_x
     const int R = ceil_div(H, n);
     if (n > 1 && ceil_div(H, n - 1) == R) continue;
     const int wgs = *tiles_x * n;
-    const double waves = (double)ceil_div(wgs, kCUs * per_cu);
+    const double waves = (double)ceil_div(wgs, kCUs);
     // rows solved per segment plus a share for the moment warm-up rows
     const double cost = waves * ((double)R + 2.0 * hc + 0.5 * r) + 1e-3 * n;
     if (cost < best) {
@@ -360,6 +362,30 @@ inline void plan_walk(int kind, int H, int W, int r, int tile_rows, int* tiles_x
     }
   }
   *seg_rows = ceil_div(H, best_n);
+  *n_seg = ceil_div(H, *seg_rows);
+}
+
+// Tiles of the averaging kernel: tile_rows, when set; else, for r <= 8, four
+// rows where they give kAvgMinGroups workgroups (tile and channel), so that
+// a plane row is fetched (4 + 2r) / 4 times instead of (2 + 2r) / 2, and two
+// rows below, where the shorter chain and the workgroup count win. Measured,
+// r = 8, 2 / 4 / 8 rows: 256 x 256, Q = 12, C = 3 16.8 / 17.8 / 19.6 us; 540p,
+// Q = 8 44 / 38 / 42; 1080p, Q = 8 176 / 135 / 132; 1440p 311 / 230 / 229
+// (eight rows take 242 registers, two wavefronts per SIMD, and gain nothing).
+// r > 8 (33 and more rows per window) takes eight rows on large frames, two
+// else: r = 16, 540p, C = 1 35 / 39 / 37; 1080p, C = 3 259 / 273 / 221.
+constexpr int kAvgMinGroups = 600;
+inline void plan_avg(int H, int W, int r, int C, int tile_rows, int* tiles_x, int* n_seg,
+                     int* seg_rows) {
+  *tiles_x = ceil_div(W - avg_col0(0, r), avg_cols(r));
+  const int tall = wide_segments(r) ? 8 : 4;
+  int t = 2;
+  if (tile_rows > 0)
+    t = tile_rows < kAvgTileRows ? tile_rows : kAvgTileRows;
+  else if ((int64_t)*tiles_x * ceil_div(H, tall) * C >= kAvgMinGroups)
+    t = tall;
+  if (W < 4 && t > 2) t = 2;
+  *seg_rows = t < H ? t : H;
   *n_seg = ceil_div(H, *seg_rows);
 }
 
@@ -403,12 +429,6 @@ __host__ __device__ constexpr WalkLayout walk_layout(int Q, int C, int kind, int
   const int row_s = kLdsStride * (int)sizeof(sum_t);
   const int row_t = kLdsStride * (int)sizeof(solve_t);
   WalkLayout L{0, 0, false, 0, 0, 0};
-  if (kind == K_APPLY_AVG) {
-    // two buffers of segment prefixes, one row per output row of the tile
-    L.ag = fc;
-    L.a = L.b = (size_t)kAvgTileRows * row_t;
-    return L;
-  }
   if (kind == K_FUSED1) {
     const int va = fc * row_t;
     const int left = kLdsBytes - 2 * va;  // Va region + destination sized for F*C rows
@@ -441,7 +461,7 @@ inline size_t walk_lds_bytes(int kind, int Q, int C, int ns_walk = -1) {
 // LDS of the persistent batch kernel: the larger of the walk's and the
 // averaging kernel's (its box items use the ring where it fits in that).
 inline size_t batch_lds_bytes(int Q, int C) {
-  const size_t w = walk_lds_bytes(K_COEFFS, Q, C), v = walk_lds_bytes(K_APPLY_AVG, Q, C);
+  const size_t w = walk_lds_bytes(K_COEFFS, Q, C), v = avg_lds_bytes(kAvgTileRows);
   return w > v ? w : v;
 }
 

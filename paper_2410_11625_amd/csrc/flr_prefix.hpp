@@ -8,6 +8,31 @@
 
 namespace flr {
 
+__device__ __forceinline__ int win_count(int i, int n, int r) {
+  const int lo = i - r < 0 ? 0 : i - r;
+  const int hi = i + r > n - 1 ? n - 1 : i + r;
+  return hi - lo + 1;
+}
+
+// 1/n for a window count n >= 1: the FP32 quotient, in FP64 refined by one
+// Newton step.
+__device__ __forceinline__ float recip_count(int n, float) { return 1.f / (float)n; }
+__device__ __forceinline__ double recip_count(int n, double) {
+  const double d = (double)n;
+  const double y = (double)(1.f / (float)n);
+  return fma(y, fma(-d, y, 1.0), y);
+}
+
+// The frame and local workgroup index of a batched launch (frames are few:
+// a scan of the workgroup offsets, uniform across the workgroup).
+__device__ __forceinline__ const LaunchArgs& batch_frame(const LaunchArgs& ain, int* bid) {
+  const int b = blockIdx.x;
+  int f = 0;
+  while (f + 1 < ain.nframes && ain.wg_start[f + 1] <= b) ++f;
+  *bid = b - ain.wg_start[f];
+  return ain.frames[f];
+}
+
 // Horizontal window sums by segmented prefix sums. Lane l holds the value x_l
 // of its column. An inclusive prefix over aligned segments of L lanes (L = 16,
 // one DPP row, when 2r <= 16; else L = 64, the wavefront) is formed in
@@ -83,9 +108,6 @@ __device__ __forceinline__ void seg_prefix_n(E (&x)[N]) {
     seg_step<kDppRowBcast31, 0xc>(x);  // rows 0..1 total -> 2, 3
   }
 }
-
-// Prefix segments of 16 lanes serve windows up to 2r + 1 = 17 columns wide.
-__host__ __device__ constexpr bool wide_segments(int r) { return r > 8; }
 
 // LDS columns whose prefixes give the sum of window [j, j + 2r]:
 // P[ib] - P[ia] + P[it]. Terms that do not apply point at the row's pad
