@@ -17,7 +17,6 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
-#include <stdlib.h>
 
 #include "flr.h"
 #include "flr_net.h"
@@ -711,141 +710,74 @@ namespace flrnet {
 
 // Backward workspace: the forward's activation buffers (act_layout), then
 // in3's and out3's activations (fused away in the forward), the sigmoid
-// output, the BF16-rounded weights, the FP32 gradient tensors and the
-// weight-gradient partials.
+// output, the data-gradient weights, the FP32 gradient tensors and the
+// weight gradients' partial sums (every layer's: they are formed in one
+// launch).
 enum BwdBuf : int {
-  B_A, B_T6, B_SIG, B_WR, B_DZ1, B_GT6, B_GT5, B_GT4, B_G48, B_GD1, B_GT3, B_G96, B_GE2, B_GT2,
-  B_GE1, B_GT1, B_GE0, B_GA, B_PART, B_COUNT
+  B_A, B_T6, B_SIG, B_WD, B_DZ1, B_GT6, B_GT5, B_GT4, B_G48, B_GT3, B_G96, B_GT2, B_GE1, B_GT1,
+  B_GE0, B_GA, B_PART, B_COUNT
 };
-// Output grid of each layer: 0 full, 1 half, 2 quarter.
+// Input and output grid of each layer: 0 full, 1 half, 2 quarter.
+constexpr int kInGrid[12] = {0, 0, 0, 0, 1, 1, 1, 1, 0, 0, 0, 0};
 constexpr int kOutGrid[12] = {0, 0, 0, 1, 1, 2, 1, 1, 0, 0, 0, 0};
 
-inline size_t grid_px(const Grids& g, int which) {
-  return which == 0 ? (size_t)g.H * g.W : which == 1 ? (size_t)g.Hh * g.Wh : (size_t)g.Hq * g.Wq;
+inline int grid_h(const Grids& g, int which) { return which == 0 ? g.H : which == 1 ? g.Hh : g.Hq; }
+inline int grid_w(const Grids& g, int which) { return which == 0 ? g.W : which == 1 ? g.Wh : g.Wq; }
+
+// Layers with a data gradient through dgrad_kernel: all but the first (its
+// input is the network's) and the last (head_bwd_kernel).
+inline bool has_dgrad(int li) { return li >= 1 && li <= 10; }
+// First data-gradient fragment of layer i (i = 12: their count).
+inline size_t dfrag_offset(int i) {
+  size_t o = 0;
+  for (int j = 0; j < i; ++j)
+    if (has_dgrad(j)) o += frag_count(kLayers[j]);
+  return o;
 }
 
 inline void bwd_layout(const Grids& g, size_t off[B_COUNT + 1]) {
   size_t act[kActBufs + 1];
   act_layout(g, act);
-  const size_t F = grid_px(g, 0), Hf = grid_px(g, 1), Q = grid_px(g, 2);
+  const size_t F = (size_t)g.H * g.W, Hf = (size_t)g.Hh * g.Wh;
   size_t part = 0;
   for (int li = 0; li < 12; ++li) {
-    const WgradPlan wp = wgrad_plan(kLayers[li], stored_cin_blocks(li), grid_px(g, kOutGrid[li]));
-    const size_t S = (size_t)wp.ne * kWgAcc + kLayers[li].cout;
-    const size_t n = ((size_t)wp.nchunk + (wp.nchunk + kChunkGroup - 1) / kChunkGroup) * S;
-    if (n > part) part = n;
+    const WgradPlan wp = wgrad_plan(kLayers[li], grid_h(g, kOutGrid[li]), grid_w(g, kOutGrid[li]));
+    part += wgrad_part_floats(kLayers[li], wp);
   }
-  const size_t sz[B_COUNT] = {16 * F * 2,  16 * F * 2,  4 * F * 4,   param_offset(12) * 4,
+  const size_t sz[B_COUNT] = {16 * F * 2,  16 * F * 2,  4 * F * 4,   dfrag_offset(12) * 8,
                               4 * F * 4,   16 * F * 4,  16 * F * 4,  16 * F * 4,
-                              48 * F * 4,  32 * Hf * 4, 32 * Hf * 4, 96 * Hf * 4,
-                              64 * Q * 4,  64 * Hf * 4, 32 * Hf * 4, 32 * F * 4,
-                              16 * F * 4,  16 * F * 4,  part * 4};
+                              48 * F * 4,  32 * Hf * 4, 96 * Hf * 4, 64 * Hf * 4,
+                              32 * Hf * 4, 32 * F * 4,  16 * F * 4,  16 * F * 4,
+                              part * 4};
   off[0] = act[kActBufs];
   for (int i = 0; i < B_COUNT; ++i) off[i + 1] = off[i] + align256(sz[i]);
 }
 
-// Weight and bias gradients of layer li: chunked partials, then the
-// fixed-order sum into grad (+= when accumulate).
-hipError_t layer_wgrad(int li, const Grids& g, const float* gout, const uint16_t* act,
-                       const BwdSrc& src, int Hi, int Wi, float* part, float* grad, int accumulate,
-                       hipStream_t s) {
-  const Layer& L = kLayers[li];
-  const int ncb = stored_cin_blocks(li);
-  const int og = kOutGrid[li];
-  const int Ho = og == 0 ? g.H : og == 1 ? g.Hh : g.Hq, Wo = og == 0 ? g.W : og == 1 ? g.Wh : g.Wq;
-  const WgradPlan wp = wgrad_plan(L, ncb, (size_t)Ho * Wo);
-  WgradArgs a = {};
-  a.g = gout;
-  a.act = act;
-  a.src = src;
-  a.Hi = Hi;
-  a.Wi = Wi;
-  a.Ho = Ho;
-  a.Wo = Wo;
-  a.cout = L.cout;
-  a.ncb = ncb;
-  a.k = L.k;
-  a.stride = L.stride;
-  a.ne = wp.ne;
-  a.chunk_px = wp.chunk_px;
-  a.part = part;
-  if (L.k == 3)
-    hipLaunchKernelGGL(wgrad_kernel<3>, dim3(wp.nchunk, wp.wg_y), dim3(256), wgrad_lds_bytes(), s,
-                       a);
-  else
-    hipLaunchKernelGGL(wgrad_kernel<1>, dim3(wp.nchunk, wp.wg_y), dim3(256), wgrad_lds_bytes(), s,
-                       a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // two-level fixed-order sum over the chunks: groups of kChunkGroup, then the groups
-  const int S = wp.ne * kWgAcc + L.cout;
-  const int ng = (wp.nchunk + kChunkGroup - 1) / kChunkGroup;
-  float* groups = part + (size_t)wp.nchunk * S;
-  const ChunkSumArgs c = {part, groups, S, wp.nchunk};
-  const size_t nc = (size_t)ng * S;
-  hipLaunchKernelGGL(chunk_sum_kernel, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, c);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const WreduceArgs r = {groups, ng, wp.ne, ncb, L.cin, L.cout, L.k, grad + param_offset(li),
-                         accumulate};
-  hipLaunchKernelGGL(wreduce_kernel, dim3((S + 255) / 256), dim3(256), 0, s, r);
+// Data gradient of a layer. Workgroups take two 16-channel blocks of dx
+// (the staged tile serves both) and 64 pixels of four rows; on grids that
+// would leave most CUs idle 32 pixels (kDgNarrowGroups workgroups of 64).
+constexpr int kDgNarrowGroups = 256;
+template <int CIN, int COUT, int KS, int ST, int CBG, int NT>
+hipError_t launch_dgrad_nt(const DgradArgs& a, hipStream_t s) {
+  // tiles of dx pixels (stride 2: of the coarse grid covering dx)
+  const int Ht = (a.Hi + ST - 1) / ST, Wt = (a.Wi + ST - 1) / ST;
+  hipLaunchKernelGGL((dgrad_kernel<CIN, COUT, KS, ST, CBG, NT>),
+                     dim3((Wt + 16 * NT - 1) / (16 * NT) * (CIN / 16 / CBG), (Ht + 3) / 4), dim3(256),
+                     (dgrad_lds_bytes<KS, ST, NT>()), s, a);
   return hipGetLastError();
 }
-
-// Pixel count from which the data gradients take 16 input channels per
-// thread: FLR_DGRAD_WIDE_PX from the environment when it holds a number (a
-// tuning knob; the gradients are bit-identical either way, the sum order per
-// channel being the same), else kDgWidePx.
-static size_t dgrad_wide_px() {
-  const char* e = getenv("FLR_DGRAD_WIDE_PX");
-  if (e && *e) {
-    char* end = nullptr;
-    const long long v = strtoll(e, &end, 10);
-    if (end && *end == 0 && v >= 0) return (size_t)v;
+template <int CIN, int COUT, int KS, int ST>
+hipError_t launch_dgrad(const DgradArgs& a, hipStream_t s) {
+  constexpr int CBG = CIN % 32 == 0 ? 2 : 1;
+  const int Ht = (a.Hi + ST - 1) / ST, Wt = (a.Wi + ST - 1) / ST;
+  const int wide = (Wt + 63) / 64 * ((Ht + 3) / 4) * (CIN / 16 / CBG);
+  if constexpr (ST == 1) {
+    if (wide >= kDgNarrowGroups) return launch_dgrad_nt<CIN, COUT, KS, ST, CBG, 4>(a, s);
+    return launch_dgrad_nt<CIN, COUT, KS, ST, CBG, 2>(a, s);
+  } else {  // four parities' sums per pixel: 32 pixels, or 16
+    if (wide >= kDgNarrowGroups) return launch_dgrad_nt<CIN, COUT, KS, ST, CBG, 2>(a, s);
+    return launch_dgrad_nt<CIN, COUT, KS, ST, CBG, 1>(a, s);
   }
-  return kDgWidePx;
-}
-
-// Gradient of layer li's input (channels 0..cin-1, HWC FP32 into dx), plus
-// an optional addend tensor's channels.
-hipError_t layer_dgrad(int li, const Grids& g, const float* gout, const uint16_t* act,
-                       const float* wr, int Hi, int Wi, float* dx, const float* add, int add_cs,
-                       int add_off, hipStream_t s) {
-  const Layer& L = kLayers[li];
-  const size_t n = (size_t)Hi * Wi;
-  const int cpt = n >= dgrad_wide_px() ? 16 : 8;
-  if (L.cin % cpt) return hipErrorInvalidValue;  // whole channel groups per thread
-  const int og = kOutGrid[li];
-  DgradArgs a = {};
-  a.g = gout;
-  a.act = act;
-  a.w = wr + param_offset(li);
-  a.cin = L.cin;
-  a.cout = L.cout;
-  a.k = L.k;
-  a.stride = L.stride;
-  a.Hi = Hi;
-  a.Wi = Wi;
-  a.Ho = og == 0 ? g.H : og == 1 ? g.Hh : g.Hq;
-  a.Wo = og == 0 ? g.W : og == 1 ? g.Wh : g.Wq;
-  a.dx = dx;
-  a.add = add;
-  a.add_cs = add_cs;
-  a.add_off = add_off;
-  if (cpt == 16)
-    hipLaunchKernelGGL(dgrad_kernel<16>, dim3((unsigned)((n + 255) / 256), L.cin / 16), dim3(256),
-                       dgrad_lds_bytes(L, 16), s, a);
-  else
-    hipLaunchKernelGGL(dgrad_kernel<8>, dim3((unsigned)((n + 255) / 256), L.cin / 8), dim3(256),
-                       dgrad_lds_bytes(L, 8), s, a);
-  return hipGetLastError();
-}
-
-hipError_t up2_bwd(const float* fine, int H, int W, int cs, float* low, int Hl, int Wl, int nc,
-                   hipStream_t s) {
-  const size_t n = (size_t)Hl * Wl * nc;
-  const Up2BwdArgs a = {fine, H, W, cs, low, Hl, Wl, nc};
-  hipLaunchKernelGGL(up2_bwd_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
-  return hipGetLastError();
 }
 
 flr_status run_backward(const Grids& g, const float* guides, const float* noisy,
@@ -860,57 +792,97 @@ flr_status run_backward(const Grids& g, const float* guides, const float* noisy,
            *e2 = abuf(5), *t3 = abuf(6), *d1 = abuf(7), *t4 = abuf(8), *t5 = abuf(9);
   uint16_t* a16 = reinterpret_cast<uint16_t*>(ws + off[B_A]);
   uint16_t* t6 = reinterpret_cast<uint16_t*>(ws + off[B_T6]);
-  float *sig = fbuf(B_SIG), *wr = fbuf(B_WR), *part = fbuf(B_PART);
-  const int F = (int)grid_px(g, 0);
-  const int np = (int)param_offset(12);
+  bf16x4_t* wd = reinterpret_cast<bf16x4_t*>(ws + off[B_WD]);
+  float* sig = fbuf(B_SIG);
+  const int F = g.H * g.W;
 
-  const RoundArgs ra = {params, wr, np};
-  hipLaunchKernelGGL(round_params_kernel, dim3((np + 255) / 256), dim3(256), 0, s, ra);
+  BwdPackArgs pk = {};
+  pk.params = params;
+  pk.out = wd;
+  for (int li = 0; li < 12; ++li) {
+    pk.first[li] = (int)dfrag_offset(li);
+    pk.param[li] = (int)param_offset(li);
+    pk.cin[li] = kLayers[li].cin;
+    pk.cout[li] = kLayers[li].cout;
+    pk.k[li] = kLayers[li].k;
+  }
+  pk.first[12] = (int)dfrag_offset(12);
+  hipLaunchKernelGGL(bwd_pack_kernel, dim3((pk.first[12] + 255) / 256), dim3(256), 0, s, pk);
   if (hipGetLastError() != hipSuccess) return FLR_ERR_HIP;
   // the forward, also storing in3's and out3's activations
   flr_status st = run_forward(g, guides, noisy, packed, sig, ws, s, a16, t6);
   if (st != FLR_OK) return st;
-  const SigmoidBwdArgs sa = {dout, sig, fbuf(B_DZ1), F, FLR_NET_OUT};
-  hipLaunchKernelGGL(sigmoid_bwd_kernel, dim3((F + 255) / 256), dim3(256), 0, s, sa);
+  const HeadBwdArgs ha = {dout, sig, params + param_offset(11), fbuf(B_DZ1), fbuf(B_GT6), F};
+  hipLaunchKernelGGL(head_bwd_kernel, dim3((F + 255) / 256), dim3(256), 0, s, ha);
   if (hipGetLastError() != hipSuccess) return FLR_ERR_HIP;
 
+  // each layer's dz (output gradient and ReLU mask) and input
+  auto dzs = [](const float* go, const uint16_t* ac, int cout) {
+    return DzSrc{go, ac, cout, cout, 0, 0, 0};
+  };
+  auto up2 = [](const float* go, const uint16_t* ac, int cs, int cout, int Hf, int Wf) {
+    return DzSrc{go, ac, cs, cout, 1, Hf, Wf};
+  };
   auto plain = [](const uint16_t* in, int cs) { return BwdSrc{in, nullptr, cs, cs, 0, 0}; };
-  const BwdSrc cat48 = {d1, e0, 32, 32, 16, g.Wh};
-  const BwdSrc cat96 = {e2, e1, 64, 64, 32, g.Wq};
+  const DzSrc dz[12] = {
+      dzs(fbuf(B_GA), a16, 16),  dzs(fbuf(B_GE0), e0, 16), dzs(fbuf(B_GT1), t1, 32),
+      dzs(fbuf(B_GE1), e1, 32),  dzs(fbuf(B_GT2), t2, 64),
+      up2(fbuf(B_G96), e2, 96, 64, g.Hh, g.Wh),  // e2 through up2 and d1a
+      dzs(fbuf(B_GT3), t3, 32),
+      up2(fbuf(B_G48), d1, 48, 32, g.H, g.W),    // d1 through up2 and d0a
+      dzs(fbuf(B_GT4), t4, 16),  dzs(fbuf(B_GT5), t5, 16), dzs(fbuf(B_GT6), t6, 16),
+      dzs(fbuf(B_DZ1), nullptr, FLR_NET_OUT)};
+  const BwdSrc src[12] = {
+      plain(x0, 16), plain(a16, 16), plain(e0, 16), plain(t1, 32), plain(e1, 32), plain(t2, 64),
+      BwdSrc{e2, e1, 64, 64, 32, g.Wq}, plain(t3, 32), BwdSrc{d1, e0, 32, 32, 16, g.Wh},
+      plain(t4, 16), plain(t5, 16), plain(t6, 16)};
   bool ok = true;
-  auto W = [&](int li, const float* go, const uint16_t* ac, const BwdSrc& src, int Hi, int Wi) {
-    ok = ok && layer_wgrad(li, g, go, ac, src, Hi, Wi, part, grad, accumulate, s) == hipSuccess;
+  auto D = [&](auto kernel, int li, float* dx, const float* add = nullptr, int add_cs = 0,
+               int add_off = 0) {
+    DgradArgs a = {};
+    a.dz = dz[li];
+    a.w = wd + dfrag_offset(li);
+    a.Hi = grid_h(g, kInGrid[li]);
+    a.Wi = grid_w(g, kInGrid[li]);
+    a.Ho = grid_h(g, kOutGrid[li]);
+    a.Wo = grid_w(g, kOutGrid[li]);
+    a.dx = dx;
+    a.add = add;
+    a.add_cs = add_cs;
+    a.add_off = add_off;
+    ok = ok && kernel(a, s) == hipSuccess;
   };
-  auto D = [&](int li, const float* go, const uint16_t* ac, int Hi, int Wi, float* dx,
-               const float* add = nullptr, int add_cs = 0, int add_off = 0) {
-    ok = ok && layer_dgrad(li, g, go, ac, wr, Hi, Wi, dx, add, add_cs, add_off, s) == hipSuccess;
-  };
-  // out1 (sigmoid head, no mask) and the layers back to in3, as in the forward reversed
-  W(11, fbuf(B_DZ1), nullptr, plain(t6, 16), g.H, g.W);
-  D(11, fbuf(B_DZ1), nullptr, g.H, g.W, fbuf(B_GT6));
-  W(10, fbuf(B_GT6), t6, plain(t5, 16), g.H, g.W);
-  D(10, fbuf(B_GT6), t6, g.H, g.W, fbuf(B_GT5));
-  W(9, fbuf(B_GT5), t5, plain(t4, 16), g.H, g.W);
-  D(9, fbuf(B_GT5), t5, g.H, g.W, fbuf(B_GT4));
-  W(8, fbuf(B_GT4), t4, cat48, g.H, g.W);
-  D(8, fbuf(B_GT4), t4, g.H, g.W, fbuf(B_G48));
-  ok = ok && up2_bwd(fbuf(B_G48), g.H, g.W, 48, fbuf(B_GD1), g.Hh, g.Wh, 32, s) == hipSuccess;
-  W(7, fbuf(B_GD1), d1, plain(t3, 32), g.Hh, g.Wh);
-  D(7, fbuf(B_GD1), d1, g.Hh, g.Wh, fbuf(B_GT3));
-  W(6, fbuf(B_GT3), t3, cat96, g.Hh, g.Wh);
-  D(6, fbuf(B_GT3), t3, g.Hh, g.Wh, fbuf(B_G96));
-  ok = ok && up2_bwd(fbuf(B_G96), g.Hh, g.Wh, 96, fbuf(B_GE2), g.Hq, g.Wq, 64, s) == hipSuccess;
-  W(5, fbuf(B_GE2), e2, plain(t2, 64), g.Hh, g.Wh);
-  D(5, fbuf(B_GE2), e2, g.Hh, g.Wh, fbuf(B_GT2));
-  W(4, fbuf(B_GT2), t2, plain(e1, 32), g.Hh, g.Wh);
-  D(4, fbuf(B_GT2), t2, g.Hh, g.Wh, fbuf(B_GE1), fbuf(B_G96), 96, 64);
-  W(3, fbuf(B_GE1), e1, plain(t1, 32), g.H, g.W);
-  D(3, fbuf(B_GE1), e1, g.H, g.W, fbuf(B_GT1));
-  W(2, fbuf(B_GT1), t1, plain(e0, 16), g.H, g.W);
-  D(2, fbuf(B_GT1), t1, g.H, g.W, fbuf(B_GE0), fbuf(B_G48), 48, 32);
-  W(1, fbuf(B_GE0), e0, plain(a16, 16), g.H, g.W);
-  D(1, fbuf(B_GE0), e0, g.H, g.W, fbuf(B_GA));
-  W(0, fbuf(B_GA), a16, plain(x0, 16), g.H, g.W);
+  // from out3 back to in1, as in the forward reversed
+  D(launch_dgrad<16, 16, 3, 1>, 10, fbuf(B_GT5));
+  D(launch_dgrad<16, 16, 3, 1>, 9, fbuf(B_GT4));
+  D(launch_dgrad<48, 16, 3, 1>, 8, fbuf(B_G48));
+  D(launch_dgrad<32, 32, 3, 1>, 7, fbuf(B_GT3));
+  D(launch_dgrad<96, 32, 3, 1>, 6, fbuf(B_G96));
+  D(launch_dgrad<64, 64, 3, 2>, 5, fbuf(B_GT2));
+  D(launch_dgrad<32, 64, 3, 1>, 4, fbuf(B_GE1), fbuf(B_G96), 96, 64);
+  D(launch_dgrad<32, 32, 3, 2>, 3, fbuf(B_GT1));
+  D(launch_dgrad<16, 32, 3, 1>, 2, fbuf(B_GE0), fbuf(B_G48), 48, 32);
+  D(launch_dgrad<16, 16, 1, 1>, 1, fbuf(B_GA));
+  // every layer's weight and bias gradients
+  WgradArgs w = {};
+  w.accumulate = accumulate;
+  float* part = fbuf(B_PART);
+  for (int li = 0; li < 12; ++li) {
+    const Layer& L = kLayers[li];
+    const int Ho = grid_h(g, kOutGrid[li]), Wo = grid_w(g, kOutGrid[li]);
+    const WgradPlan p = wgrad_plan(L, Ho, Wo);
+    w.layer[li] = WgradLayer{dz[li], src[li], grid_h(g, kInGrid[li]), grid_w(g, kInGrid[li]), Ho,
+                             Wo, p.ncb, p.npair, L.k, L.stride, p.tiles_x, p.ntile, p.chunk,
+                             p.nchunk, part, L.cin, L.cout, grad + param_offset(li)};
+    part += wgrad_part_floats(L, p);
+    w.first[li + 1] = w.first[li] + p.nchunk * p.npair;
+    w.rfirst[li + 1] = w.rfirst[li] + p.npair * (L.k * L.k * 256 + 16);
+  }
+  hipLaunchKernelGGL(wgrad_kernel, dim3(w.first[12]), dim3(256), wgrad_lds_bytes(), s, w);
+  ok = ok && hipGetLastError() == hipSuccess;
+  hipLaunchKernelGGL(wreduce_kernel, dim3((w.rfirst[12] + 63) / 64), dim3(256),
+                     4 * 64 * sizeof(float), s, w);
+  ok = ok && hipGetLastError() == hipSuccess;
   return ok ? FLR_OK : FLR_ERR_HIP;
 }
 }  // namespace flrnet

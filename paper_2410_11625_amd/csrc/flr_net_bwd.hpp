@@ -4,8 +4,8 @@
 // Straight-through reading of the BF16 network: the backward treats every
 // BF16 rounding of the forward as the identity, so the gradients are those of
 // the exact network evaluated at the BF16 weights and activations the forward
-// produced. All backward arithmetic is FP32; gradients between layers are FP32
-// HWC tensors ([pixel][channel]).
+// produced. Gradients between layers are FP32 HWC tensors ([pixel][channel]),
+// products and sums FP32 on the matrix cores.
 //
 //   ReLU layer      dz = g * [a > 0], a the stored BF16 activation (a > 0
 //                   exactly when the FP32 pre-activation is > 0: BF16 keeps
@@ -18,41 +18,272 @@
 //   up2 + concat    the coarse tensor collects the gradients of the 2x2 fine
 //                   pixels that copied it; the skip takes its channels as is
 //
-// Weight gradients reduce over every output pixel: each workgroup sums one
-// pixel chunk into a partial, and a second kernel adds the chunks in a fixed
-// order, so the result does not depend on scheduling.
+// Launches: the head, one data gradient per layer (each needs the one before),
+// then every layer's weight gradient in one launch (they only need the stored
+// dz and activations), and one launch that adds the weight gradients' partial
+// sums in a fixed order, so the result does not depend on scheduling.
+//
+// What bounds it: at a training crop's sizes the chain of data gradients (ten
+// launches of 6 to 22 us, most of them with fewer workgroups than the chip has
+// room for) and the weight gradients' FP32 matrix instructions. Measured at
+// 256 x 256 against FP32 vector kernels (one thread per pixel and 8 channels of
+// dx, one wave per 4 x 8 channels of a weight gradient's taps, 48 launches):
+// data gradients 435 -> 152 us, weight gradients and their sums 480 -> 98 us,
+// the whole call 962 -> 379 us, 137 us of it the recomputed forward.
 
 namespace flrnet {
 
-constexpr int kWgOB = 4;  // output channels per weight-gradient entry
-constexpr int kWgCB = 8;  // input channels per weight-gradient entry
-constexpr int kWgAcc = kWgOB * kWgCB;
-
-// wr[i] = BF16 rounding of p[i] (the weights the forward multiplies by).
-struct RoundArgs {
-  const float* p;
-  float* wr;
-  int n;
+// Data-gradient weights: BF16 fragments of W^T (rows: input channels c, K:
+// output channels o), layer after layer, (tap, o block, c block, lane) of 4
+// BF16: lane l holds input channel 16 cb + l % 16 and output channels
+// 16 ob + 4 (l / 16) .. + 3.
+struct BwdPackArgs {
+  const float* params;
+  bf16x4_t* out;
+  int first[13];  // first fragment of each layer (equal: none)
+  int param[12];  // first parameter of each layer
+  int cin[12], cout[12], k[12];
 };
-__global__ void __launch_bounds__(256) round_params_kernel(RoundArgs a) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < a.n) a.wr[i] = bf2f(f2bf(a.p[i]));
+__global__ void __launch_bounds__(256) bwd_pack_kernel(BwdPackArgs a) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= a.first[12]) return;
+  int li = 0;
+  while (idx >= a.first[li + 1]) ++li;
+  const int i = idx - a.first[li];
+  const int cin = a.cin[li], cout = a.cout[li], k = a.k[li];
+  const int ncb = (cin + 15) / 16, nob = (cout + 15) / 16;
+  const int lane = i & 63, cb = (i >> 6) % ncb, ob = (i >> 6) / ncb % nob;
+  const int tap = (i >> 6) / ncb / nob;
+  const int c = cb * 16 + (lane & 15);
+  const float* w = a.params + a.param[li];
+  uint16_t h[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int o = ob * 16 + 4 * (lane >> 4) + j;
+    h[j] = o < cout && c < cin ? f2bf(w[((size_t)o * cin + c) * k * k + tap]) : (uint16_t)0;
+  }
+  a.out[idx] = pack4(h[0], h[1], h[2], h[3]);
 }
 
-// dz[q][o] = dout[o][q] s (1 - s), s = sig[o][q] (planar in, HWC out).
-struct SigmoidBwdArgs {
+// dz1[q][o] = dout[o][q] s (1 - s), s = sig[o][q] (planar in, HWC out): the
+// sigmoid head's gradient; and the gradient of its input, the 16 channels
+// of out3's output, gt[q][c] = sum_o W[o][c] dz1[q][o] with the BF16-rounded
+// weights.
+struct HeadBwdArgs {
   const float* dout;
   const float* sig;
-  float* dz;
-  int npx, nout;
+  const float* w;  // [4][16]
+  float* dz1;
+  float* gt;
+  int npx;
 };
-__global__ void __launch_bounds__(256) sigmoid_bwd_kernel(SigmoidBwdArgs a) {
+__global__ void __launch_bounds__(256) head_bwd_kernel(HeadBwdArgs a) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= a.npx) return;
-  for (int o = 0; o < a.nout; ++o) {
+  float d[FLR_NET_OUT];
+#pragma unroll
+  for (int o = 0; o < FLR_NET_OUT; ++o) {
     const float s = a.sig[(size_t)o * a.npx + q];
-    a.dz[(size_t)q * a.nout + o] = a.dout[(size_t)o * a.npx + q] * s * (1.f - s);
+    d[o] = a.dout[(size_t)o * a.npx + q] * s * (1.f - s);
   }
+  *reinterpret_cast<float4*>(a.dz1 + (size_t)q * FLR_NET_OUT) = float4{d[0], d[1], d[2], d[3]};
+#pragma unroll
+  for (int c = 0; c < 16; c += 4) {
+    float g[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float s = 0.f;
+#pragma unroll
+      for (int o = 0; o < FLR_NET_OUT; ++o) s += bf2f(f2bf(a.w[o * 16 + c + i])) * d[o];
+      g[i] = s;
+    }
+    *reinterpret_cast<float4*>(a.gt + (size_t)q * 16 + c) = float4{g[0], g[1], g[2], g[3]};
+  }
+}
+
+// dz of a layer: the gradient g of its output activation (HWC, channel stride
+// cs), masked by the stored activation where act is given. up: g is the
+// gradient of the 2x upsampled copy, on a grid of Hf x Wf pixels; the coarse
+// pixel takes the sum of its (up to four) fine pixels.
+struct DzSrc {
+  const float* g;
+  const uint16_t* act;  // [pixel][cout]
+  int cs, cout;
+  int up, Hf, Wf;
+};
+
+// Four channels o .. o + 3 at pixel (y, x) of the H x W grid (clamped by the
+// caller); zero past cout.
+__device__ __forceinline__ float4 load_dz4(const DzSrc& s, int y, int x, int W, int o) {
+  if (o >= s.cout) return float4{0.f, 0.f, 0.f, 0.f};
+  float4 d;
+  if (s.up) {
+    d = float4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int di = 0; di < 2; ++di)
+#pragma unroll
+      for (int dj = 0; dj < 2; ++dj) {
+        const int fy = 2 * y + di, fx = 2 * x + dj;
+        const bool ok = fy < s.Hf && fx < s.Wf;
+        const size_t q = (size_t)(fy < s.Hf ? fy : s.Hf - 1) * s.Wf + (fx < s.Wf ? fx : s.Wf - 1);
+        const float4 t = *reinterpret_cast<const float4*>(s.g + q * s.cs + o);
+        d.x += ok ? t.x : 0.f;
+        d.y += ok ? t.y : 0.f;
+        d.z += ok ? t.z : 0.f;
+        d.w += ok ? t.w : 0.f;
+      }
+  } else {
+    d = *reinterpret_cast<const float4*>(s.g + ((size_t)y * W + x) * s.cs + o);
+  }
+  if (s.act) {
+    const uint2 a = *reinterpret_cast<const uint2*>(s.act + ((size_t)y * W + x) * s.cout + o);
+    d.x = (a.x & 0xffffu) != 0 && !(a.x & 0x8000u) ? d.x : 0.f;
+    d.y = (a.x >> 16) != 0 && !(a.x & 0x80000000u) ? d.y : 0.f;
+    d.z = (a.y & 0xffffu) != 0 && !(a.y & 0x8000u) ? d.z : 0.f;
+    d.w = (a.y >> 16) != 0 && !(a.y & 0x80000000u) ? d.w : 0.f;
+  }
+  return d;
+}
+
+// x = hi + mid + lo exactly (24 bits in three BF16, each the truncation of
+// what is left); infinities and NaN stay in hi alone.
+__device__ __forceinline__ void split3(float x, uint16_t (&h)[3]) {
+  const uint32_t u = __float_as_uint(x);
+  const bool fin = (u & 0x7f800000u) != 0x7f800000u;
+  const float r1 = fin ? x - __uint_as_float(u & 0xffff0000u) : 0.f;
+  const uint32_t u1 = __float_as_uint(r1);
+  const float r2 = r1 - __uint_as_float(u1 & 0xffff0000u);
+  // a NaN whose set bits all lie in the low half must stay one
+  h[0] = (uint16_t)((u >> 16) | ((u & 0x7fffffffu) > 0x7f800000u ? 0x40u : 0u));
+  h[1] = (uint16_t)(u1 >> 16);
+  h[2] = (uint16_t)(__float_as_uint(r2) >> 16);
+}
+
+struct DgradArgs {
+  DzSrc dz;
+  const bf16x4_t* w;  // the layer's data-gradient fragments
+  int Hi, Wi, Ho, Wo;
+  float* dx;          // [Hi*Wi][cin]
+  const float* add;   // optional addend add[p * add_cs + add_off + c]
+  int add_cs, add_off;
+};
+
+// Data gradient of one layer (CIN channels of dx from COUT of dz, both
+// multiples of 16; kernel KS, stride ST) as an implicit GEMM on the BF16
+// matrix cores: D (c x pixels) += W^T (c x o) dz (o x pixels). The weights are
+// BF16 as they are; dz is FP32 and is split exactly into three BF16 parts
+// when it is staged, three products each, accumulated in FP32: the error is
+// that of FP32 sums. (The FP32 matrix instruction runs at a sixteenth of the
+// BF16 rate: three BF16 products are the cheaper way to FP32.)
+//
+// A workgroup of four waves computes CBG 16-channel blocks of dx for four
+// rows (stride 2: four coarse rows, both row and both column parities) of
+// 16 NT pixels; per 16 output channels it stages the dz tile with its halo in
+// LDS (three planes of HWC BF16, zero outside the grid) and runs the taps.
+template <int CIN, int COUT, int KS, int ST, int CBG, int NT>
+__global__ void __launch_bounds__(256) dgrad_kernel(DgradArgs a) {
+  constexpr int NCB = CIN / 16, NOB = COUT / 16;
+  constexpr int HALO = KS == 1 ? 0 : (ST == 1 ? 2 : 1);  // staged rows and columns beyond the tile
+  constexpr int LO = KS == 3 && ST == 1 ? 1 : 0;         // of which before it
+  constexpr int SR = 4 + HALO, SP = 16 * NT + HALO;
+  constexpr int NPAR = ST * ST, NCG = NCB / CBG;
+  bf16x4_t* st = reinterpret_cast<bf16x4_t*>(flr::lds);  // [3][SR][SP][4]
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, kq = lane >> 4;
+  const int x0 = blockIdx.x / NCG * 16 * NT, y0 = blockIdx.y * 4, cb0 = blockIdx.x % NCG * CBG;
+  f32x4_t acc[NPAR][NT][CBG];
+#pragma unroll
+  for (int p = 0; p < NPAR; ++p)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int cb = 0; cb < CBG; ++cb) acc[p][t][cb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int ob = 0; ob < NOB; ++ob) {
+    if (ob > 0) __syncthreads();  // the previous block's tile has been read
+    constexpr int NIT = SR * SP * 4, B = 4;
+    for (int b0 = 0; b0 < NIT; b0 += B * 256) {
+      float4 d[B];
+      bool ok[B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int i = b0 + u * 256 + tid, ic = i < NIT ? i : NIT - 1;
+        const int pix = ic >> 2, q = ic & 3;
+        const int sr = pix / SP, sx = pix - sr * SP;
+        const int y = y0 - LO + sr, x = x0 - LO + sx;
+        ok[u] = y >= 0 && y < a.Ho && x >= 0 && x < a.Wo;
+        d[u] = load_dz4(a.dz, min(max(y, 0), a.Ho - 1), min(max(x, 0), a.Wo - 1), a.Wo,
+                        ob * 16 + 4 * q);
+      }
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int i = b0 + u * 256 + tid;
+        const float v[4] = {d[u].x, d[u].y, d[u].z, d[u].w};
+        uint16_t h[4][3];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) split3(ok[u] ? v[j] : 0.f, h[j]);
+        if (i < NIT) {
+#pragma unroll
+          for (int s = 0; s < 3; ++s)
+            st[s * NIT + i] = pack4(h[0][s], h[1][s], h[2][s], h[3][s]);
+        }
+      }
+    }
+    __syncthreads();
+    // tap (u, v): stride 1 reads dz at (+1 - u, +1 - v); stride 2 reads, for
+    // output parity (py, px), (py + 1 - u) / 2 where that is whole
+#pragma unroll
+    for (int u = 0; u < KS; ++u) {
+#pragma unroll
+      for (int v = 0; v < KS; ++v) {
+        const int tap = u * KS + v;
+        const int par = ST == 1 ? 0 : ((u + 1) & 1) * 2 + ((v + 1) & 1);
+        const int dy = KS == 1 ? 0 : (ST == 1 ? 2 - u : (u == 0 ? 1 : 0));
+        const int dx = KS == 1 ? 0 : (ST == 1 ? 2 - v : (v == 0 ? 1 : 0));
+        bf16x4_t av[CBG];
+#pragma unroll
+        for (int cb = 0; cb < CBG; ++cb)
+          av[cb] = a.w[((tap * NOB + ob) * NCB + cb0 + cb) * 64 + lane];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const int i = ((wv + dy) * SP + t * 16 + (lane & 15) + dx) * 4 + kq;
+          const bf16x4_t b0 = st[i], b1 = st[NIT + i], b2 = st[2 * NIT + i];
+#pragma unroll
+          for (int cb = 0; cb < CBG; ++cb) {
+            f32x4_t c = acc[par][t][cb];
+            c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[cb], b2, c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[cb], b1, c, 0, 0, 0);
+            acc[par][t][cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[cb], b0, c, 0, 0, 0);
+          }
+        }
+      }
+    }
+  }
+  // lane: channels 4 kq .. + 3 of each block at one pixel
+#pragma unroll
+  for (int p = 0; p < NPAR; ++p) {
+    const int y = (y0 + wv) * ST + (p >> 1);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int x = (x0 + t * 16 + (lane & 15)) * ST + (p & 1);
+      if (y >= a.Hi || x >= a.Wi) continue;
+      const size_t q = (size_t)y * a.Wi + x;
+#pragma unroll
+      for (int cb = 0; cb < CBG; ++cb) {
+        const int c = (cb0 + cb) * 16 + 4 * kq;
+        const f32x4_t s = acc[p][t][cb];
+        float4 o{s[0], s[1], s[2], s[3]};
+        if (a.add) {
+          const float4 e = *reinterpret_cast<const float4*>(a.add + q * a.add_cs + a.add_off + c);
+          o = float4{o.x + e.x, o.y + e.y, o.z + e.z, o.w + e.w};
+        }
+        *reinterpret_cast<float4*>(a.dx + q * CIN + c) = o;
+      }
+    }
+  }
+}
+template <int KS, int ST, int NT>
+constexpr size_t dgrad_lds_bytes() {
+  constexpr int halo = KS == 1 ? 0 : (ST == 1 ? 2 : 1);
+  return (size_t)3 * (4 + halo) * (16 * NT + halo) * 4 * sizeof(bf16x4_t);
 }
 
 // Input of a layer as the backward reads it: one HWC BF16 tensor, or
@@ -64,308 +295,234 @@ struct BwdSrc {
   int Wl;
 };
 
-// Eight input channels c0..c0+7 (c0 % 8 == 0) at input pixel (yi, xi), which
-// the caller has clamped into the grid.
-__device__ __forceinline__ void load_x8(const BwdSrc& s, int Wi, int yi, int xi, int c0,
-                                        float (&x)[kWgCB]) {
-  const uint16_t* p;
-  if (s.Wl > 0 && c0 < s.cup)
-    p = s.in0 + ((size_t)(yi >> 1) * s.Wl + (xi >> 1)) * s.cs0 + c0;
-  else if (s.Wl > 0)
-    p = s.in1 + ((size_t)yi * Wi + xi) * s.cs1 + (c0 - s.cup);
-  else
-    p = s.in0 + ((size_t)yi * Wi + xi) * s.cs0 + c0;
-  const uint4 v = *reinterpret_cast<const uint4*>(p);
-  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    x[2 * k] = __uint_as_float(w[k] << 16);
-    x[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u);
-  }
-}
-
-// dz at output pixel q, channels o..o+3: the output gradient, masked by the
-// stored ReLU activation when act is given.
-__device__ __forceinline__ float4 load_dz4(const float* g, const uint16_t* act, size_t q, int cout,
-                                           int o) {
-  float4 d = *reinterpret_cast<const float4*>(g + q * cout + o);
-  if (act) {
-    const uint2 a = *reinterpret_cast<const uint2*>(act + q * cout + o);
-    d.x = (a.x & 0xffffu) != 0 && !(a.x & 0x8000u) ? d.x : 0.f;
-    d.y = (a.x >> 16) != 0 && !(a.x & 0x80000000u) ? d.y : 0.f;
-    d.z = (a.y & 0xffffu) != 0 && !(a.y & 0x8000u) ? d.z : 0.f;
-    d.w = (a.y >> 16) != 0 && !(a.y & 0x80000000u) ? d.w : 0.f;
-  }
-  return d;
-}
-
-struct WgradArgs {
-  const float* g;       // [Ho*Wo][cout] gradient of the layer's output activation
-  const uint16_t* act;  // [Ho*Wo][cout] stored activation (ReLU mask), or null
+// One layer of the weight-gradient launch. Its workgroups are (16 x 16 block
+// of output x input channels, pixel chunk), chunk-major.
+struct WgradLayer {
+  DzSrc dz;
   BwdSrc src;
   int Hi, Wi, Ho, Wo;
-  int cout, ncb, k, stride;  // ncb: 8-channel blocks of the stored input
-  int ne;                    // entries: (cout / 4) * ncb * k * k
-  int chunk_px;              // output pixels per chunk (blockIdx.x)
-  float* part;               // [nchunk][ne * 32 + cout]: entries' sums, then the bias sums
+  int ncb, npair;    // input channel blocks, block pairs
+  int k, stride;
+  int tiles_x, ntile, chunk;  // tiles of 4 x 64 output pixels; tiles per chunk
+  int nchunk;
+  float* part;       // [nchunk][npair][k k 256 + 16]: sums, then the bias sums
+  int cin, cout;
+  float* grad;       // the layer's weights [cout][cin][k][k] then bias [cout]
 };
-
-// One wave per row of KW taps (kernel row u) of 4 output channels x 8 input
-// channels: entries e0 .. e0 + KW - 1 with e0 = ((ob ncb + cb) k + u) k.
-// The 64 lanes stride over a chunk of output pixels, loading dz once for the
-// row's taps; the lanes' sums are added in LDS in lane order, one tap at a
-// time.
-template <int KW>
-__global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a) {
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int kk = KW * KW;
-  const int nrow = a.ne / KW;
-  const int w = blockIdx.y * 4 + wave;
-  const bool live = w < nrow;
-  const int u = live ? w % KW : 0;
-  const int cb = live ? (w / KW) % a.ncb : 0;
-  const int ob = live ? w / KW / a.ncb : 0;
-  const int e0 = ((ob * a.ncb + cb) * KW + u) * KW;
-  const int pd = KW / 2;
-  const bool with_bias = live && cb == 0 && u == 0;
-  float acc[KW][kWgAcc];
-  float bacc[kWgOB];
-#pragma unroll
-  for (int v = 0; v < KW; ++v)
-#pragma unroll
-    for (int i = 0; i < kWgAcc; ++i) acc[v][i] = 0.f;
-#pragma unroll
-  for (int i = 0; i < kWgOB; ++i) bacc[i] = 0.f;
-  const size_t npx = (size_t)a.Ho * a.Wo;
-  const size_t q0 = (size_t)blockIdx.x * a.chunk_px;
-  const size_t q1 = q0 + a.chunk_px < npx ? q0 + a.chunk_px : npx;
-  if (live) {
-    for (size_t q = q0 + lane; q < q1; q += 64) {
-      const int i = (int)(q / a.Wo), j = (int)(q % a.Wo);
-      const int yi = a.stride * i + u - pd;
-      const bool oky = yi >= 0 && yi < a.Hi;
-      const int yc = yi < 0 ? 0 : (yi >= a.Hi ? a.Hi - 1 : yi);
-      float x[KW][kWgCB];
-#pragma unroll
-      for (int v = 0; v < KW; ++v) {
-        const int xi = a.stride * j + v - pd;
-        const bool ok = oky && xi >= 0 && xi < a.Wi;
-        const int xc = xi < 0 ? 0 : (xi >= a.Wi ? a.Wi - 1 : xi);
-        load_x8(a.src, a.Wi, yc, xc, cb * kWgCB, x[v]);
-#pragma unroll
-        for (int c = 0; c < kWgCB; ++c) x[v][c] = ok ? x[v][c] : 0.f;
-      }
-      const float4 d4 = load_dz4(a.g, a.act, q, a.cout, ob * kWgOB);
-      const float d[kWgOB] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-      for (int o = 0; o < kWgOB; ++o) {
-        bacc[o] += d[o];
-#pragma unroll
-        for (int v = 0; v < KW; ++v)
-#pragma unroll
-          for (int c = 0; c < kWgCB; ++c) acc[v][o * kWgCB + c] += d[o] * x[v][c];
-      }
-    }
-  }
-  constexpr int kRow = kWgAcc + kWgOB + 1;  // + 1: staggers the LDS banks
-  float* red = flr::lds + wave * 64 * kRow;
-  float* row = a.part + (size_t)blockIdx.x * (a.ne * kWgAcc + a.cout);
-#pragma unroll
-  for (int v = 0; v < KW; ++v) {
-    if (v > 0) __syncthreads();  // the previous tap's sums have been read
-#pragma unroll
-    for (int i = 0; i < kWgAcc; ++i) red[lane * kRow + i] = acc[v][i];
-#pragma unroll
-    for (int i = 0; i < kWgOB; ++i) red[lane * kRow + kWgAcc + i] = bacc[i];
-    __syncthreads();
-    if (live && lane < kWgAcc + kWgOB) {
-      float s = 0.f;
-      for (int l = 0; l < 64; ++l) s += red[l * kRow + lane];
-      if (lane < kWgAcc)
-        row[(e0 + v) * kWgAcc + lane] = s;
-      else if (with_bias && v == 0)
-        row[a.ne * kWgAcc + ob * kWgOB + (lane - kWgAcc)] = s;
-    }
-  }
-}
-constexpr size_t wgrad_lds_bytes() { return 4 * 64 * (kWgAcc + kWgOB + 1) * sizeof(float); }
-
-// First level of the chunk sum: out[g][slot] = sum of in[ch][slot] over
-// the chunks ch of group g (kChunkGroup consecutive chunks), in order.
-constexpr int kChunkGroup = 32;
-struct ChunkSumArgs {
-  const float* in;
-  float* out;
-  int S, nchunk;
-};
-__global__ void __launch_bounds__(256) chunk_sum_kernel(ChunkSumArgs a) {
-  const int ng = (a.nchunk + kChunkGroup - 1) / kChunkGroup;
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)ng * a.S) return;
-  const int g = (int)(idx / a.S), slot = (int)(idx % a.S);
-  const int c0 = g * kChunkGroup;
-  const int c1 = c0 + kChunkGroup < a.nchunk ? c0 + kChunkGroup : a.nchunk;
-  float s = 0.f;
-  for (int ch = c0; ch < c1; ++ch) s += a.in[(size_t)ch * a.S + slot];
-  a.out[idx] = s;
-}
-
-struct WreduceArgs {
-  const float* part;  // [nchunk][ne * 32 + cout]
-  int nchunk, ne, ncb, cin, cout, k;
-  float* grad;  // the layer's weights [cout][cin][k][k] then bias [cout]
+struct WgradArgs {
+  WgradLayer layer[12];
+  int first[13];      // first workgroup of each layer's weight gradients
+  int rfirst[13];     // first element of each layer in the reduction
   int accumulate;
 };
 
-// grad = (accumulate ? grad : 0) + the chunk partials, added in chunk order.
-// One thread per partial slot (entry e, slot j), so the chunk loop reads
-// consecutive addresses across the wave; the result goes to its weight.
-__global__ void __launch_bounds__(256) wreduce_kernel(WreduceArgs a) {
-  const int kk = a.k * a.k;
-  const int np = a.ne * kWgAcc, S = np + a.cout;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= S) return;
-  int dst;
-  if (idx < np) {
-    const int e = idx / kWgAcc, j = idx % kWgAcc;
-    const int tap = e % kk, cb = (e / kk) % a.ncb, ob = e / kk / a.ncb;
-    const int o = ob * kWgOB + j / kWgCB, c = cb * kWgCB + j % kWgCB;
-    if (c >= a.cin) return;  // padding channels of the stored input
-    dst = (o * a.cin + c) * kk + tap;
-  } else {
-    dst = a.cout * a.cin * kk + (idx - np);
-  }
-  float s = 0.f;
-  for (int ch = 0; ch < a.nchunk; ++ch) s += a.part[(size_t)ch * S + idx];
-  a.grad[dst] = a.accumulate ? a.grad[dst] + s : s;
+// D = A B + C of 16 x 16 x 4 FP32 (lane l: A row l % 16, k = l / 16; B k =
+// l / 16, column l % 16; C, D as the BF16 instruction). b holds a BF16 value.
+__device__ __forceinline__ f32x4_t mfma_f32(float a, float b, f32x4_t c) {
+#if __has_builtin(__builtin_amdgcn_mfma_f32_16x16x4f32)
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+#else  // hosts that emulate the BF16 instruction only: the same products in three parts
+  uint16_t h[3];
+  split3(a, h);
+  const bf16x4_t bv = pack4((uint16_t)(__float_as_uint(b) >> 16), 0, 0, 0);
+  for (int s = 2; s >= 0; --s)
+    c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pack4(h[s], 0, 0, 0), bv, c, 0, 0, 0);
+  return c;
+#endif
 }
 
-struct DgradArgs {
-  const float* g;       // [Ho*Wo][cout]
-  const uint16_t* act;  // ReLU mask or null
-  const float* w;       // BF16-rounded weights [cout][cin][k][k]
-  int cin, cout, k, stride;
-  int Hi, Wi, Ho, Wo;
-  float* dx;            // [Hi*Wi][cin]
-  const float* add;     // optional addend add[p * add_cs + add_off + c]
-  int add_cs, add_off;
-};
-
-// One thread per input pixel and kDgC input channels (blockIdx.y picks
-// them); the workgroup first stages those channels' weights in LDS as
-// [tap][o][kDgC]. 16 channels halve the dz loads per multiply-add; 8 give
-// twice the workgroups, which small frames need to fill the chip.
-template <int kDgC>
-__global__ void __launch_bounds__(256) dgrad_kernel(DgradArgs a) {
-  float* wl = flr::lds;
-  const int c0 = blockIdx.y * kDgC;
-  const int pd = a.k / 2, kk = a.k * a.k;
-  const int nw = kk * a.cout * kDgC;
-  for (int t = threadIdx.x; t < nw; t += blockDim.x) {
-    const int c = t % kDgC, o = (t / kDgC) % a.cout, tap = t / (kDgC * a.cout);
-    wl[t] = a.w[((size_t)o * a.cin + c0 + c) * kk + tap];
-  }
-  __syncthreads();
-  const size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t npx = (size_t)a.Hi * a.Wi;
-  if (p >= npx) return;
-  const int y = (int)(p / a.Wi), x = (int)(p % a.Wi);
-  float acc[kDgC];
+// Weight gradients as GEMMs over pixels on the matrix cores: D (o x c) += dz
+// (o x pixels) x (pixels x c), one accumulator per tap. A workgroup stages a
+// tile of 4 x 64 output pixels' dz (16 channels, FP32) and the input pixels
+// its taps read (16 channels, BF16) in LDS, HWC: the FP32 instruction takes
+// one pixel and one channel per lane, so both operands are read as they lie,
+// 64 consecutive values. Wave w sums row w; the four sums are added in wave
+// order at the end of the chunk.
+template <int KS, int ST>
+__device__ __forceinline__ void wgrad_tile(const WgradLayer& a, const int wg) {
+  constexpr int KK = KS * KS, PD = KS / 2;
+  constexpr int XR = 3 * ST + KS, XP = 63 * ST + KS;  // staged input rows and columns
+  float* zs = flr::lds;                               // [4][64][16]
+  uint16_t* xs = reinterpret_cast<uint16_t*>(flr::lds + 4 * 64 * 16);  // [XR][XP][16]
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int chunk = wg / a.npair, pair = wg - chunk * a.npair;
+  const int ob = pair / a.ncb, cb = pair - ob * a.ncb;
+  f32x4_t acc[KK], bacc = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int c = 0; c < kDgC; ++c) acc[c] = 0.f;
-  for (int u = 0; u < a.k; ++u) {
-    const int ny = y + pd - u;
-    if (ny < 0 || ny % a.stride) continue;
-    const int i = ny / a.stride;
-    if (i >= a.Ho) continue;
-    for (int v = 0; v < a.k; ++v) {
-      const int nx = x + pd - v;
-      if (nx < 0 || nx % a.stride) continue;
-      const int j = nx / a.stride;
-      if (j >= a.Wo) continue;
-      const size_t q = (size_t)i * a.Wo + j;
-      const float* wt = wl + (size_t)(u * a.k + v) * a.cout * kDgC;
-      for (int o = 0; o < a.cout; o += 4) {
-        const float4 d4 = load_dz4(a.g, a.act, q, a.cout, o);
-        const float d[4] = {d4.x, d4.y, d4.z, d4.w};
+  for (int t = 0; t < KK; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const float one = (lane & 15) == 0 ? 1.f : 0.f;
+  const int t0 = chunk * a.chunk, t1 = min(t0 + a.chunk, a.ntile);
+  for (int tile = t0; tile < t1; ++tile) {
+    const int ty = tile / a.tiles_x, tx = tile - ty * a.tiles_x;
+    const int y0 = ty * 4, x0 = tx * 64;
+    if (tile > t0) __syncthreads();  // the previous tile has been read
+    {
+      float4 d[4];
+      bool ok[4];
 #pragma unroll
-        for (int oo = 0; oo < 4; ++oo) {
+      for (int u = 0; u < 4; ++u) {
+        const int i = u * 256 + tid, pix = i >> 2, q = i & 3;
+        const int y = y0 + (pix >> 6), x = x0 + (pix & 63);
+        ok[u] = y < a.Ho && x < a.Wo;
+        d[u] = load_dz4(a.dz, min(y, a.Ho - 1), min(x, a.Wo - 1), a.Wo, ob * 16 + 4 * q);
+      }
 #pragma unroll
-          for (int c4 = 0; c4 < kDgC; c4 += 4) {
-            const float4 w4 = *reinterpret_cast<const float4*>(wt + (o + oo) * kDgC + c4);
-            acc[c4 + 0] += w4.x * d[oo];
-            acc[c4 + 1] += w4.y * d[oo];
-            acc[c4 + 2] += w4.z * d[oo];
-            acc[c4 + 3] += w4.w * d[oo];
-          }
-        }
+      for (int u = 0; u < 4; ++u) {
+        *reinterpret_cast<float4*>(zs + (u * 256 + tid) * 4) =
+            float4{ok[u] ? d[u].x : 0.f, ok[u] ? d[u].y : 0.f, ok[u] ? d[u].z : 0.f,
+                   ok[u] ? d[u].w : 0.f};
       }
     }
-  }
-  float* dst = a.dx + p * a.cin + c0;
-  if (a.add) {
-    const float* ad = a.add + p * a.add_cs + a.add_off + c0;
+    // input pixels: two 16-byte halves each
+    constexpr int NIT = XR * XP * 2, B = 4;
+    const int c0 = cb * 16;
+    const bool low = a.src.Wl > 0 && c0 < a.src.cup;
+    for (int b0 = 0; b0 < NIT; b0 += B * 256) {
+      uint4 v[B];
+      bool ok[B];
 #pragma unroll
-    for (int c = 0; c < kDgC; ++c) dst[c] = acc[c] + ad[c];
-  } else {
+      for (int u = 0; u < B; ++u) {
+        const int i = b0 + u * 256 + tid, ic = i < NIT ? i : NIT - 1;
+        const int pix = ic >> 1, hf = ic & 1;
+        const int sr = pix / XP, sx = pix - sr * XP;
+        const int y = y0 * ST - PD + sr, x = x0 * ST - PD + sx;
+        ok[u] = y >= 0 && y < a.Hi && x >= 0 && x < a.Wi;
+        const int yc = min(max(y, 0), a.Hi - 1), xc = min(max(x, 0), a.Wi - 1);
+        const uint16_t* p =
+            low ? a.src.in0 + ((size_t)(yc >> 1) * a.src.Wl + (xc >> 1)) * a.src.cs0 + c0
+            : a.src.Wl > 0
+                ? a.src.in1 + ((size_t)yc * a.Wi + xc) * a.src.cs1 + (c0 - a.src.cup)
+                : a.src.in0 + ((size_t)yc * a.Wi + xc) * a.src.cs0 + c0;
+        v[u] = *reinterpret_cast<const uint4*>(p + 8 * hf);
+      }
 #pragma unroll
-    for (int c = 0; c < kDgC; ++c) dst[c] = acc[c];
-  }
-}
-inline size_t dgrad_lds_bytes(const Layer& L, int cpt) {
-  return (size_t)L.k * L.k * L.cout * cpt * sizeof(float);
-}
-// grids from 2^18 pixels take 16 channels per thread (the sum order per
-// channel is the same either way; a build may lower the threshold)
-#ifndef FLR_DGRAD_WIDE_PX
-#define FLR_DGRAD_WIDE_PX (1 << 18)
-#endif
-constexpr size_t kDgWidePx = (size_t)(FLR_DGRAD_WIDE_PX);
-
-// low[(i,j)][c] = sum of fine[(2i+di, 2j+dj)][c] over the fine pixels in the
-// H x W grid, channels c < nc of a fine tensor with channel stride cs.
-struct Up2BwdArgs {
-  const float* fine;
-  int H, W, cs;
-  float* low;
-  int Hl, Wl, nc;
-};
-__global__ void __launch_bounds__(256) up2_bwd_kernel(Up2BwdArgs a) {
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)a.Hl * a.Wl * a.nc) return;
-  const int c = (int)(idx % a.nc);
-  const size_t pl = idx / a.nc;
-  const int i = (int)(pl / a.Wl), j = (int)(pl % a.Wl);
-  float s = 0.f;
-  for (int di = 0; di < 2; ++di)
-    for (int dj = 0; dj < 2; ++dj) {
-      const int y = 2 * i + di, x = 2 * j + dj;
-      if (y < a.H && x < a.W) s += a.fine[((size_t)y * a.W + x) * a.cs + c];
+      for (int u = 0; u < B; ++u) {
+        const int i = b0 + u * 256 + tid;
+        const uint32_t keep = ok[u] ? 0xffffffffu : 0u;
+        if (i < NIT)
+          *reinterpret_cast<uint4*>(xs + i * 8) =
+              uint4{v[u].x & keep, v[u].y & keep, v[u].z & keep, v[u].w & keep};
+      }
     }
-  a.low[idx] = s;
+    __syncthreads();
+    const float* zr = zs + wv * 64 * 16 + lane;  // pixel 4 s + lane / 16, channel lane % 16
+    const uint16_t* xr = xs + ((wv * ST) * XP + (lane >> 4) * ST) * 16 + (lane & 15);
+#pragma unroll 4
+    for (int s = 0; s < 16; ++s) {
+      const float z = zr[s * 64];
+      if (cb == 0) bacc = mfma_f32(z, one, bacc);
+#pragma unroll
+      for (int u = 0; u < KS; ++u)
+#pragma unroll
+        for (int v = 0; v < KS; ++v) {
+          const float x = bf2f(xr[(u * XP + 4 * s * ST + v) * 16]);
+          acc[u * KS + v] = mfma_f32(z, x, acc[u * KS + v]);
+        }
+    }
+  }
+  // add the four waves' sums: [wave][tap][o][c], then the bias [wave][o]
+  __syncthreads();
+  float* red = flr::lds;
+  constexpr int S = KK * 256 + 16;
+#pragma unroll
+  for (int t = 0; t < KK; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      red[wv * S + t * 256 + (4 * (lane >> 4) + i) * 16 + (lane & 15)] = acc[t][i];
+  if ((lane & 15) == 0)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[wv * S + KK * 256 + 4 * (lane >> 4) + i] = bacc[i];
+  __syncthreads();
+  float* out = a.part + ((size_t)chunk * a.npair + pair) * S;
+  for (int i = tid; i < S; i += 256)
+    out[i] = ((red[i] + red[S + i]) + red[2 * S + i]) + red[3 * S + i];
+}
+constexpr size_t wgrad_lds_bytes() {
+  // the stride-2 tile (9 x 129 input pixels) or the closing sums, whichever is larger
+  return 4 * 64 * 16 * sizeof(float) + (size_t)9 * 129 * 16 * sizeof(uint16_t);
+}
+static_assert(wgrad_lds_bytes() >= 4 * (9 * 256 + 16) * sizeof(float), "closing sums fit");
+
+__global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a) {
+  const int b = blockIdx.x;
+  int li = 0;
+  while (b >= a.first[li + 1]) ++li;
+  const WgradLayer& L = a.layer[li];
+  if (L.k == 1)
+    wgrad_tile<1, 1>(L, b - a.first[li]);
+  else if (L.stride == 1)
+    wgrad_tile<3, 1>(L, b - a.first[li]);
+  else
+    wgrad_tile<3, 2>(L, b - a.first[li]);
 }
 
-// Chunking of a weight-gradient launch: about kWgTarget workgroups (4 per
-// CU), chunks of whole waves of pixels and at least kWgMinIters pixels per
-// lane, so that the pixel loop outweighs the wave's closing LDS reduction.
-constexpr int kWgTarget = 2048;
-constexpr int kWgMinIters = 16;
+// grad = (accumulate ? grad : 0) + the chunks' partial sums in chunk order:
+// 64 elements per workgroup, each wave a quarter of the chunks (16 loads in
+// flight), then the four quarters in order.
+__global__ void __launch_bounds__(256) wreduce_kernel(WgradArgs a) {
+  float* red = flr::lds;  // [4][64]
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + lane;
+  const int total = a.rfirst[12];
+  int li = 0;
+  while (li < 11 && e >= a.rfirst[li + 1]) ++li;
+  const WgradLayer& L = a.layer[li];
+  const int i = e - a.rfirst[li];
+  const int kk = L.k * L.k, S = kk * 256 + 16;
+  const int pair = i / S, s = i - pair * S;
+  const int per = (L.nchunk + 3) / 4;
+  const int c0 = wv * per, c1 = min(c0 + per, L.nchunk);
+  float sum = 0.f;
+  if (e < total) {
+    const size_t step = (size_t)L.npair * S;
+    const float* p = L.part + i + (size_t)c0 * step;
+    int c = c0;
+    for (; c + 16 <= c1; c += 16) {
+      float t[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) t[k] = p[k * step];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) sum += t[k];
+      p += 16 * step;
+    }
+    for (; c < c1; ++c, p += step) sum += *p;
+  }
+  red[wv * 64 + lane] = sum;
+  __syncthreads();
+  if (wv != 0 || e >= total) return;
+  const float t = ((red[lane] + red[64 + lane]) + red[128 + lane]) + red[192 + lane];
+  const int ob = pair / L.ncb, cb = pair - ob * L.ncb;
+  int dst;
+  if (s < kk * 256) {
+    const int tap = s >> 8, o = ob * 16 + ((s >> 4) & 15), c = cb * 16 + (s & 15);
+    if (o >= L.cout || c >= L.cin) return;  // padding channels
+    dst = (o * L.cin + c) * kk + tap;
+  } else {
+    const int o = ob * 16 + (s - kk * 256);
+    if (cb != 0 || o >= L.cout) return;
+    dst = L.cout * L.cin * kk + o;
+  }
+  L.grad[dst] = a.accumulate ? L.grad[dst] + t : t;
+}
+
+// Chunking of a layer's weight gradient: about kWgTarget workgroups.
+constexpr int kWgTarget = 160;
 struct WgradPlan {
-  int ne, wg_y, chunk_px, nchunk;
+  int ncb, npair, tiles_x, ntile, chunk, nchunk;
 };
-inline WgradPlan wgrad_plan(const Layer& L, int ncb, size_t npx) {
+inline WgradPlan wgrad_plan(const Layer& L, int Ho, int Wo) {
   WgradPlan p;
-  p.ne = (L.cout / kWgOB) * ncb * L.k * L.k;
-  p.wg_y = (p.ne / L.k + 3) / 4;  // one wave per row of L.k taps
-  const size_t waves = (npx + 63) / 64;
-  size_t want = (kWgTarget + p.wg_y - 1) / p.wg_y;
-  if (want > (waves + kWgMinIters - 1) / kWgMinIters) want = (waves + kWgMinIters - 1) / kWgMinIters;
-  if (want < 1) want = 1;
-  const size_t per = (waves + want - 1) / want;
-  p.chunk_px = (int)(per * 64);
-  p.nchunk = (int)((npx + p.chunk_px - 1) / p.chunk_px);
+  p.ncb = (L.cin + 15) / 16;
+  p.npair = p.ncb * ((L.cout + 15) / 16);
+  p.tiles_x = (Wo + 63) / 64;
+  p.ntile = p.tiles_x * ((Ho + 3) / 4);
+  const int want = kWgTarget / p.npair > 1 ? kWgTarget / p.npair : 1;
+  p.chunk = (p.ntile + want - 1) / want;
+  p.nchunk = (p.ntile + p.chunk - 1) / p.chunk;
   return p;
 }
-inline int stored_cin_blocks(int li) { return li == 0 ? 2 : kLayers[li].cin / kWgCB; }
+inline size_t wgrad_part_floats(const Layer& L, const WgradPlan& p) {
+  return (size_t)p.nchunk * p.npair * (L.k * L.k * 256 + 16);
+}
 
 }  // namespace flrnet
