@@ -2,7 +2,7 @@
 // declared in include/flr_net.h) on the gfx950 matrix cores, and FLNR
 // denoising (network, then FLR over the 12 guides).
 //
-// Every layer is one implicit-GEMM kernel. Activations are BF16 in HWC order
+// Every 3x3 layer is one implicit-GEMM kernel. Activations are BF16 in HWC order
 // (channels innermost, a multiple of 16), so the 16 channels of one K step
 // of a pixel are 32 contiguous bytes. With A = weights (c_out x k) and
 // B = input (k x pixels), v_mfma_f32_16x16x16_bf16 gives lane l the
@@ -10,10 +10,18 @@
 // consecutive channels, stored as one 8-byte write, and exactly the B
 // operand layout of a following 1x1 layer, which is therefore fused into the
 // producing kernel (in3 + in1, out3 + out1). Upsampling and concatenation
-// are folded into the consumer's operand loads. A workgroup of four waves
-// covers 64 consecutive output pixels of one row, each wave 16 pixels and
-// all output channels; weights are packed once into the per-lane fragment
-// order, so each A operand is one contiguous 512-byte read per wave.
+// are folded into the consumer's staging. A workgroup of four waves computes
+// four output rows from an input tile in LDS; weights are packed once into the
+// per-lane fragment order, so each A operand is one contiguous 512-byte read
+// per wave.
+//
+// What bounds it: 668 bytes per full-resolution pixel between the layers (270
+// us at 1080p at the 5.2 TB/s of a large copy) and, per layer, staging and
+// epilogue instructions beside few matrix instructions. Measured against
+// 8-byte staging with per-chunk clamps, a separate pass for the input and the
+// 64- and 96-channel layers reading operands from L2, 64 pixels per wave at
+// every size: 1080p 802 -> 608 us; 256 x 256 137 -> 75 us (its half and quarter
+// grids left most CUs idle).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -31,7 +39,7 @@ namespace flrnet {
 typedef short bf16x4_t __attribute__((vector_size(8)));
 typedef float f32x4_t __attribute__((vector_size(16)));
 
-enum InKind : int { IN_HWC = 0, IN_UPCAT = 2 };
+enum InKind : int { IN_HWC = 0, IN_PLANES = 1, IN_UPCAT = 2 };
 enum Fuse : int { FUSE_NONE = 0, FUSE_1X1_RELU = 1, FUSE_1X1_SIGMOID = 2 };
 
 struct ConvArgs {
@@ -45,6 +53,9 @@ struct ConvArgs {
   float* outf;          // FUSE_1X1_SIGMOID: planar FP32 output
   uint16_t* mid;        // fused layers: when set, the first layer's BF16
                         // activations are stored here too (HWC, 16 channels)
+  const float* guides;  // IN_PLANES: the network's input planes,
+  const float* noisy;
+  uint16_t* x0;         // and, when set, its compressed BF16 copy (HWC, 16 channels)
   int Hi, Wi;           // input grid
   int Hl, Wl;           // IN_UPCAT: grid of in0
   int Ho, Wo;           // output grid
@@ -58,6 +69,9 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+// Four FP32 values rounded to BF16 (as f2bf; two conversion instructions).
+__device__ __forceinline__ bf16x4_t round4(float a, float b, float c, float d);
+
 __device__ __forceinline__ bf16x4_t pack4(uint16_t a, uint16_t b, uint16_t c, uint16_t d) {
   bf16x4_t v;
   v[0] = (short)a;
@@ -67,334 +81,234 @@ __device__ __forceinline__ bf16x4_t pack4(uint16_t a, uint16_t b, uint16_t c, ui
   return v;
 }
 
-// Four consecutive input channels c..c+3 of input pixel (yi, xi), which
-// the caller has clamped into the input grid; the caller zeroes padding.
-// CB: the 16-channel block (compile-time, so the source choice folds);
-// c4 = 4 * (lane / 16), the lane's channel quad within the block.
-template <int CIN, int CUP, int IN, int CB>
-__device__ __forceinline__ bf16x4_t load_in(const ConvArgs& a, int yi, int xi, int c4) {
-  constexpr int c0 = CB * 16;
-  if constexpr (IN == IN_UPCAT && c0 < CUP)
-    return *reinterpret_cast<const bf16x4_t*>(a.in0 + ((size_t)(yi >> 1) * a.Wl + (xi >> 1)) * CUP +
-                                              c0 + c4);
-  else if constexpr (IN == IN_UPCAT)
-    return *reinterpret_cast<const bf16x4_t*>(a.in1 + ((size_t)yi * a.Wi + xi) * (CIN - CUP) +
-                                              (c0 - CUP) + c4);
-  else
-    return *reinterpret_cast<const bf16x4_t*>(a.in0 + ((size_t)yi * a.Wi + xi) * CIN + c0 + c4);
+#if defined(__gfx950__)
+__device__ __forceinline__ bf16x4_t round4(float a, float b, float c, float d) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 h2 __attribute__((ext_vector_type(2)));
+  const h2 v[2] = {__builtin_convertvector(f2{a, b}, h2), __builtin_convertvector(f2{c, d}, h2)};
+  bf16x4_t r;
+  __builtin_memcpy(&r, v, sizeof r);
+  return r;
+}
+#else
+__device__ __forceinline__ bf16x4_t round4(float a, float b, float c, float d) {
+  return pack4(f2bf(a), f2bf(b), f2bf(c), f2bf(d));
+}
+#endif
+
+// Network input at one pixel, channels c0 .. c0 + 7 of the 16 (8 guides, 3
+// noisy planes, zero): sign(v) log(1 + |v|), rounded to BF16.
+__device__ __forceinline__ float compress(float v) { return copysignf(log1pf(fabsf(v)), v); }
+
+__device__ __forceinline__ f32x4_t load_bias(const float* b) {
+  return *reinterpret_cast<const f32x4_t*>(b);
+}
+__device__ __forceinline__ bf16x4_t relu_round(f32x4_t v) {
+  return round4(fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f));
 }
 
-// All NCB channel blocks of one input pixel (zero where !ok).
-template <int CIN, int CUP, int IN, int NCB, int CB = 0>
-__device__ __forceinline__ void load_blocks(const ConvArgs& a, int yi, int xi, int c4, bool ok,
-                                            bf16x4_t (&dst)[NCB]) {
-  if constexpr (CB < NCB) {
-    const bf16x4_t v = load_in<CIN, CUP, IN, CB>(a, yi, xi, c4);
-    dst[CB] = ok ? v : pack4(0, 0, 0, 0);
-    load_blocks<CIN, CUP, IN, NCB, CB + 1>(a, yi, xi, c4, ok, dst);
-  }
-}
-
-// Network input: the 8 guides and 3 noisy planes (planar FP32) of one pixel,
-// each compressed to sign(v) log(1 + |v|), rounded to BF16 and written as
-// one HWC row of 16 channels (the last 5 zero).
-struct PrepArgs {
-  const float* g;
-  const float* y;
-  uint16_t* out;
-  int H, W;
-};
-__global__ void __launch_bounds__(256) prep_kernel(PrepArgs a) {
-  const size_t pl = (size_t)a.H * a.W;
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= pl) return;
-  uint16_t h[16];
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    float v = 0.f;
-    if (c < FLR_NET_IN_GUIDES) v = a.g[c * pl + i];
-    else if (c < FLR_NET_IN_GUIDES + FLR_NET_IN_NOISY) v = a.y[(c - FLR_NET_IN_GUIDES) * pl + i];
-    h[c] = f2bf(copysignf(log1pf(fabsf(v)), v));
-  }
-  bf16x4_t* o = reinterpret_cast<bf16x4_t*>(a.out + i * 16);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) o[q] = pack4(h[4 * q], h[4 * q + 1], h[4 * q + 2], h[4 * q + 3]);
-}
-
-// One conv layer (CIN, COUT multiples of 16; KS 1 or 3; stride ST), bias and
-// ReLU, optionally followed by a fused 1x1 layer to COUT2 channels (ReLU to
-// HWC BF16, or sigmoid to planar FP32).
-// Bias, ReLU and store of one tile (lane l: channels 4*(l/16)..+3 of each
-// 16-channel block, pixel px), or the fused 1x1 layer on those activations.
-template <int COUT, int FUSE, int COUT2>
-__device__ __forceinline__ void epilogue(const ConvArgs& a, int y, int px, bool pin, int kq,
-                                         int lane, const f32x4_t (&acc)[COUT / 16]) {
+// Bias, ReLU and store of TPW tiles of one output row (lane l: channels
+// 4*(l/16)..+3 of each 16-channel block, pixel px0 + 16 t + l % 16), or the
+// fused 1x1 layer on those activations.
+template <int COUT, int FUSE, int COUT2, int TPW>
+__device__ __forceinline__ void epilogue(const ConvArgs& a, int y, int px0, int lane,
+                                         const f32x4_t (&acc)[TPW][COUT / 16]) {
   constexpr int NB = COUT / 16;
+  const int kq = lane >> 4;
+  const size_t row = (size_t)y * a.Wo;
   if constexpr (FUSE == FUSE_NONE) {
-    if (!pin) return;
-    uint16_t* o = a.out + ((size_t)y * a.Wo + px) * COUT + 4 * kq;
+    f32x4_t bias[NB];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      uint16_t h[4];
+    for (int nb = 0; nb < NB; ++nb) bias[nb] = load_bias(a.b + nb * 16 + 4 * kq);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) h[i] = f2bf(fmaxf(acc[nb][i] + a.b[nb * 16 + 4 * kq + i], 0.f));
-      *reinterpret_cast<bf16x4_t*>(o + nb * 16) = pack4(h[0], h[1], h[2], h[3]);
+    for (int t = 0; t < TPW; ++t) {
+      const int px = px0 + t * 16 + (lane & 15);
+      if (px >= a.Wo) continue;
+      uint16_t* o = a.out + (row + px) * COUT + 4 * kq;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        *reinterpret_cast<bf16x4_t*>(o + nb * 16) = relu_round(acc[t][nb] + bias[nb]);
     }
   } else {
     static_assert(COUT == 16, "a fused 1x1 layer reads 16 channels");
-    // this layer's activations are the B operand of the 1x1 layer as they are
-    uint16_t h[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) h[i] = f2bf(fmaxf(acc[0][i] + a.b[4 * kq + i], 0.f));
-    const bf16x4_t hv = pack4(h[0], h[1], h[2], h[3]);
-    if (a.mid && pin)
-      *reinterpret_cast<bf16x4_t*>(a.mid + ((size_t)y * a.Wo + px) * 16 + 4 * kq) = hv;
-    constexpr int NB2 = (COUT2 + 15) / 16;
-#pragma unroll
-    for (int nb = 0; nb < NB2; ++nb) {
-      f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f};
-      d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.w2[nb * 64 + lane], hv, d, 0, 0, 0);
-      if (!pin) continue;
-      if (FUSE == FUSE_1X1_RELU) {
-        uint16_t q[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) q[i] = f2bf(fmaxf(d[i] + a.b2[nb * 16 + 4 * kq + i], 0.f));
-        *reinterpret_cast<bf16x4_t*>(a.out + ((size_t)y * a.Wo + px) * COUT2 + nb * 16 + 4 * kq) =
-            pack4(q[0], q[1], q[2], q[3]);
-      } else {
-        const size_t pl = (size_t)a.Ho * a.Wo, off = (size_t)y * a.Wo + px;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int c = nb * 16 + 4 * kq + i;
-          if (c < COUT2) a.outf[c * pl + off] = 1.f / (1.f + expf(-(d[i] + a.b2[c])));
-        }
-      }
-    }
-  }
-}
-
-// DPP lane move of an 8-byte fragment within 16-lane rows (two 32-bit moves).
-constexpr int kDppRowShl1 = 0x101, kDppRowShr1 = 0x111, kDppRowRor1 = 0x121,
-              kDppRowRor15 = 0x12F;
-template <int CTRL>
-__device__ __forceinline__ bf16x4_t dpp_frag(bf16x4_t v) {
-  int w[2];
-  __builtin_memcpy(w, &v, sizeof w);
-  w[0] = __builtin_amdgcn_update_dpp(0, w[0], CTRL, 0xf, 0xf, true);
-  w[1] = __builtin_amdgcn_update_dpp(0, w[1], CTRL, 0xf, 0xf, true);
-  bf16x4_t r;
-  __builtin_memcpy(&r, w, sizeof w);
-  return r;
-}
-
-// Four tiles of 16 output pixels per wave: the input fragments of the four
-// tiles for one kernel row are in flight together and each weight fragment
-// is reused across them.
-__host__ __device__ constexpr int tiles_per_wave(int) { return 4; }
-
-template <int CIN, int COUT, int KS, int ST, int IN, int CUP, int FUSE, int COUT2>
-__global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
-  constexpr int NCB = CIN / 16, NB = COUT / 16, P = KS / 2, TPW = tiles_per_wave(CIN);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int y = blockIdx.y;
-  const int kq = lane >> 4;
-  int px[TPW];
-  bool pin[TPW];
-#pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    px[t] = (blockIdx.x * 4 + wv) * TPW * 16 + t * 16 + (lane & 15);
-    pin[t] = px[t] < a.Wo;
-  }
-  // partial sums (K steps round-robin) so that at least 8 independent MFMA
-  // chains are in flight per wave
-  constexpr int KSPL = (TPW * NB >= 8) ? 1 : 8 / (TPW * NB);
-  f32x4_t acc[TPW][NB][KSPL];
-#pragma unroll
-  for (int t = 0; t < TPW; ++t)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int k = 0; k < KSPL; ++k) acc[t][nb][k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int ky = 0; ky < KS; ++ky) {
-    const int yi = y * ST + ky - P;
-    const bool oky = yi >= 0 && yi < a.Hi;
-    const int yc = min(max(yi, 0), a.Hi - 1);
-    // this kernel row's input fragments of every tile, then their products
-    bf16x4_t bv[TPW][KS][NCB];
-    if constexpr (ST == 1 && KS == 3) {
-      // Only the centre column (kx = 1) of each tile and one pixel beyond
-      // each end of the four tiles are loaded. In the B layout a 16-lane DPP
-      // row holds 16 consecutive pixels of one channel group, so kx = 0 is
-      // the centre shifted right by one lane (row_shr) with lane 0 taking
-      // lane 15 of the tile before (row_ror:1), and kx = 2 the centre shifted
-      // left (row_shl) with lane 15 taking lane 0 of the next tile
-      // (row_ror:15). Out-of-image pixels are zero in the centre and halo
-      // loads, hence in every shifted copy.
-      bf16x4_t hl[NCB], hr[NCB];
+    const f32x4_t bias = load_bias(a.b + 4 * kq);
+    if constexpr (FUSE == FUSE_1X1_RELU) {
+      constexpr int NB2 = COUT2 / 16;
 #pragma unroll
       for (int t = 0; t < TPW; ++t) {
-        const int xc = min(max(px[t], 0), a.Wi - 1);
-        load_blocks<CIN, CUP, IN, NCB>(a, yc, xc, 4 * kq, pin[t] && oky, bv[t][1]);
-      }
-      {
-        const int xl = px[0] - 1, xr = px[TPW - 1] + 1;
-        load_blocks<CIN, CUP, IN, NCB>(a, yc, min(max(xl, 0), a.Wi - 1), 4 * kq,
-                                       oky && xl >= 0 && xl < a.Wi, hl);
-        load_blocks<CIN, CUP, IN, NCB>(a, yc, min(max(xr, 0), a.Wi - 1), 4 * kq,
-                                       oky && xr >= 0 && xr < a.Wi, hr);
-      }
-      const bool first = (lane & 15) == 0, last = (lane & 15) == 15;
+        const int px = px0 + t * 16 + (lane & 15);
+        // this layer's activations are the B operand of the 1x1 layer as they are
+        const bf16x4_t hv = relu_round(acc[t][0] + bias);
+        if (a.mid && px < a.Wo)
+          *reinterpret_cast<bf16x4_t*>(a.mid + (row + px) * 16 + 4 * kq) = hv;
 #pragma unroll
-      for (int t = 0; t < TPW; ++t) {
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-          const bf16x4_t left = t == 0 ? hl[cb] : dpp_frag<kDppRowRor1>(bv[t - 1][1][cb]);
-          const bf16x4_t shr = dpp_frag<kDppRowShr1>(bv[t][1][cb]);
-          bv[t][0][cb] = first ? left : shr;
-          const bf16x4_t right = t == TPW - 1 ? hr[cb] : dpp_frag<kDppRowRor15>(bv[t + 1][1][cb]);
-          const bf16x4_t shl = dpp_frag<kDppRowShl1>(bv[t][1][cb]);
-          bv[t][2][cb] = last ? right : shl;
-        }
-      }
-    } else if constexpr (ST == 2 && KS == 3 && CIN <= 32) {
-      // Stride 2: kx = 1 and kx = 2 read input pixels 2p and 2p + 1; kx = 0
-      // reads 2p - 1, the kx = 2 pixel of the lane before (row_shr), lane 0
-      // taking lane 15 of the tile before (row_ror:1) or, for the first
-      // tile, one loaded halo pixel. (Measured: faster at 32 input channels,
-      // slower at 64, where the three loads per tile are kept.)
-      bf16x4_t hl[NCB];
-#pragma unroll
-      for (int t = 0; t < TPW; ++t) {
-#pragma unroll
-        for (int kx = 1; kx < 3; ++kx) {
-          const int xi = px[t] * 2 + kx - 1;
-          const int xc = min(max(xi, 0), a.Wi - 1);
-          load_blocks<CIN, CUP, IN, NCB>(a, yc, xc, 4 * kq, pin[t] && oky && xi < a.Wi,
-                                         bv[t][kx]);
-        }
-      }
-      {
-        const int xl = px[0] * 2 - 1;
-        load_blocks<CIN, CUP, IN, NCB>(a, yc, min(max(xl, 0), a.Wi - 1), 4 * kq,
-                                       oky && xl >= 0 && xl < a.Wi, hl);
-      }
-      const bool first = (lane & 15) == 0;
-#pragma unroll
-      for (int t = 0; t < TPW; ++t) {
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-          const bf16x4_t left = t == 0 ? hl[cb] : dpp_frag<kDppRowRor1>(bv[t - 1][2][cb]);
-          const bf16x4_t shr = dpp_frag<kDppRowShr1>(bv[t][2][cb]);
-          bv[t][0][cb] = first ? left : shr;
+        for (int nb = 0; nb < NB2; ++nb) {
+          f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f};
+          d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.w2[nb * 64 + lane], hv, d, 0, 0, 0);
+          if (px < a.Wo)
+            *reinterpret_cast<bf16x4_t*>(a.out + (row + px) * COUT2 + nb * 16 + 4 * kq) =
+                relu_round(d + load_bias(a.b2 + nb * 16 + 4 * kq));
         }
       }
     } else {
+      // Four output channels: the A operand repeats their rows in every row
+      // group, so that each lane group holds all four at its pixel; group g
+      // then finishes tile g: one sigmoid per lane and channel, and stores of
+      // whole rows of pixels.
+      static_assert(COUT2 == 4, "the head has four channels");
+      const bf16x4_t w2 = a.w2[(lane & 48) | (lane & 3)];
+      f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int t = 0; t < TPW; ++t) {
+        const int px = px0 + t * 16 + (lane & 15);
+        const bf16x4_t hv = relu_round(acc[t][0] + bias);
+        if (a.mid && px < a.Wo)
+          *reinterpret_cast<bf16x4_t*>(a.mid + (row + px) * 16 + 4 * kq) = hv;
+        f32x4_t e = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        e = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w2, hv, e, 0, 0, 0);
 #pragma unroll
-        for (int kx = 0; kx < KS; ++kx) {
-          const int xi = px[t] * ST + kx - P;
-          const bool ok = pin[t] && oky && xi >= 0 && xi < a.Wi;
-          const int xc = min(max(xi, 0), a.Wi - 1);
-          load_blocks<CIN, CUP, IN, NCB>(a, yc, xc, 4 * kq, ok, bv[t][kx]);
-        }
+        for (int i = 0; i < 4; ++i) d[i] = kq == t ? e[i] : d[i];
       }
-    }
+      const int px = px0 + kq * 16 + (lane & 15);
+      if (kq < TPW && px < a.Wo) {
+        const size_t pl = (size_t)a.Ho * a.Wo;
 #pragma unroll
-    for (int kx = 0; kx < KS; ++kx) {
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) {
-        const int tap = ky * KS + kx;
-        const int ks = (tap * NCB + cb) % KSPL;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          const bf16x4_t av = a.w[((tap * NCB + cb) * NB + nb) * 64 + lane];
-#pragma unroll
-          for (int t = 0; t < TPW; ++t)
-            acc[t][nb][ks] =
-                __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv[t][kx][cb], acc[t][nb][ks], 0, 0, 0);
-        }
+        for (int c = 0; c < 4; ++c)
+          a.outf[c * pl + row + px] = 1.f / (1.f + expf(-(d[c] + a.b2[c])));
       }
     }
   }
-  f32x4_t sum[TPW][NB];
-#pragma unroll
-  for (int t = 0; t < TPW; ++t)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      sum[t][nb] = acc[t][nb][0];
-#pragma unroll
-      for (int k = 1; k < KSPL; ++k) sum[t][nb] += acc[t][nb][k];
-    }
-#pragma unroll
-  for (int t = 0; t < TPW; ++t) epilogue<COUT, FUSE, COUT2>(a, y, px[t], pin[t], kq, lane, sum[t]);
 }
 
-// Stride-1 3x3 layers, input tile in LDS. A workgroup computes kTileRows
-// output rows (one per wave) of kTilePx pixels (four tiles of 16) for all
-// output channels. It first stages the (kTileRows + 2) x (kTilePx + 2) input
-// pixels of the tile with all their channels in LDS (HWC, 8-byte chunks,
-// zero outside the image; the decoder's upsampling and concatenation happen
-// here), so each input row is fetched by 1.5 output rows instead of 3, and
-// the MFMA B fragments are then read from LDS. The MFMA sequence is that of
-// conv_kernel, so the two give identical results.
-constexpr int kTileRows = 4, kTilePx = 64;
-constexpr int kStRows = kTileRows + 2, kStPx = kTilePx + 2;
-__host__ __device__ constexpr size_t conv_tile_lds_bytes(int cin) {
-  return (size_t)kStRows * kStPx * cin * sizeof(uint16_t);
-}
+// One 3x3 layer (CIN, COUT multiples of 16; stride ST), bias and ReLU,
+// optionally followed by a fused 1x1 layer to COUT2 channels (ReLU to HWC
+// BF16, or sigmoid to planar FP32).
+//
+// A workgroup computes four output rows (one per wave) of 16 TPW pixels for
+// all output channels. It first stages the input pixels of the tile with all
+// their channels in LDS (16-byte chunks, zero outside the image; the network
+// input's compression and the decoder's upsampling and concatenation happen
+// here), then reads the MFMA B fragments from there. LDS holds one plane per
+// 16-channel block, 32 bytes a pixel, so that the 16 pixels x 4 channel quads
+// of a fragment are 512 consecutive bytes; at stride 2 the even columns of a
+// row come first, then the odd ones, for the same reason. K steps run over
+// taps, then channel blocks, whatever the tile: results do not depend on it.
+template <int CIN, int ST, int TPW>
+struct ConvTile {
+  static constexpr int NCB = CIN / 16;
+  static constexpr int SR = 3 * ST + 3, SP = (16 * TPW - 1) * ST + 3;  // staged rows, columns
+  static constexpr int SPH = (SP + 1) / 2, SPL = ST == 2 ? 2 * SPH : SP;
+  static constexpr size_t lds_bytes() { return (size_t)NCB * SR * SPL * 32; }
+  // 16-channel unit of block cb, staged row sr, column sx
+  __device__ static int unit(int cb, int sr, int sx) {
+    return (cb * SR + sr) * SPL + (ST == 2 ? (sx & 1) * SPH + (sx >> 1) : sx);
+  }
+};
 
-template <int CIN, int COUT, int IN, int CUP, int FUSE, int COUT2>
-__global__ void __launch_bounds__(256) conv_tile_kernel(ConvArgs a) {
-  constexpr int NCB = CIN / 16, NB = COUT / 16, TPW = 4, KS = 3;
-  constexpr int CQ = CIN / 4;                   // 8-byte chunks per pixel
-  constexpr int NCH = kStRows * kStPx * CQ;     // chunks to stage
-  bf16x4_t* st = reinterpret_cast<bf16x4_t*>(flr::lds);
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, kq = lane >> 4;
-  const int x0 = blockIdx.x * kTilePx, y0 = blockIdx.y * kTileRows;
-  for (int b0 = 0; b0 < NCH; b0 += 8 * 256) {
-    bf16x4_t v[8];
-    bool ok[8];
+template <int CIN, int ST, int IN, int CUP, int TPW, bool EDGE>
+__device__ __forceinline__ void stage_tile(const ConvArgs& a, const int x0, const int y0) {
+  using T = ConvTile<CIN, ST, TPW>;
+  constexpr int NCH = CIN / 8;  // chunks per pixel
+  constexpr int NIT = T::SR * T::SP * NCH, B = 4;
+  uint4* st = reinterpret_cast<uint4*>(flr::lds);
+  const int tid = threadIdx.x;
+  const int yb = y0 * ST - 1, xb = x0 * ST - 1;  // the tile's first input pixel
+#pragma unroll 1
+  for (int b0 = 0; b0 < NIT; b0 += B * 256) {
+    uint4 v[B];
+    int dst[B];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int i = b0 + u * 256 + tid;
-      const int ic = i < NCH ? i : NCH - 1;
-      const int pix = ic / CQ, c = 4 * (ic - pix * CQ);
-      const int sr = pix / kStPx, sx = pix - sr * kStPx;
-      const int yi = y0 - 1 + sr, xi = x0 - 1 + sx;
-      ok[u] = i < NCH && yi >= 0 && yi < a.Hi && xi >= 0 && xi < a.Wi;
-      const int yc = min(max(yi, 0), a.Hi - 1), xc = min(max(xi, 0), a.Wi - 1);
+    for (int u = 0; u < B; ++u) {
+      const int i = b0 + u * 256 + tid, ic = i < NIT ? i : NIT - 1;
+      const int pix = ic / NCH, ch = ic - pix * NCH;
+      const int sr = pix / T::SP, sx = pix - sr * T::SP;
+      dst[u] = i < NIT ? T::unit(ch >> 1, sr, sx) * 2 + (ch & 1) : -1;
+      int y = yb + sr, x = xb + sx;
+      bool ok = true;
+      if constexpr (EDGE) {
+        ok = y >= 0 && y < a.Hi && x >= 0 && x < a.Wi;
+        y = min(max(y, 0), a.Hi - 1);
+        x = min(max(x, 0), a.Wi - 1);
+      }
       const uint16_t* src;
       if constexpr (IN == IN_UPCAT) {
         // one load from a selected address: the upsampled coarse half or the skip
-        // (both addresses in range: the unused one's channel is clamped)
-        const int cl = c < CUP ? c : CUP - 4, ch = c < CUP ? 0 : c - CUP;
-        const uint16_t* lo = a.in0 + ((size_t)(yc >> 1) * a.Wl + (xc >> 1)) * CUP + cl;
-        const uint16_t* hi = a.in1 + ((size_t)yc * a.Wi + xc) * (CIN - CUP) + ch;
-        src = c < CUP ? lo : hi;
+        const bool low = ch * 8 < CUP;
+        const size_t p = low ? (size_t)(y >> 1) * a.Wl + (x >> 1) : (size_t)y * a.Wi + x;
+        const size_t o = p * (low ? CUP : CIN - CUP) + (low ? ch * 8 : ch * 8 - CUP);
+        src = (low ? a.in0 : a.in1) + o;
       } else {
-        src = a.in0 + ((size_t)yc * a.Wi + xc) * CIN + c;
+        src = a.in0 + ((size_t)y * a.Wi + x) * CIN + ch * 8;
       }
-      v[u] = *reinterpret_cast<const bf16x4_t*>(src);
+      v[u] = *reinterpret_cast<const uint4*>(src);
+      if constexpr (EDGE) {
+        const uint32_t keep = ok ? 0xffffffffu : 0u;
+        v[u] = uint4{v[u].x & keep, v[u].y & keep, v[u].z & keep, v[u].w & keep};
+      }
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int i = b0 + u * 256 + tid;
-      if (i < NCH) st[i] = ok[u] ? v[u] : pack4(0, 0, 0, 0);
+    for (int u = 0; u < B; ++u)
+      if (dst[u] >= 0) st[dst[u]] = v[u];
+  }
+}
+
+// The network's input (IN_PLANES): compressed while it is staged, one pixel
+// per lane; x0, when set, receives the tile's own pixels (HWC, 16 channels).
+template <int TPW>
+__device__ __forceinline__ void stage_input(const ConvArgs& a, const int x0, const int y0) {
+  using T = ConvTile<16, 1, TPW>;
+  constexpr int NPX = T::SR * T::SP, NIN = FLR_NET_IN_GUIDES + FLR_NET_IN_NOISY;
+  bf16x4_t* st = reinterpret_cast<bf16x4_t*>(flr::lds);
+  const size_t pl = (size_t)a.Hi * a.Wi;
+#pragma unroll 1
+  for (int i = threadIdx.x; i < NPX; i += 256) {
+    const int sr = i / T::SP, sx = i - sr * T::SP;
+    const int y = y0 - 1 + sr, x = x0 - 1 + sx;
+    const bool ok = y >= 0 && y < a.Hi && x >= 0 && x < a.Wi;
+    const size_t p = (size_t)min(max(y, 0), a.Hi - 1) * a.Wi + min(max(x, 0), a.Wi - 1);
+    float v[12];
+#pragma unroll
+    for (int c = 0; c < NIN; ++c)
+      v[c] = c < FLR_NET_IN_GUIDES ? a.guides[c * pl + p] : a.noisy[(c - FLR_NET_IN_GUIDES) * pl + p];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) v[c] = c < NIN && ok ? compress(v[c]) : 0.f;
+    bf16x4_t h[4];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) h[q] = round4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    h[3] = pack4(0, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) st[T::unit(0, sr, sx) * 4 + q] = h[q];
+    if (a.x0 && ok && sr >= 1 && sr <= 4 && sx >= 1 && sx <= 16 * TPW) {
+      bf16x4_t* o = reinterpret_cast<bf16x4_t*>(a.x0 + p * 16);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = h[q];
     }
+  }
+}
+
+template <int CIN, int COUT, int ST, int IN, int CUP, int FUSE, int COUT2, int TPW>
+__global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
+  using T = ConvTile<CIN, ST, TPW>;
+  constexpr int NCB = T::NCB, NB = COUT / 16;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, kq = lane >> 4;
+  const int x0 = blockIdx.x * 16 * TPW, y0 = blockIdx.y * 4;
+  if constexpr (IN == IN_PLANES) {
+    stage_input<TPW>(a, x0, y0);
+  } else {
+    const bool edge = x0 == 0 || y0 == 0 || x0 * ST - 1 + T::SP > a.Wi ||
+                      y0 * ST - 1 + T::SR > a.Hi;
+    if (edge)
+      stage_tile<CIN, ST, IN, CUP, TPW, true>(a, x0, y0);
+    else
+      stage_tile<CIN, ST, IN, CUP, TPW, false>(a, x0, y0);
   }
   __syncthreads();
   const int y = y0 + wv;
   if (y >= a.Ho) return;  // uniform across the wave; no barrier follows
-  int px[TPW];
-  bool pin[TPW];
-#pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    px[t] = x0 + t * 16 + (lane & 15);
-    pin[t] = px[t] < a.Wo;
-  }
-  constexpr int KSPL = (TPW * NB >= 8) ? 1 : 8 / (TPW * NB);
+  const bf16x4_t* st = reinterpret_cast<const bf16x4_t*>(flr::lds);
+  // partial sums (K steps round-robin) for layers of one output block, so
+  // that enough independent MFMA chains are in flight per wave
+  constexpr int KSPL = NB >= 2 ? 1 : 2;
   f32x4_t acc[TPW][NB][KSPL];
 #pragma unroll
   for (int t = 0; t < TPW; ++t)
@@ -403,26 +317,24 @@ __global__ void __launch_bounds__(256) conv_tile_kernel(ConvArgs a) {
 #pragma unroll
       for (int k = 0; k < KSPL; ++k) acc[t][nb][k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int ky = 0; ky < KS; ++ky) {
+  for (int ky = 0; ky < 3; ++ky) {
 #pragma unroll
-    for (int kx = 0; kx < KS; ++kx) {
-      bf16x4_t bv[TPW][NCB];
-#pragma unroll
-      for (int t = 0; t < TPW; ++t)
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-          bv[t][cb] = st[((wv + ky) * kStPx + t * 16 + (lane & 15) + kx) * CQ + cb * 4 + kq];
+    for (int kx = 0; kx < 3; ++kx) {
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
-        const int tap = ky * KS + kx;
+        const int tap = ky * 3 + kx;
         const int ks = (tap * NCB + cb) % KSPL;
+        bf16x4_t bv[TPW];
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+          bv[t] = st[(T::unit(cb, wv * ST + ky, kx) + t * 16 + (lane & 15)) * 4 + kq];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
           const bf16x4_t av = a.w[((tap * NCB + cb) * NB + nb) * 64 + lane];
 #pragma unroll
           for (int t = 0; t < TPW; ++t)
             acc[t][nb][ks] =
-                __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv[t][cb], acc[t][nb][ks], 0, 0, 0);
+                __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv[t], acc[t][nb][ks], 0, 0, 0);
         }
       }
     }
@@ -436,8 +348,7 @@ __global__ void __launch_bounds__(256) conv_tile_kernel(ConvArgs a) {
 #pragma unroll
       for (int k = 1; k < KSPL; ++k) sum[t][nb] += acc[t][nb][k];
     }
-#pragma unroll
-  for (int t = 0; t < TPW; ++t) epilogue<COUT, FUSE, COUT2>(a, y, px[t], pin[t], kq, lane, sum[t]);
+  epilogue<COUT, FUSE, COUT2, TPW>(a, y, x0, lane, sum);
 }
 
 // Packing: FP32 weight [cout][cin][k][k] -> fragments (tap, cin block,
@@ -575,24 +486,34 @@ bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
   return a0 < b0 + nb && b0 < a0 + na;
 }
 
-template <int CIN, int COUT, int KS, int ST, int IN, int CUP, int FUSE, int COUT2>
-hipError_t launch(const ConvArgs& a, hipStream_t s) {
-  // (measured: the LDS tile is faster up to 48 input channels; at 96 its
-  // 76 KB tile allows two workgroups per CU and the direct kernel wins)
-  if constexpr (KS == 3 && ST == 1 && CIN <= 48) {
-    auto k = conv_tile_kernel<CIN, COUT, IN, CUP, FUSE, COUT2>;
-    const size_t lds = conv_tile_lds_bytes(CIN);
+// Tiles of 64 pixels where they give kConvMinGroups workgroups (two per CU),
+// else 32, else 16: at training-crop sizes the half and quarter grids would
+// otherwise leave most CUs idle. 96 input channels: at most 32 pixels (64
+// would fill half a CU's LDS).
+constexpr int kConvMinGroups = 512;
+template <int CIN, int COUT, int ST, int IN, int CUP, int FUSE, int COUT2, int TPW>
+hipError_t launch_tpw(const ConvArgs& a, hipStream_t s) {
+  auto k = conv_kernel<CIN, COUT, ST, IN, CUP, FUSE, COUT2, TPW>;
+  const size_t lds = ConvTile<CIN, ST, TPW>::lds_bytes();
+  if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, dim3((a.Wo + kTilePx - 1) / kTilePx, (a.Ho + kTileRows - 1) / kTileRows),
-                       dim3(256), lds, s, a);
-    return hipGetLastError();
   }
-  constexpr int px_per_block = 4 * tiles_per_wave(CIN) * 16;
-  hipLaunchKernelGGL((conv_kernel<CIN, COUT, KS, ST, IN, CUP, FUSE, COUT2>),
-                     dim3((a.Wo + px_per_block - 1) / px_per_block, a.Ho), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k, dim3((a.Wo + 16 * TPW - 1) / (16 * TPW), (a.Ho + 3) / 4), dim3(256), lds, s,
+                     a);
   return hipGetLastError();
+}
+template <int CIN, int COUT, int ST, int IN, int CUP, int FUSE, int COUT2>
+hipError_t launch(const ConvArgs& a, hipStream_t s) {
+  constexpr int MAX = CIN * ST >= 64 ? 2 : 4;
+  const int rows = (a.Ho + 3) / 4;
+  if constexpr (MAX == 4)
+    if ((a.Wo + 63) / 64 * rows >= kConvMinGroups)
+      return launch_tpw<CIN, COUT, ST, IN, CUP, FUSE, COUT2, 4>(a, s);
+  if ((a.Wo + 31) / 32 * rows >= kConvMinGroups)
+    return launch_tpw<CIN, COUT, ST, IN, CUP, FUSE, COUT2, 2>(a, s);
+  return launch_tpw<CIN, COUT, ST, IN, CUP, FUSE, COUT2, 1>(a, s);
 }
 
 // The forward pass into the activation buffers at the start of ws (the
@@ -619,44 +540,40 @@ flr_status run_forward(const Grids& g, const float* guides, const float* noisy, 
     return a;
   };
   hipError_t e;
-  {  // input compression and layout
-    const PrepArgs pa = {guides, noisy, x0, g.H, g.W};
-    const size_t n = (size_t)g.H * g.W;
-    hipLaunchKernelGGL(prep_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pa);
-    if (hipGetLastError() != hipSuccess) return FLR_ERR_HIP;
-  }
   {  // in3 + in1 -> e0
     ConvArgs a = args(0, g.H, g.W, g.H, g.W);
-    a.in0 = x0;
+    a.guides = guides;
+    a.noisy = noisy;
+    a.x0 = mid_in3 ? x0 : nullptr;  // the backward and the trace read it
     a.w2 = layer_w(packed, 1);
     a.b2 = layer_b(packed, 1);
     a.out = e0;
     a.mid = mid_in3;
-    if ((e = launch<16, 16, 3, 1, IN_HWC, 0, FUSE_1X1_RELU, 16>(a, s)) != hipSuccess) return FLR_ERR_HIP;
+    if ((e = launch<16, 16, 1, IN_PLANES, 0, FUSE_1X1_RELU, 16>(a, s)) != hipSuccess) return FLR_ERR_HIP;
   }
   {  // e1a
     ConvArgs a = args(2, g.H, g.W, g.H, g.W);
     a.in0 = e0;
     a.out = t1;
-    if ((e = launch<16, 32, 3, 1, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
+    if ((e = launch<16, 32, 1, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
   }
   {  // e1b (stride 2)
     ConvArgs a = args(3, g.H, g.W, g.Hh, g.Wh);
     a.in0 = t1;
     a.out = e1;
-    if ((e = launch<32, 32, 3, 2, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
+    if ((e = launch<32, 32, 2, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
   }
   {  // e2a
     ConvArgs a = args(4, g.Hh, g.Wh, g.Hh, g.Wh);
     a.in0 = e1;
     a.out = t2;
-    if ((e = launch<32, 64, 3, 1, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
+    if ((e = launch<32, 64, 1, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
   }
   {  // e2b (stride 2)
     ConvArgs a = args(5, g.Hh, g.Wh, g.Hq, g.Wq);
     a.in0 = t2;
     a.out = e2;
-    if ((e = launch<64, 64, 3, 2, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
+    if ((e = launch<64, 64, 2, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
   }
   {  // d1a: [up2(e2), e1]
     ConvArgs a = args(6, g.Hh, g.Wh, g.Hh, g.Wh);
@@ -665,13 +582,13 @@ flr_status run_forward(const Grids& g, const float* guides, const float* noisy, 
     a.Wl = g.Wq;
     a.in1 = e1;
     a.out = t3;
-    if ((e = launch<96, 32, 3, 1, IN_UPCAT, 64, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
+    if ((e = launch<96, 32, 1, IN_UPCAT, 64, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
   }
   {  // d1b
     ConvArgs a = args(7, g.Hh, g.Wh, g.Hh, g.Wh);
     a.in0 = t3;
     a.out = d1;
-    if ((e = launch<32, 32, 3, 1, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
+    if ((e = launch<32, 32, 1, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
   }
   {  // d0a: [up2(d1), e0]
     ConvArgs a = args(8, g.H, g.W, g.H, g.W);
@@ -680,13 +597,13 @@ flr_status run_forward(const Grids& g, const float* guides, const float* noisy, 
     a.Wl = g.Wh;
     a.in1 = e0;
     a.out = t4;
-    if ((e = launch<48, 16, 3, 1, IN_UPCAT, 32, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
+    if ((e = launch<48, 16, 1, IN_UPCAT, 32, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
   }
   {  // d0b
     ConvArgs a = args(9, g.H, g.W, g.H, g.W);
     a.in0 = t4;
     a.out = t5;
-    if ((e = launch<16, 16, 3, 1, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
+    if ((e = launch<16, 16, 1, IN_HWC, 0, FUSE_NONE, 0>(a, s)) != hipSuccess) return FLR_ERR_HIP;
   }
   {  // out3 + out1 (sigmoid) -> planar FP32
     ConvArgs a = args(10, g.H, g.W, g.H, g.W);
@@ -695,7 +612,7 @@ flr_status run_forward(const Grids& g, const float* guides, const float* noisy, 
     a.b2 = layer_b(packed, 11);
     a.outf = out;
     a.mid = mid_out3;
-    if ((e = launch<16, 16, 3, 1, IN_HWC, 0, FUSE_1X1_SIGMOID, FLR_NET_OUT>(a, s)) != hipSuccess)
+    if ((e = launch<16, 16, 1, IN_HWC, 0, FUSE_1X1_SIGMOID, FLR_NET_OUT>(a, s)) != hipSuccess)
       return FLR_ERR_HIP;
   }
   return FLR_OK;
