@@ -99,10 +99,14 @@ typedef enum { FLR_REG_RIDGE = 0, FLR_REG_PAPER = 1 } flr_reg_mode;
 /* flr_denoise execution paths (flr_params.fused) */
 typedef enum {
   FLR_PATH_STAGES = 0,   /* flr_moments -> flr_solve -> flr_apply, images in the workspace */
-  FLR_PATH_FUSED = 1,    /* one kernel: moments, solve, average, reconstruction; with
-                            averaging, coefficients pass through a per-workgroup ring
-                            in the workspace and r coefficient rows are recomputed at
-                            each workgroup's top and bottom */
+  FLR_PATH_FUSED = 1,    /* without averaging: one kernel for moments, solve and
+                            reconstruction; with averaging: as TWO_PASS where the
+                            workspace holds its coefficient image (what
+                            flr_denoise_workspace_bytes asks for), else one kernel
+                            whose coefficients pass through a per-workgroup ring in
+                            the workspace, r coefficient rows recomputed at each
+                            workgroup's top and bottom (slower, and on large frames
+                            a smaller workspace) */
   FLR_PATH_TWO_PASS = 2  /* with averaging: one kernel for moments and solve writing the
                             coefficient image to the workspace, then the averaging and
                             reconstruction of flr_apply; the image holds each intercept
@@ -157,13 +161,14 @@ size_t flr_num_coeff_planes(int32_t num_guides, int32_t num_channels);
 /* Workspace bytes flr_denoise needs for these parameters (0 if invalid):
  * FLR_PATH_STAGES: the moment and coefficient images, (M + F*C)*H*W floats
  * (the coefficient image starts at the next 256-byte boundary);
- * FLR_PATH_FUSED with averaging: a per-workgroup ring of 2r+1 coefficient rows;
- * FLR_PATH_TWO_PASS with averaging: the coefficient image with intercept
+ * FLR_PATH_FUSED, FLR_PATH_TWO_PASS with averaging: the coefficient image with intercept
  * pairs, (F + 1)*C*H*W floats (F = Q + 1; when Q + C + Q(Q+1)/2 + Q*C
  * exceeds 78 moment channels the walk is split in two: first a moment
  * image of M planes, of which the first slice's are written, then the
  * coefficient image at the next 256-byte boundary);
- * without averaging: 0 (STAGES aside). Depends on the launch geometry only. */
+ * without averaging: 0 (STAGES aside). Depends on the launch geometry only.
+ * FLR_PATH_FUSED also takes a smaller workspace that holds its ring: per
+ * workgroup 2r+1 rows of (Q+1)*C*256 floats. */
 size_t flr_denoise_workspace_bytes(const flr_params* p);
 
 /* Window moments (Sec. 3.2). Reads guides, noisy; writes moments [M][H][W]. */

@@ -108,6 +108,14 @@ size_t unfused_coeff_offset(const flr_params* p) {
   return (mb + 255) / 256 * 256;
 }
 
+// Workspace of the two-pass path: the coefficient image b (hi), a, b (lo),
+// after the first slice's moment planes when the walk is split.
+size_t two_pass_bytes(const flr_params* p) {
+  const int Q = p->num_guides, C = p->num_channels;
+  const size_t cb = (size_t)(Q + 2) * C * plane_bytes(p);
+  return flr::split_walk(Q, C) ? unfused_coeff_offset(p) + cb : cb;
+}
+
 // Workspace of flr_denoise_backward, byte offsets of 256-aligned FP64
 // regions: the window sums of the anchored input products (later reused for
 // the window sums of the solve fields), the coefficients a, the window sums
@@ -327,13 +335,9 @@ size_t flr_denoise_workspace_bytes(const flr_params* p) {
   if (p->fused == FLR_PATH_STAGES)
     return unfused_coeff_offset(p) + flr_num_coeff_planes(p->num_guides, p->num_channels) * pb;
   if (!p->average_coeffs) return 0;
-  // the two-pass path's coefficient image: b (hi), a, then b (lo)
-  const size_t cb = (flr_num_coeff_planes(p->num_guides, p->num_channels) + p->num_channels) * pb;
-  if (p->fused == FLR_PATH_TWO_PASS && !flr::split_walk(p->num_guides, p->num_channels))
-    return cb;
-  if (p->fused == FLR_PATH_TWO_PASS)  // split walks: first slice's moment planes, coefficients
-    return unfused_coeff_offset(p) + cb;
-  return ring_bytes(p);
+  // the two-pass path and, as the faster form wherever it was measured, the
+  // fused path (flr_denoise)
+  return two_pass_bytes(p);
 }
 
 flr_status flr_moments(const flr_params* p, const float* guides, const float* noisy,
@@ -431,7 +435,22 @@ flr_status flr_denoise(const flr_params* p_in, const float* guides, const float*
   if (overlaps(out, ob, guides, p->num_guides * pb) ||
       overlaps(out, ob, noisy, p->num_channels * pb))
     return FLR_ERR_ALIAS;
-  const size_t need = flr_denoise_workspace_bytes(p);
+  size_t need = flr_denoise_workspace_bytes(p);
+  // FLR_PATH_FUSED with averaging runs as the two-pass path where the
+  // workspace holds its coefficient image (and overlaps nothing there); a
+  // workspace that only holds the one-kernel form's ring gets that form.
+  // Measured, one kernel / two: 64 x 96, Q = 4, C = 1 51 / 14 us; 256 x 256,
+  // Q = 4, C = 1 59 / 19; 717 x 1283, Q = 6, C = 3, r = 5 238 / 155; 1080p,
+  // Q = 3, C = 1, r = 3 119 / 94; 1080p, Q = 8, C = 3 654 / 397: one kernel's
+  // ring leaves L2, its segments recompute 2r coefficient rows each, and small
+  // frames give it a few long segments.
+  bool two_pass = p->fused == FLR_PATH_TWO_PASS && p->average_coeffs;
+  if (p->fused == FLR_PATH_FUSED && p->average_coeffs) {
+    const size_t gb = p->num_guides * pb, nb = p->num_channels * pb;
+    two_pass = workspace && workspace_bytes >= need && !overlaps(workspace, need, guides, gb) &&
+               !overlaps(workspace, need, noisy, nb) && !overlaps(workspace, need, out, ob);
+    if (!two_pass) need = ring_bytes(p);
+  }
   if (need > 0) {
     if (!workspace || workspace_bytes < need) return FLR_ERR_WORKSPACE;
     if (!aligned16(workspace)) return FLR_ERR_ALIGN;
@@ -451,7 +470,7 @@ flr_status flr_denoise(const flr_params* p_in, const float* guides, const float*
     plan(p, flr::K_APPLY_AVG, &a);
     return dispatch(Q, C, flr::K_APPLY_AVG, a, stream);
   };
-  if (p->fused == FLR_PATH_TWO_PASS && p->average_coeffs && !flr::split_walk(Q, C)) {
+  if (two_pass && !flr::split_walk(Q, C)) {
     float* coeffs = static_cast<float*>(workspace);
     LaunchArgs a = base_args(p);
     a.guides = guides;
@@ -462,7 +481,7 @@ flr_status flr_denoise(const flr_params* p_in, const float* guides, const float*
     if ((st = dispatch(Q, C, flr::K_COEFFS, a, stream)) != FLR_OK) return st;
     return apply_lo(coeffs);
   }
-  if (p->fused == FLR_PATH_TWO_PASS && p->average_coeffs) {
+  if (two_pass) {
     // Too many moment channels for one LDS-resident walk: the walk over the
     // first slice of the product channels writes its moment planes, the
     // walk over the second reads them back at each pixel and solves there
