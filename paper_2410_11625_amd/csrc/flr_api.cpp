@@ -52,9 +52,9 @@ void plan(const flr_params* p, int kind, LaunchArgs* a) {
                   &a->n_seg, &a->seg_rows);
     return;
   }
-  flr::plan_walk(kind, p->height, p->width, p->radius, p->tile_rows, &a->tiles_x, &a->n_seg,
-                 &a->seg_rows);
   const int Q = p->num_guides, C = p->num_channels, r = p->radius;
+  flr::plan_walk(kind, p->height, p->width, Q, C, r, p->tile_rows, &a->tiles_x, &a->n_seg,
+                 &a->seg_rows);
   const int ncoef = flr::kThreads - 2 * r;
   const flr::WalkLayout L = flr::walk_layout(Q, C, kind);
   a->hchunk_m = L.mg > 0 ? flr::plan_chunk(L.mg, ncoef, r) : 1;
@@ -87,8 +87,8 @@ flr_status dispatch(int Q, int C, int kind, const LaunchArgs& a, void* stream) {
 
 size_t ring_bytes(const flr_params* p) {
   int tiles_x, n_seg, seg_rows;
-  flr::plan_walk(flr::K_FUSED1, p->height, p->width, p->radius, p->tile_rows, &tiles_x, &n_seg,
-                 &seg_rows);
+  flr::plan_walk(flr::K_FUSED1, p->height, p->width, p->num_guides, p->num_channels, p->radius,
+                 p->tile_rows, &tiles_x, &n_seg, &seg_rows);
   return (size_t)tiles_x * n_seg *
          flr::ring_bytes_per_block(p->num_guides, p->num_channels, p->radius);
 }

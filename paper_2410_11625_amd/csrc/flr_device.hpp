@@ -571,7 +571,8 @@ __device__ __forceinline__ void walk_tile(const LaunchArgs a, const int bid) {
   const HWin hw = hwin<WIDE>(tid, r);
   // zero pad column of every prefix row of both buffers (no other pass
   // writes column kThreads; the first group's barrier orders these stores)
-  for (int m = tid; m < 2 * MG; m += kThreads) (m < MG ? S0 : S1)[(m % MG) * kLdsStride + kThreads] = sum_t(0);
+  constexpr int NPAD = LAY.b ? 2 * MG : MG;
+  for (int m = tid; m < NPAD; m += kThreads) (m < MG ? S0 : S1)[(m % MG) * kLdsStride + kThreads] = sum_t(0);
 
   float cg[Q];
   {

@@ -333,38 +333,6 @@ inline int avg_groups(int tiles, int C) {
 // Rows of coefficient halo a walker recomputes above and below its segment.
 inline int row_halo(int kind, int r) { return kind == K_FUSED1 ? r : 0; }
 
-// Pick tiles and segments. With tile_rows > 0 the caller fixes the segment
-// length; otherwise minimise (workgroup waves) x (rows walked per segment).
-// K_MOMENTS, K_FUSED0 and K_COEFFS have no coefficient-row halo.
-inline void plan_walk(int kind, int H, int W, int r, int tile_rows, int* tiles_x, int* n_seg,
-                      int* seg_rows) {
-  const int tout = strip_out_cols(kind, r);
-  *tiles_x = ceil_div(W, tout);
-  if (tile_rows > 0) {
-    *seg_rows = tile_rows < H ? tile_rows : H;
-    *n_seg = ceil_div(H, *seg_rows);
-    return;
-  }
-  const int hc = row_halo(kind, r);
-  double best = 1e300;
-  int best_n = 1;
-  const int nmax = H < 4096 ? H : 4096;
-  for (int n = 1; n <= nmax; ++n) {
-    const int R = ceil_div(H, n);
-    if (n > 1 && ceil_div(H, n - 1) == R) continue;
-    const int wgs = *tiles_x * n;
-    const double waves = (double)ceil_div(wgs, kCUs);
-    // rows solved per segment plus a share for the moment warm-up rows
-    const double cost = waves * ((double)R + 2.0 * hc + 0.5 * r) + 1e-3 * n;
-    if (cost < best) {
-      best = cost;
-      best_n = n;
-    }
-  }
-  *seg_rows = ceil_div(H, best_n);
-  *n_seg = ceil_div(H, *seg_rows);
-}
-
 // Tiles of the averaging kernel: tile_rows, when set; else, for r <= 8, four
 // rows where they give kAvgMinGroups workgroups (tile and channel), so that
 // a plane row is fetched (4 + 2r) / 4 times instead of (2 + 2r) / 2, and two
@@ -450,12 +418,63 @@ __host__ __device__ constexpr WalkLayout walk_layout(int Q, int C, int kind, int
   const size_t m = (size_t)L.mg * row_s;
   const size_t c = (size_t)L.ag * row_t;
   L.a = L.b = m > c ? m : c;
+  // all channels in one group, resident in LDS: the second buffer is not used
+  if (kind != K_FUSED1 && L.mg >= ns) L.b = 0;
   return L;
 }
 
 inline size_t walk_lds_bytes(int kind, int Q, int C, int ns_walk = -1) {
   const WalkLayout L = walk_layout(Q, C, kind, ns_walk);
   return L.a + L.b + L.va;
+}
+
+// Workgroups of a walker kernel that share a CU (by LDS; registers allow four).
+inline int workgroups_per_cu(int kind, int Q, int C) {
+  if (kind == K_FUSED1) return 1;
+  const int n = (int)(kLdsBytes / walk_lds_bytes(kind, Q, C));
+  return n < 1 ? 1 : (n > 4 ? 4 : n);
+}
+// Time of a row step with k workgroups on a CU, against one alone. Measured
+// at 1080p, Q = 4, C = 1: one workgroup per CU 2.24 us per row, two 2.8, four
+// 5 (one wave per SIMD leaves most issue slots empty, four fill them).
+inline double shared_step(int k) { return k <= 1 ? 1.0 : 0.15 + 0.55 * k; }
+
+// Pick tiles and segments. With tile_rows > 0 the caller fixes the segment
+// length; otherwise minimise the rounds of workgroups, each the rows walked
+// per segment at the speed of the workgroups that then share a CU. Measured,
+// coefficients at 1080p, Q = 4, C = 1: segments of 34 rows (one workgroup per
+// CU) 88.7 us, of 17 (two) 62.8, of 9 (four) 68.9; Q = 6, C = 1 130 / 96.5.
+// K_MOMENTS, K_FUSED0 and K_COEFFS have no coefficient-row halo.
+inline void plan_walk(int kind, int H, int W, int Q, int C, int r, int tile_rows, int* tiles_x,
+                      int* n_seg, int* seg_rows) {
+  const int tout = strip_out_cols(kind, r);
+  *tiles_x = ceil_div(W, tout);
+  if (tile_rows > 0) {
+    *seg_rows = tile_rows < H ? tile_rows : H;
+    *n_seg = ceil_div(H, *seg_rows);
+    return;
+  }
+  const int hc = row_halo(kind, r);
+  const int per_cu = workgroups_per_cu(kind, Q, C);
+  double best = 1e300;
+  int best_n = 1;
+  const int nmax = H < 4096 ? H : 4096;
+  for (int n = 1; n <= nmax; ++n) {
+    const int R = ceil_div(H, n);
+    if (n > 1 && ceil_div(H, n - 1) == R) continue;
+    const int wgs = *tiles_x * n;
+    const int full = wgs / (kCUs * per_cu), rest = wgs - full * kCUs * per_cu;
+    const double rounds = full * shared_step(per_cu) +
+                          (rest > 0 ? shared_step(ceil_div(rest, kCUs)) : 0.0);
+    // rows solved per segment plus a share for the moment warm-up rows
+    const double cost = rounds * ((double)R + 2.0 * hc + 0.5 * r) + 1e-3 * n;
+    if (cost < best) {
+      best = cost;
+      best_n = n;
+    }
+  }
+  *seg_rows = ceil_div(H, best_n);
+  *n_seg = ceil_div(H, *seg_rows);
 }
 
 // LDS of the persistent batch kernel: the larger of the walk's and the
