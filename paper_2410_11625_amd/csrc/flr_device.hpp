@@ -518,6 +518,78 @@ enum WalkMode : int { W_MOMENTS = 0, W_FUSED0 = 1, W_FUSED1 = 2, W_COEFFS = 3, W
 // POFF, PCNT: the slice of product channels this walker carries (all by
 // default); W_MOMENTS over a slice writes that slice's planes (and, for the
 // first slice, n and the means).
+// What a moment or coefficient walker writes at pixel `off` from its centred
+// moments: the moment planes (W_MOMENTS), or the coefficient planes of the
+// regularised fit (W_COEFFS, W_SPLITSOLVE).
+template <int Q, int C, int MODE, int POFF, int PC>
+__device__ __forceinline__ void walk_emit(const LaunchArgs& a, const int64_t pl, const int64_t off,
+                                          const int ni, const float (&cg)[Q],
+                                          const solve_t (&mu)[Q], const solve_t (&nu)[C],
+                                          chol_t (&Hm)[Q * (Q + 1) / 2], chol_t (&R)[Q * C]) {
+  using T = solve_t;
+  constexpr int NP = Q * (Q + 1) / 2;
+  if constexpr (MODE == W_MOMENTS) {
+    // a slice writes its own product planes; the first one also n, mu, nu
+    if (POFF == 0) a.out[off] = (float)ni;
+    if (!a.raw) {
+      if (POFF == 0) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) a.out[(1 + q) * pl + off] = (float)(mu[q] + (T)cg[q]);
+#pragma unroll
+        for (int c = 0; c < C; ++c) a.out[(1 + Q + c) * pl + off] = (float)nu[c];
+      }
+#pragma unroll
+      for (int k = POFF; k < POFF + PC; ++k)
+        a.out[(1 + Q + C + k) * pl + off] = k < NP ? (float)Hm[k] : (float)R[k - NP];
+    }
+  } else {
+    if constexpr (MODE == W_SPLITSOLVE) {
+      // the first slice's product channels: central moments written by
+      // the walk over that slice (shift-free, so the anchors agree)
+#pragma unroll
+      for (int k = 0; k < POFF; ++k) {
+        const chol_t v = (chol_t)a.planes[(int64_t)(1 + Q + C + k) * pl + off];
+        if (k < NP)
+          Hm[k] = v;
+        else
+          R[k - NP] = v;
+      }
+    }
+    T mu_o[Q];
+    chol_t mu_c[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      mu_o[q] = mu[q] + (T)cg[q];
+      mu_c[q] = (chol_t)mu_o[q];
+    }
+    regularise<Q, chol_t>(Hm, mu_c, (chol_t)arg_eps(a), (chol_t)arg_eps_mul(a), a.reg_mode);
+    chol_solve<Q, C, chol_t>(Hm, R);
+    // b = nu - a^T mu in original units
+    if (a.coef_lo) {
+      // from the slopes as stored, kept as hi + lo
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        T b = nu[c];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) b = fma_t(-(T)(float)R[q * C + c], mu_o[q], b);
+        const float hi = (float)b;
+        a.out[c * pl + off] = hi;
+        a.out[((Q + 1) * C + c) * pl + off] = (float)(b - (T)hi);
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        T b = nu[c];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) b = fma_t(-(T)R[q * C + c], mu_o[q], b);
+        a.out[c * pl + off] = (float)b;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < Q * C; ++k) a.out[(C + k) * pl + off] = (float)R[k];
+  }
+}
+
 // One workgroup's tile (strip sx = bid % tiles_x, segment bid / tiles_x) of
 // frame a.
 template <int Q, int C, int MODE, bool WIDE, int POFF = 0, int PCNT = -1>
@@ -776,33 +848,9 @@ __device__ __forceinline__ void walk_tile(const LaunchArgs a, const int bid) {
         read_group(gi);
       }
       if (cvalid) {
-        if (MODE == W_MOMENTS) {
-          // a slice writes its own product planes; the first one also n, mu, nu
-          if (POFF == 0) a.out[off] = (float)ni;
-          if (!a.raw) {
-            if (POFF == 0) {
-#pragma unroll
-              for (int q = 0; q < Q; ++q) a.out[(1 + q) * pl + off] = (float)(mu[q] + (T)cg[q]);
-#pragma unroll
-              for (int c = 0; c < C; ++c) a.out[(1 + Q + c) * pl + off] = (float)nu[c];
-            }
-#pragma unroll
-            for (int k = POFF; k < POFF + PC; ++k)
-              a.out[(1 + Q + C + k) * pl + off] = k < NP ? (float)Hm[k] : (float)R[k - NP];
-          }
+        if constexpr (MODE == W_MOMENTS || MODE == W_COEFFS || MODE == W_SPLITSOLVE) {
+          walk_emit<Q, C, MODE, POFF, PC>(a, pl, off, ni, cg, mu, nu, Hm, R);
         } else {
-          if constexpr (MODE == W_SPLITSOLVE) {
-            // the first slice's product channels: central moments written by
-            // the walk over that slice (shift-free, so the anchors agree)
-#pragma unroll
-            for (int k = 0; k < POFF; ++k) {
-              const chol_t v = (chol_t)a.planes[(int64_t)(1 + Q + C + k) * pl + off];
-              if (k < NP)
-                Hm[k] = v;
-              else
-                R[k - NP] = v;
-            }
-          }
           T mu_o[Q];
           chol_t mu_c[Q];
 #pragma unroll
@@ -812,31 +860,7 @@ __device__ __forceinline__ void walk_tile(const LaunchArgs a, const int bid) {
           }
           regularise<Q, chol_t>(Hm, mu_c, (chol_t)arg_eps(a), (chol_t)arg_eps_mul(a), a.reg_mode);
           chol_solve<Q, C, chol_t>(Hm, R);
-          if (MODE == W_COEFFS || MODE == W_SPLITSOLVE) {
-            // b = nu - a^T mu in original units
-            if (a.coef_lo) {
-              // from the slopes as stored, kept as hi + lo
-#pragma unroll
-              for (int c = 0; c < C; ++c) {
-                T b = nu[c];
-#pragma unroll
-                for (int q = 0; q < Q; ++q) b = fma_t(-(T)(float)R[q * C + c], mu_o[q], b);
-                const float hi = (float)b;
-                a.out[c * pl + off] = hi;
-                a.out[((Q + 1) * C + c) * pl + off] = (float)(b - (T)hi);
-              }
-            } else {
-#pragma unroll
-              for (int c = 0; c < C; ++c) {
-                T b = nu[c];
-#pragma unroll
-                for (int q = 0; q < Q; ++q) b = fma_t(-(T)R[q * C + c], mu_o[q], b);
-                a.out[c * pl + off] = (float)b;
-              }
-            }
-#pragma unroll
-            for (int k = 0; k < Q * C; ++k) a.out[(C + k) * pl + off] = (float)R[k];
-          } else if (MODE == W_FUSED0) {
+          if (MODE == W_FUSED0) {
             T gp[Q];
 #pragma unroll
             for (int q = 0; q < Q; ++q) gp[q] = ((T)a.guides[q * pl + off] - (T)cg[q]) - mu[q];
@@ -928,6 +952,201 @@ __global__ void __launch_bounds__(kThreads, 1) walk_kernel(LaunchArgs ain) {
   int bid = blockIdx.x;
   const LaunchArgs a = BATCH ? batch_frame(ain, &bid) : ain;
   walk_tile<Q, C, MODE, WIDE, POFF, PCNT>(a, bid);
+}
+
+// The walker of W_COEFFS and W_MOMENTS as two wave groups (walkers whose
+// moment channels fill both LDS groups, which leaves a CU one workgroup). A
+// workgroup is twice kThreads: waves 0..3 own the columns and bring the LDS
+// prefix rows from one image row to the next, waves 4..7 read the windows,
+// solve and store. The groups A and B of prefix rows pass between them at two
+// barriers per row:
+//   waves 0..3:  A(y0) | B(y)       | A(y + 1)               | B(y + 1) ...
+//   waves 4..7:        | windows A(y) | windows B(y), solve, store | windows A(y + 1) ...
+// so that each SIMD holds one wave of either kind and one's latencies are
+// the other's issue slots; neither needs more than 256 registers. The
+// arithmetic and its order are walk_tile's: the results are the same bits.
+// Measured against walk_tile (one wave per SIMD doing both in turn): 1080p,
+// Q = 8, C = 3 279 -> 212 us; 717 x 1283, Q = 6, C = 3, r = 5 95 -> 72; the first
+// slice of 720p, Q = 12, C = 3 146 -> 113.
+template <int Q, int C, int MODE, bool WIDE, int POFF, int PCNT>
+__device__ __forceinline__ void walk_pair_tile(const LaunchArgs a, const int bid) {
+  using D = Dims<Q, C>;
+  using T = solve_t;
+  constexpr int NPQ = D::NP + D::NQC;
+  constexpr int PC = PCNT < 0 ? NPQ : PCNT;
+  constexpr int NS = Q + C + PC;
+  constexpr int NP = D::NP;
+  constexpr WalkLayout LAY = walk_layout(Q, C, MODE == W_MOMENTS ? K_MOMENTS : K_COEFFS, NS);
+  constexpr int MG = LAY.mg;
+  static_assert((NS + MG - 1) / MG == 2, "two LDS groups of channels");
+  constexpr int IL = 4;  // channels whose lane moves interleave
+  extern __shared__ float lds[];
+  sum_t* S0 = reinterpret_cast<sum_t*>(lds);
+  sum_t* S1 = reinterpret_cast<sum_t*>(reinterpret_cast<char*>(lds) + LAY.a);
+  const int role = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);
+  const int tid = (int)threadIdx.x % kThreads;
+  const int r = a.r, H = a.H, W = a.W;
+  const int64_t pl = (int64_t)H * W;
+  const int tout = kThreads - 2 * r;
+  const int sx = bid % a.tiles_x;
+  const int X0 = sx * tout;
+  const int Y0 = bid / a.tiles_x * a.seg_rows;
+  const int Y1 = min(Y0 + a.seg_rows, H);
+  float cg[Q];
+  {
+    const int yr = min((Y0 + Y1) / 2, H - 1), xr = min(X0 + tout / 2, W - 1);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) cg[q] = a.raw ? 0.f : a.guides[q * pl + (int64_t)yr * W + xr];
+  }
+  if (role == 0) {
+    const int xi = X0 - r + tid;  // input column of this lane
+    const bool xin = xi >= 0 && xi < W;
+    for (int m = tid; m < 2 * MG; m += kThreads)
+      (m < MG ? S0 : S1)[(m % MG) * kLdsStride + kThreads] = sum_t(0);
+    {
+      // rows [Y0 - r, Y0 + r) of the first window, each row's loads issued
+      // one step ahead, then their prefixes
+      sum_t V[NS], zg[Q], zy[C];
+#pragma unroll
+      for (int m = 0; m < NS; ++m) V[m] = sum_t(0);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) zg[q] = sum_t(0);
+#pragma unroll
+      for (int c = 0; c < C; ++c) zy[c] = sum_t(0);
+      float wb[Q + C];
+      bool wok = xin && Y0 - r >= 0 && Y0 - r < H;
+      load_raw<Q, C>(a, pl, (int64_t)(Y0 - r) * W + xi, wok, wb);
+      for (int yy = Y0 - r; yy < Y0 + r; ++yy) {
+        float cur[Q + C];
+#pragma unroll
+        for (int i = 0; i < Q + C; ++i) cur[i] = wb[i];
+        const bool cok = wok;
+        if (yy + 1 < Y0 + r) {
+          wok = xin && yy + 1 >= 0 && yy + 1 < H;
+          load_raw<Q, C>(a, pl, (int64_t)(yy + 1) * W + xi, wok, wb);
+        }
+        sum_t g[Q], y[C];
+        shift_raw<Q, C>(cur, cok, cg, g, y);
+        vupdate<Q, C, POFF, PC>(V, g, y, zg, zy);
+      }
+#pragma unroll
+      for (int m0 = 0; m0 < NS; m0 += IL) {
+        sum_t x[IL];
+#pragma unroll
+        for (int i = 0; i < IL; ++i) x[i] = m0 + i < NS ? V[m0 + i] : sum_t(0);
+        seg_prefix_n<WIDE>(x);
+#pragma unroll
+        for (int i = 0; i < IL; ++i)
+          if (m0 + i < NS)
+            (m0 + i < MG ? S0 : S1)[(m0 + i) % MG * kLdsStride + tid] = x[i];
+      }
+    }
+    float fa[Q + C], fs[Q + C];
+    bool okA = false, okS = false;
+    auto fetch = [&](int y) {
+      const int ya = y + r, ys = y - r - 1;
+      okA = xin && ya >= 0 && ya < H;
+      okS = xin && y > Y0 && ys >= 0 && ys < H;
+      load_raw<Q, C>(a, pl, (int64_t)ya * W + xi, okA, fa);
+      load_raw<Q, C>(a, pl, (int64_t)ys * W + xi, okS, fs);
+    };
+    sum_t ga[Q], yA[C], gs[Q], yS[C];
+    // prefixes of group gi's channels: this row's is the previous row's (own
+    // column, read one chunk ahead) plus the prefix of this row's change
+    auto update = [&](auto GI) {
+      constexpr int g0 = decltype(GI)::value * MG;
+      constexpr int gn = NS - g0 < MG ? NS - g0 : MG;
+      sum_t* P = decltype(GI)::value ? S1 : S0;
+      sum_t nx[IL];
+#pragma unroll
+      for (int i = 0; i < IL; ++i) nx[i] = i < gn ? P[i * kLdsStride + tid] : sum_t(0);
+#pragma unroll
+      for (int m0 = 0; m0 < gn; m0 += IL) {
+        sum_t x[IL];
+#pragma unroll
+        for (int i = 0; i < IL; ++i) x[i] = nx[i];
+#pragma unroll
+        for (int i = 0; i < IL; ++i)
+          nx[i] = m0 + IL + i < gn ? P[(m0 + IL + i) * kLdsStride + tid] : sum_t(0);
+        __builtin_amdgcn_sched_barrier(0);
+        sum_t dl[IL];
+        group_deltas<Q, C, IL, POFF, PC>(g0 + m0, gn - m0 < IL ? gn - m0 : IL, ga, yA, gs, yS, dl);
+#pragma unroll
+        for (int i = 0; i < IL; ++i) dl[i] = m0 + i < gn ? dl[i] : sum_t(0);
+        seg_prefix_n<WIDE>(dl);
+#pragma unroll
+        for (int i = 0; i < IL; ++i)
+          if (m0 + i < gn) P[(m0 + i) * kLdsStride + tid] = x[i] + dl[i];
+      }
+    };
+    auto next_row = [&](int y) {
+      shift_raw<Q, C>(fa, okA, cg, ga, yA);
+      shift_raw<Q, C>(fs, okS, cg, gs, yS);
+      if (y + 1 < Y1) fetch(y + 1);
+      update(std::integral_constant<int, 0>{});
+    };
+    fetch(Y0);
+    next_row(Y0);
+    __syncthreads();
+    for (int y = Y0; y < Y1; ++y) {
+      update(std::integral_constant<int, 1>{});
+      __syncthreads();
+      if (y + 1 < Y1) next_row(y + 1);
+      __syncthreads();
+    }
+  } else {
+    const int xc = X0 + tid;
+    const bool cvalid = tid < tout && xc < W;
+    const HWin hw = hwin<WIDE>(tid, r);
+    T mu[Q], nu[C];
+    chol_t Hm[NP], R[Q * C];
+    auto read = [&](auto GI, int64_t off, T inv_n) {
+      constexpr int gi = decltype(GI)::value;
+      constexpr int g0 = gi * MG;
+      constexpr int gn = NS - g0 < MG ? NS - g0 : MG;
+      const sum_t* P = gi ? S1 : S0;
+      const GroupAddr gad = group_addr(P, hw);  // every lane (DPP)
+      const HWin hr = hwin_opaque(hw);
+      if (!cvalid) return;
+      if (MODE == W_MOMENTS && a.raw) {
+#pragma unroll
+        for (int m = 0; m < gn; ++m) {
+          constexpr int first = Q + C;
+          const int l = g0 + m;  // local channel -> global channel
+          const int gch = l < first ? l : l + POFF;
+          if (POFF == 0 || l >= first)
+            a.out[(1 + gch) * pl + off] = (float)hwin_sum(P + m * kLdsStride, hr);
+        }
+      } else {
+        centre_group<Q, C, MG, POFF, PC, T, chol_t>(g0, gn, gad, inv_n, mu, nu, Hm, R);
+      }
+    };
+    __syncthreads();
+    for (int y = Y0; y < Y1; ++y) {
+      const int64_t off = (int64_t)y * W + xc;
+      const int ni = cvalid ? win_count(y, H, r) * win_count(xc, W, r) : 1;
+      const T inv_n = recip_count(ni, T(0));
+      read(std::integral_constant<int, 0>{}, off, inv_n);
+      __syncthreads();
+      read(std::integral_constant<int, 1>{}, off, inv_n);
+      if (cvalid) walk_emit<Q, C, MODE, POFF, PC>(a, pl, off, ni, cg, mu, nu, Hm, R);
+      __syncthreads();
+    }
+  }
+}
+
+// Whether a walk runs as walk_pair_kernel: both LDS groups in use.
+template <int Q, int C, int MODE, int PCNT = -1>
+constexpr bool paired_walk() {
+  constexpr int ns = PCNT < 0 ? num_sums(Q, C) : Q + C + PCNT;
+  return (MODE == W_COEFFS || MODE == W_MOMENTS) && group_count(ns, sizeof(sum_t)) == 2;
+}
+
+template <int Q, int C, int MODE, bool WIDE, int POFF = 0, int PCNT = -1, bool BATCH = false>
+__global__ void __launch_bounds__(2 * kThreads, 1) walk_pair_kernel(LaunchArgs ain) {
+  int bid = blockIdx.x;
+  const LaunchArgs a = BATCH ? batch_frame(ain, &bid) : ain;
+  walk_pair_tile<Q, C, MODE, WIDE, POFF, PCNT>(a, bid);
 }
 
 // ---------------------------------------------------------------------------
@@ -1092,12 +1311,28 @@ __global__ void __launch_bounds__(kThreads, 1) batch_kernel(LaunchArgs ain) {
 // Host-side launch of one kernel kind for a fixed (Q, C).
 template <typename K>
 static hipError_t launch_with_lds(K kernel, int blocks, size_t lds, const LaunchArgs& a,
-                                  hipStream_t s) {
+                                  hipStream_t s, int threads = kThreads) {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), lds, s, a);
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), lds, s, a);
   return hipGetLastError();
+}
+
+// A moment or coefficient walk of `blocks` workgroups, in its form.
+template <int Q, int C, int MODE, int POFF = 0, int PCNT = -1, bool BATCH = false>
+static hipError_t launch_walk(int blocks, size_t lds, const LaunchArgs& a, hipStream_t s) {
+  const bool wide = wide_segments(a.r);
+  if constexpr (paired_walk<Q, C, MODE, PCNT>())
+    return wide ? launch_with_lds(walk_pair_kernel<Q, C, MODE, true, POFF, PCNT, BATCH>, blocks,
+                                  lds, a, s, 2 * kThreads)
+                : launch_with_lds(walk_pair_kernel<Q, C, MODE, false, POFF, PCNT, BATCH>, blocks,
+                                  lds, a, s, 2 * kThreads);
+  else
+    return wide
+               ? launch_with_lds(walk_kernel<Q, C, MODE, true, POFF, PCNT, BATCH>, blocks, lds, a, s)
+               : launch_with_lds(walk_kernel<Q, C, MODE, false, POFF, PCNT, BATCH>, blocks, lds, a,
+                                 s);
 }
 
 template <typename K>
@@ -1120,8 +1355,7 @@ hipError_t launch_qc(int kind, const LaunchArgs& a, hipStream_t s) {
   auto lds_of = [](int k) { return walk_lds_bytes(k, Q, C); };
   switch (kind) {
     case K_MOMENTS:
-      return wide ? launch_with_lds(walk_kernel<Q, C, W_MOMENTS, true>, wblocks, lds, a, s)
-                  : launch_with_lds(walk_kernel<Q, C, W_MOMENTS, false>, wblocks, lds, a, s);
+      return launch_walk<Q, C, W_MOMENTS>(wblocks, lds, a, s);
     case K_FUSED0:
       return wide ? launch_with_lds(walk_kernel<Q, C, W_FUSED0, true>, wblocks, lds, a, s)
                   : launch_with_lds(walk_kernel<Q, C, W_FUSED0, false>, wblocks, lds, a, s);
@@ -1129,30 +1363,24 @@ hipError_t launch_qc(int kind, const LaunchArgs& a, hipStream_t s) {
       return wide ? launch_with_lds(walk_kernel<Q, C, W_FUSED1, true>, wblocks, lds, a, s)
                   : launch_with_lds(walk_kernel<Q, C, W_FUSED1, false>, wblocks, lds, a, s);
     case K_COEFFS:
-      return wide ? launch_with_lds(walk_kernel<Q, C, W_COEFFS, true>, wblocks, lds, a, s)
-                  : launch_with_lds(walk_kernel<Q, C, W_COEFFS, false>, wblocks, lds, a, s);
+      return launch_walk<Q, C, W_COEFFS>(wblocks, lds, a, s);
     case K_MOMENTS_A:
     case K_MOMENTS_B:
       if constexpr (split_walk(Q, C)) {
         constexpr int PA = split_first(Q, C), NPQ = num_products(Q, C);
         if (kind == K_MOMENTS_A) {
           const size_t l2 = walk_lds_bytes(K_MOMENTS, Q, C, Q + C + PA);
-          return wide ? launch_with_lds(walk_kernel<Q, C, W_MOMENTS, true, 0, PA>, wblocks, l2, a, s)
-                      : launch_with_lds(walk_kernel<Q, C, W_MOMENTS, false, 0, PA>, wblocks, l2, a, s);
+          return launch_walk<Q, C, W_MOMENTS, 0, PA>(wblocks, l2, a, s);
         }
         const size_t l2 = walk_lds_bytes(K_MOMENTS, Q, C, Q + C + NPQ - PA);
-        return wide ? launch_with_lds(walk_kernel<Q, C, W_MOMENTS, true, PA, NPQ - PA>, wblocks, l2, a, s)
-                    : launch_with_lds(walk_kernel<Q, C, W_MOMENTS, false, PA, NPQ - PA>, wblocks, l2, a, s);
+        return launch_walk<Q, C, W_MOMENTS, PA, NPQ - PA>(wblocks, l2, a, s);
       }
       return hipErrorInvalidValue;
     case K_SPLIT_COEFFS:
       if constexpr (split_walk(Q, C)) {
         constexpr int PA = split_first(Q, C), NPQ = num_products(Q, C);
         const size_t l2 = walk_lds_bytes(K_COEFFS, Q, C, Q + C + NPQ - PA);
-        return wide ? launch_with_lds(walk_kernel<Q, C, W_SPLITSOLVE, true, PA, NPQ - PA>,
-                                      wblocks, l2, a, s)
-                    : launch_with_lds(walk_kernel<Q, C, W_SPLITSOLVE, false, PA, NPQ - PA>,
-                                      wblocks, l2, a, s);
+        return launch_walk<Q, C, W_SPLITSOLVE, PA, NPQ - PA>(wblocks, l2, a, s);
       }
       return hipErrorInvalidValue;
     case K_SOLVE:
@@ -1182,10 +1410,7 @@ hipError_t launch_qc(int kind, const LaunchArgs& a, hipStream_t s) {
     }
     case K_COEFFS_BATCH:
       if constexpr (!split_walk(Q, C)) {
-        return wide ? launch_with_lds(walk_kernel<Q, C, W_COEFFS, true, 0, -1, true>,
-                                      a.batch_blocks, lds_of(K_COEFFS), a, s)
-                    : launch_with_lds(walk_kernel<Q, C, W_COEFFS, false, 0, -1, true>,
-                                      a.batch_blocks, lds_of(K_COEFFS), a, s);
+        return launch_walk<Q, C, W_COEFFS, 0, -1, true>(a.batch_blocks, lds_of(K_COEFFS), a, s);
       }
       return hipErrorInvalidValue;
     case K_UP_APPLY_BATCH:
