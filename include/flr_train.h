@@ -68,6 +68,15 @@ flr_status flr_adamw_step(int64_t n, float* params, const float* grads, float* m
                           int32_t step, float lr, float beta1, float beta2, float eps,
                           float weight_decay, void* stream);
 
+/* dst[i] = ((src[i] + src[stride + i]) + src[2 stride + i]) + ... over `count`
+ * vectors of n FP32 values, added in order: the per-crop weight gradients of a
+ * batch whose crops ran side by side, with the bits that accumulating them
+ * one after the other gives. FLR_ERR_SHAPE for n < 1, count < 1 or stride < n,
+ * FLR_ERR_NULL, FLR_ERR_ALIGN (16 bytes), FLR_ERR_ALIAS when dst overlaps
+ * src. */
+flr_status flr_sum_vectors(int32_t count, int64_t n, const float* src, int64_t stride,
+                           float* dst, void* stream);
+
 /* Adam on the logarithms of FLR's regularisers, on the device (the
  * Appendix learns its regularisers by backpropagation; the logarithm keeps
  * them positive): reg = device float[2] (eps, eps_mul), updated in place and

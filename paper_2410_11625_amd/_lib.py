@@ -39,7 +39,7 @@ EXPORTED = ("flr_num_moment_planes", "flr_num_coeff_planes", "flr_denoise_worksp
             "flr_flnr_workspace_bytes", "flr_flnr_denoise", "flr_net_trace_bytes",
             "flr_net_trace_tensor", "flr_net_forward_trace",
             # include/flr_train.h
-            "flr_l1_workspace_bytes", "flr_l1_loss_grad", "flr_adamw_step",
+            "flr_l1_workspace_bytes", "flr_l1_loss_grad", "flr_adamw_step", "flr_sum_vectors",
             "flr_l1_loss_grad_noalloc", "flr_reg_adam_step")
 
 
@@ -205,6 +205,8 @@ def lib() -> ctypes.CDLL:
     f = ctypes.c_float
     L.flr_adamw_step.argtypes = [ctypes.c_int64, vp, vp, vp, vp, ctypes.c_int32, f, f, f, f, f, vp]
     L.flr_adamw_step.restype = ctypes.c_int
+    L.flr_sum_vectors.argtypes = [ctypes.c_int32, ctypes.c_int64, vp, ctypes.c_int64, vp, vp]
+    L.flr_sum_vectors.restype = ctypes.c_int
     L.flr_status_str.argtypes = [ctypes.c_int]
     L.flr_status_str.restype = ctypes.c_char_p
     _lib = L

@@ -201,6 +201,21 @@ flr_status l1_launch(int64_t n, const float* out, const float* target, float sca
   return hipGetLastError() == hipSuccess ? FLR_OK : FLR_ERR_HIP;
 }
 
+struct SumArgs {
+  const float* src;
+  float* dst;
+  int64_t n, stride;
+  int count;
+};
+// One thread per element; HBM-trivial (a few MB of gradients).
+__global__ void __launch_bounds__(kBlock) sum_vectors_kernel(SumArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= a.n) return;
+  float s = a.src[i];
+  for (int k = 1; k < a.count; ++k) s += a.src[k * a.stride + i];
+  a.dst[i] = s;
+}
+
 }  // namespace flrtrain
 
 using namespace flrtrain;
@@ -260,6 +275,19 @@ flr_status flr_reg_adam_step(float* reg, double* state, const double* dreg, int3
   const RegAdamArgs a = {reg, state, dreg, n, learn_mul, lr, beta1, beta2, adam_eps};
   hipLaunchKernelGGL(reg_adam_kernel, dim3(1), dim3(64), 0, reinterpret_cast<hipStream_t>(stream),
                      a);
+  return hipGetLastError() == hipSuccess ? FLR_OK : FLR_ERR_HIP;
+}
+
+flr_status flr_sum_vectors(int32_t count, int64_t n, const float* src, int64_t stride,
+                           float* dst, void* stream) {
+  if (n < 1 || n > kMaxElems || count < 1 || stride < n || stride > kMaxElems) return FLR_ERR_SHAPE;
+  if (!src || !dst) return FLR_ERR_NULL;
+  if (!aligned16(src) || !aligned16(dst)) return FLR_ERR_ALIGN;
+  const size_t sb = ((size_t)(count - 1) * stride + n) * sizeof(float);
+  if (overlaps(src, sb, dst, (size_t)n * sizeof(float))) return FLR_ERR_ALIAS;
+  const SumArgs a = {src, dst, n, stride, count};
+  hipLaunchKernelGGL(sum_vectors_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock),
+                     0, reinterpret_cast<hipStream_t>(stream), a);
   return hipGetLastError() == hipSuccess ? FLR_OK : FLR_ERR_HIP;
 }
 
