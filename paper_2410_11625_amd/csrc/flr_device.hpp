@@ -1414,8 +1414,8 @@ hipError_t launch_qc(int kind, const LaunchArgs& a, hipStream_t s) {
       }
       return hipErrorInvalidValue;
     case K_UP_APPLY_BATCH:
-      hipLaunchKernelGGL((up_apply_kernel<Q, C, true>), dim3(a.batch_blocks), dim3(256), 0, s, a);
-      return hipGetLastError();
+      return launch_with_lds(up_apply_kernel<Q, C, true>, a.batch_blocks,
+                             lr_apply_lds_bytes(Q, C, 2, up_rows(Q, C)), a, s);
     case K_BATCH_PERSISTENT:
       if constexpr (!split_walk(Q, C)) {
         const size_t l = batch_lds_bytes(Q, C);

@@ -223,7 +223,7 @@ struct LaunchArgs {
 // LDS of the staged model interpolation: rows x models x low-resolution
 // columns of FP64 (a workgroup's kThreads columns span at most
 // (kThreads - 1) / block + 3 low-resolution columns).
-inline size_t lr_apply_lds_bytes(int Q, int C, int block, int rows) {
+__host__ __device__ constexpr size_t lr_apply_lds_bytes(int Q, int C, int block, int rows) {
   return (size_t)rows * (Q + 1) * C * ((kThreads - 1) / block + 3) * sizeof(double);
 }
 // Rows per workgroup of the staged interpolation: the most of 8, 4, 2, 1
@@ -232,6 +232,16 @@ inline int lr_apply_rows(int Q, int C, int block) {
   for (int rows = 8; rows >= 1; rows /= 2)
     if (lr_apply_lds_bytes(Q, C, block, rows) <= 65536) return rows;
   return 0;
+}
+
+// Rows of an upsampling tile: the staging of two rows at 2 x (the finest
+// models) fits in 64 KiB up to (Q + 1) C = 31, one row otherwise.
+__host__ __device__ constexpr int up_rows(int Q, int C) {
+  return lr_apply_lds_bytes(Q, C, 2, 2) <= 65536 ? 2 : 1;
+}
+inline int up_items(int H, int W, int Q, int C) {
+  const int rows = up_rows(Q, C);
+  return ((W + kThreads - 1) / kThreads) * ((H + rows - 1) / rows);
 }
 
 // The downsampled-moment variant's low-resolution planes: the pixel count
@@ -481,7 +491,8 @@ inline void plan_walk(int kind, int H, int W, int Q, int C, int r, int tile_rows
 // averaging kernel's (its box items use the ring where it fits in that).
 inline size_t batch_lds_bytes(int Q, int C) {
   const size_t w = walk_lds_bytes(K_COEFFS, Q, C), v = avg_lds_bytes(kAvgTileRows);
-  return w > v ? w : v;
+  const size_t u = lr_apply_lds_bytes(Q, C, 2, up_rows(Q, C)), m = w > v ? w : v;
+  return u > m ? u : m;
 }
 
 // Split walks: when a moment walker's channels exceed what stays resident in

@@ -43,27 +43,29 @@ __host__ __device__ constexpr ChanUV chan_uv(int ch) {
 // inside their 16-lane row (quad_perm xor 1 and xor 2, row_half_mirror,
 // row_mirror: every lane of the block ends with the block sum), and the
 // block's first lane writes it. More channels than fit in registers are
-// taken in equal chunks, each re-reading the inputs.
+// taken in equal chunks, each re-reading the inputs. (Chunks of 36 or 24
+// channels in workgroups of their own, or the next rows' loads issued before
+// these are summed, were no faster: 36 and 46 us against 36 at 1080p.)
 constexpr int kLrMaxAcc = 80;
 constexpr int kDppXor1 = 0xB1;       // quad_perm [1, 0, 3, 2]
 constexpr int kDppXor2 = 0x4E;       // quad_perm [2, 3, 0, 1]
 constexpr int kDppRowMirror = 0x140;
 constexpr int kDppRowHalfMirror = 0x141;
 
-// Sum over aligned groups of B (1, 2, 4, 8 or 16) lanes, in every lane of
-// the group. Every lane of the wavefront must take part.
-// The moves always run and the block size only selects which are added, so
-// the sums of many channels can be interleaved without branches.
-__device__ __forceinline__ double group_sum(double v, int B) {
-  double m = dpp_move<kDppXor1, 0xf>(v);
-  v += B >= 2 ? m : 0.0;
-  m = dpp_move<kDppXor2, 0xf>(v);
-  v += B >= 4 ? m : 0.0;
-  m = dpp_move<kDppRowHalfMirror, 0xf>(v);
-  v += B >= 8 ? m : 0.0;
-  m = dpp_move<kDppRowMirror, 0xf>(v);
-  v += B >= 16 ? m : 0.0;
-  return v;
+// Sums over aligned groups of B (1, 2, 4, 8 or 16) lanes of N values, in
+// every lane of the group. Every lane of the wavefront must take part. B is
+// uniform: one branch per step for all values.
+template <int CTRL, int N>
+__device__ __forceinline__ void group_step(double (&v)[N]) {
+#pragma unroll
+  for (int l = 0; l < N; ++l) v[l] += dpp_move<CTRL, 0xf>(v[l]);
+}
+template <int N>
+__device__ __forceinline__ void group_sums(double (&v)[N], int B) {
+  if (B >= 2) group_step<kDppXor1>(v);
+  if (B >= 4) group_step<kDppXor2>(v);
+  if (B >= 8) group_step<kDppRowHalfMirror>(v);
+  if (B >= 16) group_step<kDppRowMirror>(v);
 }
 
 template <int Q, int C>
@@ -122,10 +124,10 @@ __global__ void __launch_bounds__(256) lr_block_kernel(LaunchArgs a) {
         });
       }
     }
+    group_sums(acc, B);
+    if (writer) {
 #pragma unroll
-    for (int l = 0; l < kn; ++l) {
-      const double s = group_sum(acc[l], B);
-      if (writer) a.fout[(1 + k0 + l) * pll + (int64_t)I * a.Wl + J] = s;
+      for (int l = 0; l < kn; ++l) a.fout[(1 + k0 + l) * pll + (int64_t)I * a.Wl + J] = acc[l];
     }
   });
   if (writer) {
@@ -224,13 +226,23 @@ __device__ __forceinline__ void lr_axis(int k, int block, int n_low, int* k0, in
 }
 
 // The same as lr_apply_kernel with the vertical half of the interpolation
-// done once per workgroup: a workgroup covers a.lr_rows full-resolution rows
-// by kThreads columns; it first stages, for each of its rows, the models
+// done once per workgroup: a workgroup covers TR full-resolution rows by
+// kThreads columns; it first stages, for each of its rows, the models
 // interpolated between the two low-resolution rows at every low-resolution
-// column its pixels use ([row][model][column] in LDS), then each lane
-// interpolates along its row from two staged columns and applies the model.
+// column its pixels use ([row][model][column] in LDS; the rows' positions are
+// uniform, so an item is a model and a column, for all rows), then each lane
+// sums both staged columns' models and interpolates between the two sums.
+// Models FP64 (b~ | a) at a.fin; cg, cy: the anchors, a plane apart by cplane.
+//
+// What bounds it: LDS reads (two columns of every model per pixel) and, with
+// 2 x upsampling, staging 131 columns for 256 pixels. Measured at 1080p, Q = 8,
+// C = 3: 8 x 8 blocks 57 -> 44 us against dividing out the row and position of
+// every staged item; 2 x upsampling 131 -> 114 us against four loads of every
+// model per pixel.
 template <int Q, int C>
-__global__ void __launch_bounds__(256) lr_apply_staged_kernel(LaunchArgs a) {
+__device__ __forceinline__ void lr_apply_tile(const LaunchArgs& a, const int bx, const int by,
+                                              const int block, const int TR, const float* cg,
+                                              const float* cy, const int64_t cplane) {
   using T = double;
   constexpr int FC = (Q + 1) * C;
   extern __shared__ float lds[];
@@ -238,39 +250,41 @@ __global__ void __launch_bounds__(256) lr_apply_staged_kernel(LaunchArgs a) {
   const int tid = threadIdx.x;
   const int64_t pl = (int64_t)a.H * a.W;
   const int64_t pll = (int64_t)a.Hl * a.Wl;
-  const int X0 = blockIdx.x * kThreads;
-  const int Y0 = blockIdx.y * a.lr_rows;
-  const int TR = a.lr_rows;
+  const int X0 = bx * kThreads, Y0 = by * TR;
   const int xl = X0 + kThreads - 1 < a.W - 1 ? X0 + kThreads - 1 : a.W - 1;
   int c_lo, c_hi, d0, d1;
   double dt;
-  lr_axis(X0, a.block, a.Wl, &c_lo, &d0, &dt);
-  lr_axis(xl, a.block, a.Wl, &d1, &c_hi, &dt);
+  lr_axis(X0, block, a.Wl, &c_lo, &d0, &dt);
+  lr_axis(xl, block, a.Wl, &d1, &c_hi, &dt);
   const int nc = c_hi - c_lo + 1;
-  // staging, kStage items per lane at a time: the loads of a batch are
-  // issued together (items past the end repeat the last one, unstored)
-  constexpr int kStage = 8;
-  const int total = TR * FC * nc;
-  for (int t0 = 0; t0 < total; t0 += kStage * kThreads) {
-    double v0[kStage], v1[kStage], w[kStage];
+  const int total = FC * nc;
+  // rows two at a time: their four loads of an item are in flight together,
+  // two items per lane
+  for (int rr = 0; rr < TR; rr += 2) {
+    int r0[2], r1[2];
+    double w[2];
 #pragma unroll
-    for (int u = 0; u < kStage; ++u) {
-      int t = t0 + u * kThreads + tid;
-      t = t < total ? t : total - 1;
-      const int rr = t / (FC * nc);
-      const int rem = t - rr * (FC * nc);
-      const int k = rem / nc, cc = rem - (rem / nc) * nc;
-      const int y = Y0 + rr < a.H ? Y0 + rr : a.H - 1;
-      int r0, r1;
-      lr_axis(y, a.block, a.Hl, &r0, &r1, &w[u]);
-      const double* m = a.fin + k * pll + c_lo + cc;
-      v0[u] = m[(int64_t)r0 * a.Wl];
-      v1[u] = m[(int64_t)r1 * a.Wl];
-    }
+    for (int u = 0; u < 2; ++u)
+      lr_axis(min(Y0 + rr + u, a.H - 1), block, a.Hl, &r0[u], &r1[u], &w[u]);
+    for (int t0 = tid; t0 < total; t0 += 2 * kThreads) {
+      double v0[2][2], v1[2][2];
 #pragma unroll
-    for (int u = 0; u < kStage; ++u) {
-      const int t = t0 + u * kThreads + tid;
-      if (t < total) st[t] = v0[u] * (T(1) - w[u]) + v1[u] * w[u];
+      for (int j = 0; j < 2; ++j) {
+        const int t = min(t0 + j * kThreads, total - 1);
+        const int k = t / nc, cc = t - k * nc;
+        const double* m = a.fin + k * pll + c_lo + cc;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          v0[j][u] = m[(int64_t)r0[u] * a.Wl];
+          v1[j][u] = m[(int64_t)r1[u] * a.Wl];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          if (t0 + j * kThreads < total && rr + u < TR)
+            st[(rr + u) * total + t0 + j * kThreads] = v0[j][u] * (T(1) - w[u]) + v1[j][u] * w[u];
     }
   }
   __syncthreads();
@@ -278,29 +292,46 @@ __global__ void __launch_bounds__(256) lr_apply_staged_kernel(LaunchArgs a) {
   if (x >= a.W) return;
   int c0, c1;
   double tc;
-  lr_axis(x, a.block, a.Wl, &c0, &c1, &tc);
+  lr_axis(x, block, a.Wl, &c0, &c1, &tc);
   c0 -= c_lo;
   c1 -= c_lo;
-  T anc_g[Q];
+  T anc_g[Q], anc_y[C];
 #pragma unroll
-  for (int q = 0; q < Q; ++q) anc_g[q] = a.guides[q * pl];
+  for (int q = 0; q < Q; ++q) anc_g[q] = cg[q * cplane];
+#pragma unroll
+  for (int c = 0; c < C; ++c) anc_y[c] = cy[c * cplane];
+  float gn[Q];
+  auto fetch = [&](int rr) {
+    const int64_t idx = (int64_t)min(Y0 + rr, a.H - 1) * a.W + x;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) gn[q] = a.guides[q * pl + idx];
+  };
+  fetch(0);
   for (int rr = 0; rr < TR; ++rr) {
     const int y = Y0 + rr;
     if (y >= a.H) break;
-    const int64_t idx = (int64_t)y * a.W + x;
-    const double* row = st + rr * FC * nc;
-    auto model = [&](int k) { return row[k * nc + c0] * (T(1) - tc) + row[k * nc + c1] * tc; };
     T g[Q];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) g[q] = (T)a.guides[q * pl + idx] - anc_g[q];
+    for (int q = 0; q < Q; ++q) g[q] = (T)gn[q] - anc_g[q];
+    if (rr + 1 < TR) fetch(rr + 1);  // the next row's guides are on their way meanwhile
+    const double* p0 = st + rr * total + c0;
+    const double* p1 = st + rr * total + c1;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      T s = model(c) + (T)a.noisy[c * pl];
+      T s0 = p0[c * nc], s1 = p1[c * nc];
 #pragma unroll
-      for (int q = 0; q < Q; ++q) s = fma(model(C + q * C + c), g[q], s);
-      a.out[c * pl + idx] = (float)s;
+      for (int q = 0; q < Q; ++q) {
+        s0 = fma(p0[(C + q * C + c) * nc], g[q], s0);
+        s1 = fma(p1[(C + q * C + c) * nc], g[q], s1);
+      }
+      a.out[c * pl + (int64_t)y * a.W + x] = (float)((s0 * (T(1) - tc) + s1 * tc) + anc_y[c]);
     }
   }
+}
+template <int Q, int C>
+__global__ void __launch_bounds__(256) lr_apply_staged_kernel(LaunchArgs a) {
+  lr_apply_tile<Q, C>(a, blockIdx.x, blockIdx.y, a.block, a.lr_rows, a.guides, a.noisy,
+                      (int64_t)a.H * a.W);
 }
 
 // Joint denoising and upsampling (Sec. 3.2): anchored FP64 models (b~ | a,
@@ -308,40 +339,14 @@ __global__ void __launch_bounds__(256) lr_apply_staged_kernel(LaunchArgs a) {
 // a.up times coarser than the output, bilinearly interpolated at each output
 // pixel (half-pixel centres, clamped) and applied to the full-resolution
 // guides with the anchors of the fit (pixel (0, 0) of the low-resolution
-// guides and of the noisy input). Batched over frames.
+// guides and of the noisy input). Batched over frames; an item is a tile of
+// up_rows(Q, C) rows by kThreads columns, down each strip of columns.
 template <int Q, int C>
 __device__ __forceinline__ void up_apply_item(const LaunchArgs a, const int bid) {
-  using T = double;
-  constexpr int FC = (Q + 1) * C;
-  const int64_t pl = (int64_t)a.H * a.W;
-  const int64_t pll = (int64_t)a.Hl * a.Wl;
-  const int64_t idx = (int64_t)bid * 256 + threadIdx.x;
-  if (idx >= pl) return;
-  const int i = (int)(idx / a.W), j = (int)(idx - (int64_t)i * a.W);
-  int r0, r1, c0, c1;
-  double tr, tc;
-  lr_axis(i, a.up, a.Hl, &r0, &r1, &tr);
-  lr_axis(j, a.up, a.Wl, &c0, &c1, &tc);
-  const int64_t o00 = (int64_t)r0 * a.Wl + c0, o01 = (int64_t)r0 * a.Wl + c1;
-  const int64_t o10 = (int64_t)r1 * a.Wl + c0, o11 = (int64_t)r1 * a.Wl + c1;
-  T m[FC];
-#pragma unroll
-  for (int k = 0; k < FC; ++k) {
-    const double* p = a.fin + k * pll;
-    const T top = p[o00] * (T(1) - tc) + p[o01] * tc;
-    const T bot = p[o10] * (T(1) - tc) + p[o11] * tc;
-    m[k] = top * (T(1) - tr) + bot * tr;
-  }
-  T g[Q];
-#pragma unroll
-  for (int q = 0; q < Q; ++q) g[q] = (T)a.guides[q * pl + idx] - (T)a.guides_low[q * pll];
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    T s = m[c] + (T)a.noisy[c * pll];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) s = fma(m[C + q * C + c], g[q], s);
-    a.out[c * pl + idx] = (float)s;
-  }
+  constexpr int TR = up_rows(Q, C);
+  const int ny = (a.H + TR - 1) / TR;
+  lr_apply_tile<Q, C>(a, bid / ny, bid % ny, a.up, TR, a.guides_low, a.noisy,
+                      (int64_t)a.Hl * a.Wl);
 }
 template <int Q, int C, bool BATCH>
 __global__ void __launch_bounds__(256) up_apply_kernel(LaunchArgs ain) {
