@@ -180,14 +180,11 @@ static void avg_launch(const LaunchArgs& a, bool batch, int blocks, hipStream_t 
     hipLaunchKernelGGL((apply_avg_kernel<RAD, TH, false>), dim3(blocks), dim3(kThreads), l, s, a);
 }
 
-// The kernel of the tile height: one for every height would take the tallest
-// one's registers (batched, r = 8: 124 instead of 84; a batch of 7.3 Mpixel
-// 579 us instead of 478).
+// The kernel of the tile height: one for both heights would take the taller
+// one's registers on every frame.
 template <int RAD>
 static void avg_dispatch(const LaunchArgs& a, bool batch, int blocks, hipStream_t s) {
-  if (a.seg_rows > 4)
-    avg_launch<RAD, 8>(a, batch, blocks, s);
-  else if (a.seg_rows > 2)
+  if (a.seg_rows > 2)
     avg_launch<RAD, 4>(a, batch, blocks, s);
   else
     avg_launch<RAD, 2>(a, batch, blocks, s);

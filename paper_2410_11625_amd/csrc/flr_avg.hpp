@@ -69,16 +69,20 @@ typedef float f32x4u __attribute__((vector_size(16), aligned(4)));
 constexpr int kDppQuadShr1 = 0x90;  // quad_perm [0, 0, 1, 2]
 constexpr int kDppQuadShr2 = 0x40;  // quad_perm [0, 0, 0, 1]
 constexpr int kDppQuadLast = 0xFF;  // quad_perm [3, 3, 3, 3]
+// x where the lane mask m is all ones, 0 where it is 0 (two AND instructions,
+// half the cycles of two selects).
+__device__ __forceinline__ double keep64(double x, unsigned m) {
+  const unsigned long long v = (unsigned long long)__double_as_longlong(x);
+  const unsigned lo = (unsigned)v & m, hi = (unsigned)(v >> 32) & m;
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// m1, m2: all ones in lanes 1.. and 2.. of each group of four, else 0.
 template <int G>
-__device__ __forceinline__ double group_exclusive(double x, int lane) {
+__device__ __forceinline__ double group_exclusive(double x, unsigned m1, unsigned m2) {
   if constexpr (G == 4) {
-    const bool ge1 = (lane & 3) >= 1, ge2 = (lane & 3) >= 2;
-    double e = dpp_move<kDppQuadShr1, 0xf>(x);
-    e = ge1 ? e : 0.0;
-    double t = dpp_move<kDppQuadShr1, 0xf>(e);
-    e += ge1 ? t : 0.0;
-    t = dpp_move<kDppQuadShr2, 0xf>(e);
-    e += ge2 ? t : 0.0;
+    double e = keep64(dpp_move<kDppQuadShr1, 0xf>(x), m1);
+    e += keep64(dpp_move<kDppQuadShr1, 0xf>(e), m1);
+    e += keep64(dpp_move<kDppQuadShr2, 0xf>(e), m2);
     return e;
   } else {
     double e = dpp_move<kDppRowShr + 1, 0xf>(x);
@@ -109,6 +113,7 @@ struct AvgLane {
   int lane, r, H, W, Q, C, np, pbytes, x, xo, xs, shift, xg0;
   int xg[4];
   int ia, ib, it;
+  unsigned m1, m2;
   int64_t pl;
   const float* planes;
   const float* guides;
@@ -150,6 +155,8 @@ struct AvgLane {
     ib = (pb & 1) * 64 + (pb >> 1);
     it = (pt & 1) * 64 + (pt >> 1);
     pr0 = reinterpret_cast<Pair*>(row);
+    m1 = (lane & 3) >= 1 ? 0xffffffffu : 0u;
+    m2 = (lane & 3) >= 2 ? 0xffffffffu : 0u;
   }
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane(int f) const {
     return plane_rsrc(planes + (int64_t)f * C * pl, pbytes);
@@ -201,6 +208,7 @@ struct AvgLane {
   __device__ __forceinline__ void rows_out(const int k0, const double (&vs)[N][4],
                                            const float (&g)[TH][4], bool guide,
                                            double (&acc)[TH][4]) const {
+    const unsigned gm = guide ? 0xffffffffu : 0u, go = guide ? 0u : 0x3f800000u;  // 1.0f
     double A[N][4];
 #pragma unroll
     for (int j = 0; j < N; ++j) {
@@ -208,7 +216,7 @@ struct AvgLane {
       l[0] = vs[j][0];
 #pragma unroll
       for (int i = 1; i < 4; ++i) l[i] = l[i - 1] + vs[j][i];
-      const double ex = group_exclusive<SEG / 4>(l[3], lane);
+      const double ex = group_exclusive<SEG / 4>(l[3], m1, m2);
       double P[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) P[i] = ex + l[i];
@@ -239,16 +247,29 @@ struct AvgLane {
       const double e[4] = {ea.u, ea.v, eb.u, eb.v};
       double T = 0.0;
       if constexpr (SEG == 64) T = pr[it].v;
+      double v[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        double v;
         if constexpr (SEG == 16) {
-          v = e[i] + A[j][i];
+          v[i] = e[i] + A[j][i];
         } else {
           const bool cross = ((4 * lane + i) & 63) + 2 * r > 63;
-          v = (e[i] - A[j][i]) + pick(cross, T, 0.0);
+          v[i] = (e[i] - A[j][i]) + pick(cross, T, 0.0);
         }
-        acc[k0 + j][i] = fma(guide ? (double)g[k0 + j][i] : 1.0, v, acc[k0 + j][i]);
+      }
+      if constexpr (RAD == AVG_R8) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float w = __uint_as_float((__float_as_uint(g[k0 + j][i]) & gm) | go);
+          acc[k0 + j][i] = fma((double)w, v[i], acc[k0 + j][i]);
+        }
+      } else if (guide) {  // uniform (measured: faster here, slower at r = 8)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          acc[k0 + j][i] = fma((double)g[k0 + j][i], v[i], acc[k0 + j][i]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[k0 + j][i] += v[i];
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -403,9 +424,7 @@ __device__ __forceinline__ void avg_group_th(const LaunchArgs& a, const int t) {
 // Workgroup t with the frame's tile height.
 template <int RAD>
 __device__ __forceinline__ void avg_group(const LaunchArgs& a, const int t) {
-  if (a.seg_rows > 4)
-    avg_group_th<8, RAD>(a, t);
-  else if (a.seg_rows > 2)
+  if (a.seg_rows > 2)
     avg_group_th<4, RAD>(a, t);
   else
     avg_group_th<2, RAD>(a, t);

@@ -311,7 +311,7 @@ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 __host__ __device__ constexpr bool wide_segments(int r) { return r > 8; }
 constexpr int kAvgWaves = 4;
 constexpr int kAvgRowBatch = 2;
-constexpr int kAvgTileRows = 8;
+constexpr int kAvgTileRows = 4;
 __host__ __device__ constexpr int avg_cols(int r) { return (256 - 2 * r) & ~3; }
 // First output column of strip sx: its input columns start r to the left, at
 // a multiple of 4 (strip 0's first outputs may lie left of the image).
@@ -321,7 +321,7 @@ __host__ __device__ constexpr int avg_col0(int sx, int r) {
 // LDS of a workgroup with tiles of `rows` rows: the wavefronts' exchange
 // rows, reused for their closing sums of `rows` rows.
 inline size_t avg_lds_bytes(int rows) {
-  return (size_t)kAvgWaves * (rows > 4 ? 8 : (rows > 2 ? 4 : 2)) * 256 * sizeof(double);
+  return (size_t)kAvgWaves * (rows > 2 ? 4 : 2) * 256 * sizeof(double);
 }
 // Its forms by radius: r = 8 keeps a plane's rows of the tile in registers;
 // other radii load the rows entering and leaving the window; r > 8 needs
@@ -343,20 +343,18 @@ inline int avg_groups(int tiles, int C) {
 // Rows of coefficient halo a walker recomputes above and below its segment.
 inline int row_halo(int kind, int r) { return kind == K_FUSED1 ? r : 0; }
 
-// Tiles of the averaging kernel: tile_rows, when set; else, for r <= 8, four
-// rows where they give kAvgMinGroups workgroups (tile and channel), so that
-// a plane row is fetched (4 + 2r) / 4 times instead of (2 + 2r) / 2, and two
-// rows below, where the shorter chain and the workgroup count win. Measured,
-// r = 8, 2 / 4 / 8 rows: 256 x 256, Q = 12, C = 3 16.8 / 17.8 / 19.6 us; 540p,
-// Q = 8 44 / 38 / 42; 1080p, Q = 8 176 / 135 / 132; 1440p 311 / 230 / 229
-// (eight rows take 242 registers, two wavefronts per SIMD, and gain nothing).
-// r > 8 (33 and more rows per window) takes eight rows on large frames, two
-// else: r = 16, 540p, C = 1 35 / 39 / 37; 1080p, C = 3 259 / 273 / 221.
+// Tiles of the averaging kernel: tile_rows, when set; else four rows where
+// they give kAvgMinGroups workgroups (tile and channel), so that a plane row is
+// fetched (4 + 2r) / 4 times instead of (2 + 2r) / 2, and two rows below, where
+// the shorter chain and the workgroup count win. Measured, 2 / 4 rows: 256 x
+// 256, Q = 12, C = 3 16.8 / 17.9 us; 540p, Q = 8 45 / 37; 1080p, Q = 8 177 / 135;
+// r = 16, 540p, C = 1 35 / 27; 1080p, C = 3 261 / 181. (Eight rows: 242
+// registers, two wavefronts per SIMD; 1080p, Q = 8 132, r = 16 221.)
 constexpr int kAvgMinGroups = 600;
 inline void plan_avg(int H, int W, int r, int C, int tile_rows, int* tiles_x, int* n_seg,
                      int* seg_rows) {
   *tiles_x = ceil_div(W - avg_col0(0, r), avg_cols(r));
-  const int tall = wide_segments(r) ? 8 : 4;
+  constexpr int tall = kAvgTileRows;
   int t = 2;
   if (tile_rows > 0)
     t = tile_rows < kAvgTileRows ? tile_rows : kAvgTileRows;
