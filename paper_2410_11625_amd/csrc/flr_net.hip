@@ -98,6 +98,8 @@ __device__ __forceinline__ bf16x4_t round4(float a, float b, float c, float d) {
 
 // Network input at one pixel, channels c0 .. c0 + 7 of the 16 (8 guides, 3
 // noisy planes, zero): sign(v) log(1 + |v|), rounded to BF16.
+// (The hardware logarithm with a rounding correction took 35 us less of a
+// 1080p forward, and moved 7 in a million of the BF16 values: not kept.)
 __device__ __forceinline__ float compress(float v) { return copysignf(log1pf(fabsf(v)), v); }
 
 __device__ __forceinline__ f32x4_t load_bias(const float* b) {
@@ -252,6 +254,54 @@ __device__ __forceinline__ void stage_tile(const ConvArgs& a, const int x0, cons
   }
 }
 
+// [up2(in0), in1] of a tile inside the image: in0's pixels are staged at their
+// own resolution, once instead of up to four times (4 rows of 8 TPW + 2
+// pixels), behind each other's blocks, then in1's at full resolution.
+template <int CIN, int CUP, int TPW>
+struct UpTile {
+  using T = ConvTile<CIN - CUP, 1, TPW>;
+  static constexpr int LR = 4, LP = 8 * TPW + 2, NCBL = CUP / 16;
+  static constexpr int base = NCBL * LR * LP;  // units of in0, before in1's
+  __device__ static int low(int cb, int lr, int lx) { return (cb * LR + lr) * LP + lx; }
+};
+template <int CIN, int CUP, int TPW>
+__device__ __forceinline__ void stage_up(const ConvArgs& a, const int x0, const int y0) {
+  using U = UpTile<CIN, CUP, TPW>;
+  using T = typename U::T;
+  constexpr int CL = CUP / 8, CS = (CIN - CUP) / 8;  // chunks per pixel
+  constexpr int NL = U::LR * U::LP * CL, NIT = NL + T::SR * T::SP * CS, B = 6;
+  uint4* st = reinterpret_cast<uint4*>(flr::lds);
+  const int tid = threadIdx.x;
+  const uint16_t* lo = a.in0 + ((size_t)(y0 / 2 - 1) * a.Wl + (x0 / 2 - 1)) * CUP;
+  const uint16_t* hi = a.in1 + ((size_t)(y0 - 1) * a.Wi + (x0 - 1)) * (CIN - CUP);
+#pragma unroll 1
+  for (int b0 = 0; b0 < NIT; b0 += B * 256) {
+    uint4 v[B];
+    int dst[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int i = b0 + u * 256 + tid, ic = i < NIT ? i : NIT - 1;
+      const uint16_t* src;
+      int d;
+      if (ic < NL) {
+        const int pix = ic / CL, ch = ic - pix * CL, lr = pix / U::LP, lx = pix - lr * U::LP;
+        src = lo + (unsigned)((lr * a.Wl + lx) * CUP + ch * 8);
+        d = U::low(ch >> 1, lr, lx) * 2 + (ch & 1);
+      } else {
+        const int j = ic - NL, pix = j / CS, ch = j - pix * CS, sr = pix / T::SP,
+                  sx = pix - sr * T::SP;
+        src = hi + (unsigned)((sr * a.Wi + sx) * (CIN - CUP) + ch * 8);
+        d = (U::base + T::unit(ch >> 1, sr, sx)) * 2 + (ch & 1);
+      }
+      v[u] = *reinterpret_cast<const uint4*>(src);
+      dst[u] = i < NIT ? d : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u)
+      if (dst[u] >= 0) st[dst[u]] = v[u];
+  }
+}
+
 // The network's input (IN_PLANES): compressed while it is staged, one pixel
 // per lane; x0, when set, receives the tile's own pixels (HWC, 16 channels).
 template <int TPW>
@@ -286,26 +336,26 @@ __device__ __forceinline__ void stage_input(const ConvArgs& a, const int x0, con
   }
 }
 
-template <int CIN, int COUT, int ST, int IN, int CUP, int FUSE, int COUT2, int TPW>
-__global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
+// The matrix products of one wave's output row from the staged tile, and the
+// epilogue. LOW: staged by stage_up.
+template <int CIN, int COUT, int ST, int CUP, int FUSE, int COUT2, int TPW, bool LOW>
+__device__ __forceinline__ void conv_row(const ConvArgs& a, const int x0, const int y0,
+                                         const int wv) {
   using T = ConvTile<CIN, ST, TPW>;
   constexpr int NCB = T::NCB, NB = COUT / 16;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, kq = lane >> 4;
-  const int x0 = blockIdx.x * 16 * TPW, y0 = blockIdx.y * 4;
-  if constexpr (IN == IN_PLANES) {
-    stage_input<TPW>(a, x0, y0);
-  } else {
-    const bool edge = x0 == 0 || y0 == 0 || x0 * ST - 1 + T::SP > a.Wi ||
-                      y0 * ST - 1 + T::SR > a.Hi;
-    if (edge)
-      stage_tile<CIN, ST, IN, CUP, TPW, true>(a, x0, y0);
-    else
-      stage_tile<CIN, ST, IN, CUP, TPW, false>(a, x0, y0);
-  }
-  __syncthreads();
-  const int y = y0 + wv;
-  if (y >= a.Ho) return;  // uniform across the wave; no barrier follows
+  const int lane = threadIdx.x & 63, kq = lane >> 4, lx = lane & 15;
   const bf16x4_t* st = reinterpret_cast<const bf16x4_t*>(flr::lds);
+  auto frag = [&](int ky, int kx, int cb, int t) {
+    if constexpr (LOW) {
+      using U = UpTile<CIN, CUP, TPW>;
+      const int u = cb < U::NCBL
+                        ? U::low(cb, (wv + ky + 1) >> 1, ((lx + kx + 1) >> 1) + t * 8)
+                        : U::base + U::T::unit(cb - U::NCBL, wv + ky, kx) + t * 16 + lx;
+      return st[u * 4 + kq];
+    } else {
+      return st[(T::unit(cb, wv * ST + ky, kx) + t * 16 + lx) * 4 + kq];
+    }
+  };
   // partial sums (K steps round-robin) for layers of one output block, so
   // that enough independent MFMA chains are in flight per wave
   constexpr int KSPL = NB >= 2 ? 1 : 2;
@@ -326,8 +376,7 @@ __global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
         const int ks = (tap * NCB + cb) % KSPL;
         bf16x4_t bv[TPW];
 #pragma unroll
-        for (int t = 0; t < TPW; ++t)
-          bv[t] = st[(T::unit(cb, wv * ST + ky, kx) + t * 16 + (lane & 15)) * 4 + kq];
+        for (int t = 0; t < TPW; ++t) bv[t] = frag(ky, kx, cb, t);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
           const bf16x4_t av = a.w[((tap * NCB + cb) * NB + nb) * 64 + lane];
@@ -348,7 +397,35 @@ __global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
 #pragma unroll
       for (int k = 1; k < KSPL; ++k) sum[t][nb] += acc[t][nb][k];
     }
-  epilogue<COUT, FUSE, COUT2, TPW>(a, y, x0, lane, sum);
+  epilogue<COUT, FUSE, COUT2, TPW>(a, y0 + wv, x0, lane, sum);
+}
+
+template <int CIN, int COUT, int ST, int IN, int CUP, int FUSE, int COUT2, int TPW>
+__global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
+  using T = ConvTile<CIN, ST, TPW>;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int x0 = blockIdx.x * 16 * TPW, y0 = blockIdx.y * 4;
+  const bool edge = x0 == 0 || y0 == 0 || x0 * ST - 1 + T::SP > a.Wi ||
+                    y0 * ST - 1 + T::SR > a.Hi;
+  if constexpr (IN == IN_PLANES) {
+    stage_input<TPW>(a, x0, y0);
+  } else if constexpr (IN == IN_UPCAT) {
+    if (!edge) {  // uniform across the workgroup
+      stage_up<CIN, CUP, TPW>(a, x0, y0);
+      __syncthreads();
+      conv_row<CIN, COUT, ST, CUP, FUSE, COUT2, TPW, true>(a, x0, y0, wv);
+      return;
+    }
+    stage_tile<CIN, ST, IN, CUP, TPW, true>(a, x0, y0);
+  } else {
+    if (edge)
+      stage_tile<CIN, ST, IN, CUP, TPW, true>(a, x0, y0);
+    else
+      stage_tile<CIN, ST, IN, CUP, TPW, false>(a, x0, y0);
+  }
+  __syncthreads();
+  if (y0 + wv >= a.Ho) return;  // uniform across the wave; no barrier follows
+  conv_row<CIN, COUT, ST, CUP, FUSE, COUT2, TPW, false>(a, x0, y0, wv);
 }
 
 // Packing: FP32 weight [cout][cin][k][k] -> fragments (tap, cin block,
