@@ -207,7 +207,7 @@ struct ConvTile {
   }
 };
 
-template <int CIN, int ST, int IN, int CUP, int TPW, bool EDGE>
+template <int CIN, int ST, int TPW, bool EDGE>
 __device__ __forceinline__ void stage_tile(const ConvArgs& a, const int x0, const int y0) {
   using T = ConvTile<CIN, ST, TPW>;
   constexpr int NCH = CIN / 8;  // chunks per pixel
@@ -232,16 +232,7 @@ __device__ __forceinline__ void stage_tile(const ConvArgs& a, const int x0, cons
         y = min(max(y, 0), a.Hi - 1);
         x = min(max(x, 0), a.Wi - 1);
       }
-      const uint16_t* src;
-      if constexpr (IN == IN_UPCAT) {
-        // one load from a selected address: the upsampled coarse half or the skip
-        const bool low = ch * 8 < CUP;
-        const size_t p = low ? (size_t)(y >> 1) * a.Wl + (x >> 1) : (size_t)y * a.Wi + x;
-        const size_t o = p * (low ? CUP : CIN - CUP) + (low ? ch * 8 : ch * 8 - CUP);
-        src = (low ? a.in0 : a.in1) + o;
-      } else {
-        src = a.in0 + ((size_t)y * a.Wi + x) * CIN + ch * 8;
-      }
+      const uint16_t* src = a.in0 + ((size_t)y * a.Wi + x) * CIN + ch * 8;
       v[u] = *reinterpret_cast<const uint4*>(src);
       if constexpr (EDGE) {
         const uint32_t keep = ok ? 0xffffffffu : 0u;
@@ -254,17 +245,20 @@ __device__ __forceinline__ void stage_tile(const ConvArgs& a, const int x0, cons
   }
 }
 
-// [up2(in0), in1] of a tile inside the image: in0's pixels are staged at their
-// own resolution, once instead of up to four times (4 rows of 8 TPW + 2
-// pixels), behind each other's blocks, then in1's at full resolution.
+// [up2(in0), in1] of a tile: in0's pixels are staged at their own resolution,
+// once instead of up to four times (4 rows of 8 TPW + 2 pixels), block after
+// block, then in1's at full resolution. At the image's edge (EDGE) what lies
+// outside is staged from clamped addresses and zeroed where fragments are read
+// (a fine pixel past an odd edge shares its coarse pixel with one inside).
 template <int CIN, int CUP, int TPW>
 struct UpTile {
   using T = ConvTile<CIN - CUP, 1, TPW>;
   static constexpr int LR = 4, LP = 8 * TPW + 2, NCBL = CUP / 16;
   static constexpr int base = NCBL * LR * LP;  // units of in0, before in1's
   __device__ static int low(int cb, int lr, int lx) { return (cb * LR + lr) * LP + lx; }
+  static constexpr size_t lds_bytes() { return (size_t)base * 32 + T::lds_bytes(); }
 };
-template <int CIN, int CUP, int TPW>
+template <int CIN, int CUP, int TPW, bool EDGE>
 __device__ __forceinline__ void stage_up(const ConvArgs& a, const int x0, const int y0) {
   using U = UpTile<CIN, CUP, TPW>;
   using T = typename U::T;
@@ -272,8 +266,9 @@ __device__ __forceinline__ void stage_up(const ConvArgs& a, const int x0, const 
   constexpr int NL = U::LR * U::LP * CL, NIT = NL + T::SR * T::SP * CS, B = 6;
   uint4* st = reinterpret_cast<uint4*>(flr::lds);
   const int tid = threadIdx.x;
-  const uint16_t* lo = a.in0 + ((size_t)(y0 / 2 - 1) * a.Wl + (x0 / 2 - 1)) * CUP;
-  const uint16_t* hi = a.in1 + ((size_t)(y0 - 1) * a.Wi + (x0 - 1)) * (CIN - CUP);
+  const int ly = y0 / 2 - 1, lx0 = x0 / 2 - 1, hy = y0 - 1, hx = x0 - 1;  // first pixels
+  const uint16_t* lo = a.in0 + (EDGE ? 0 : ((size_t)ly * a.Wl + lx0) * CUP);
+  const uint16_t* hi = a.in1 + (EDGE ? 0 : ((size_t)hy * a.Wi + hx) * (CIN - CUP));
 #pragma unroll 1
   for (int b0 = 0; b0 < NIT; b0 += B * 256) {
     uint4 v[B];
@@ -285,12 +280,20 @@ __device__ __forceinline__ void stage_up(const ConvArgs& a, const int x0, const 
       int d;
       if (ic < NL) {
         const int pix = ic / CL, ch = ic - pix * CL, lr = pix / U::LP, lx = pix - lr * U::LP;
-        src = lo + (unsigned)((lr * a.Wl + lx) * CUP + ch * 8);
+        if constexpr (EDGE)
+          src = lo + ((size_t)min(max(ly + lr, 0), a.Hl - 1) * a.Wl +
+                      min(max(lx0 + lx, 0), a.Wl - 1)) * CUP + ch * 8;
+        else
+          src = lo + (unsigned)((lr * a.Wl + lx) * CUP + ch * 8);
         d = U::low(ch >> 1, lr, lx) * 2 + (ch & 1);
       } else {
         const int j = ic - NL, pix = j / CS, ch = j - pix * CS, sr = pix / T::SP,
                   sx = pix - sr * T::SP;
-        src = hi + (unsigned)((sr * a.Wi + sx) * (CIN - CUP) + ch * 8);
+        if constexpr (EDGE)
+          src = hi + ((size_t)min(max(hy + sr, 0), a.Hi - 1) * a.Wi +
+                      min(max(hx + sx, 0), a.Wi - 1)) * (CIN - CUP) + ch * 8;
+        else
+          src = hi + (unsigned)((sr * a.Wi + sx) * (CIN - CUP) + ch * 8);
         d = (U::base + T::unit(ch >> 1, sr, sx)) * 2 + (ch & 1);
       }
       v[u] = *reinterpret_cast<const uint4*>(src);
@@ -337,8 +340,9 @@ __device__ __forceinline__ void stage_input(const ConvArgs& a, const int x0, con
 }
 
 // The matrix products of one wave's output row from the staged tile, and the
-// epilogue. LOW: staged by stage_up.
-template <int CIN, int COUT, int ST, int CUP, int FUSE, int COUT2, int TPW, bool LOW>
+// epilogue. LOW: staged by stage_up, EDGE: at the image's edge.
+template <int CIN, int COUT, int ST, int CUP, int FUSE, int COUT2, int TPW, bool LOW,
+          bool EDGE>
 __device__ __forceinline__ void conv_row(const ConvArgs& a, const int x0, const int y0,
                                          const int wv) {
   using T = ConvTile<CIN, ST, TPW>;
@@ -351,7 +355,14 @@ __device__ __forceinline__ void conv_row(const ConvArgs& a, const int x0, const 
       const int u = cb < U::NCBL
                         ? U::low(cb, (wv + ky + 1) >> 1, ((lx + kx + 1) >> 1) + t * 8)
                         : U::base + U::T::unit(cb - U::NCBL, wv + ky, kx) + t * 16 + lx;
-      return st[u * 4 + kq];
+      bf16x4_t v = st[u * 4 + kq];
+      if constexpr (EDGE) {
+        const int y = y0 + wv + ky - 1, x = x0 + t * 16 + lx + kx - 1;
+        const bool in = y >= 0 && y < a.Hi && x >= 0 && x < a.Wi;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = in ? v[j] : (short)0;
+      }
+      return v;
     } else {
       return st[(T::unit(cb, wv * ST + ky, kx) + t * 16 + lx) * 4 + kq];
     }
@@ -410,22 +421,26 @@ __global__ void __launch_bounds__(256) conv_kernel(ConvArgs a) {
   if constexpr (IN == IN_PLANES) {
     stage_input<TPW>(a, x0, y0);
   } else if constexpr (IN == IN_UPCAT) {
-    if (!edge) {  // uniform across the workgroup
-      stage_up<CIN, CUP, TPW>(a, x0, y0);
-      __syncthreads();
-      conv_row<CIN, COUT, ST, CUP, FUSE, COUT2, TPW, true>(a, x0, y0, wv);
-      return;
-    }
-    stage_tile<CIN, ST, IN, CUP, TPW, true>(a, x0, y0);
+    if (edge)  // uniform across the workgroup
+      stage_up<CIN, CUP, TPW, true>(a, x0, y0);
+    else
+      stage_up<CIN, CUP, TPW, false>(a, x0, y0);
+    __syncthreads();
+    if (y0 + wv >= a.Ho) return;
+    if (edge)
+      conv_row<CIN, COUT, ST, CUP, FUSE, COUT2, TPW, true, true>(a, x0, y0, wv);
+    else
+      conv_row<CIN, COUT, ST, CUP, FUSE, COUT2, TPW, true, false>(a, x0, y0, wv);
+    return;
   } else {
     if (edge)
-      stage_tile<CIN, ST, IN, CUP, TPW, true>(a, x0, y0);
+      stage_tile<CIN, ST, TPW, true>(a, x0, y0);
     else
-      stage_tile<CIN, ST, IN, CUP, TPW, false>(a, x0, y0);
+      stage_tile<CIN, ST, TPW, false>(a, x0, y0);
   }
   __syncthreads();
   if (y0 + wv >= a.Ho) return;  // uniform across the wave; no barrier follows
-  conv_row<CIN, COUT, ST, CUP, FUSE, COUT2, TPW, false>(a, x0, y0, wv);
+  conv_row<CIN, COUT, ST, CUP, FUSE, COUT2, TPW, false, false>(a, x0, y0, wv);
 }
 
 // Packing: FP32 weight [cout][cin][k][k] -> fragments (tap, cin block,
@@ -563,15 +578,22 @@ bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
   return a0 < b0 + nb && b0 < a0 + na;
 }
 
+template <int CIN, int ST, int IN, int CUP, int TPW>
+constexpr size_t conv_lds_bytes() {
+  if constexpr (IN == IN_UPCAT)
+    return UpTile<CIN, CUP, TPW>::lds_bytes();
+  else
+    return ConvTile<CIN, ST, TPW>::lds_bytes();
+}
 // Tiles of 64 pixels where they give kConvMinGroups workgroups (two per CU),
 // else 32, else 16: at training-crop sizes the half and quarter grids would
-// otherwise leave most CUs idle. 96 input channels: at most 32 pixels (64
-// would fill half a CU's LDS).
+// otherwise leave most CUs idle. Stride 2 and the 96-channel layer: at most 32
+// pixels (their staged tiles would keep too few workgroups on a CU).
 constexpr int kConvMinGroups = 512;
 template <int CIN, int COUT, int ST, int IN, int CUP, int FUSE, int COUT2, int TPW>
 hipError_t launch_tpw(const ConvArgs& a, hipStream_t s) {
   auto k = conv_kernel<CIN, COUT, ST, IN, CUP, FUSE, COUT2, TPW>;
-  const size_t lds = ConvTile<CIN, ST, TPW>::lds_bytes();
+  const size_t lds = conv_lds_bytes<CIN, ST, IN, CUP, TPW>();
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
