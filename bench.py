@@ -78,7 +78,7 @@ def kernel_source_digest() -> str:
     launch (the counters are void once any of them changes)."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2410_11625_amd", "csrc")
-    for f in ("flr_device.hpp", "flr_launch.hpp", "flr_prefix.hpp", "flr_q08.hip"):
+    for f in ("flr_avg.hpp", "flr_device.hpp", "flr_launch.hpp", "flr_prefix.hpp", "flr_q08.hip"):
         h.update(open(os.path.join(csrc, f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -121,7 +121,7 @@ def cpu_baseline_child() -> None:
     print(json.dumps({"seconds": times, "pixels": n * n}))
 
 
-DOMINANT_KERNEL = {"two_pass": "walk_kernel<8, 3, 3", "fused": "walk_kernel<8, 3, 2",
+DOMINANT_KERNEL = {"two_pass": "walk_pair_kernel<8, 3, 3", "fused": "walk_kernel<8, 3, 2",
                    "stages": "walk_kernel<8, 3, 0"}
 
 
@@ -578,7 +578,7 @@ def time_path(flr, torch, np, sets, nsets, dev, stream, path, steps, warmup):
     if path == "two_pass":
         dom_ms = float(np.mean(first))
         dom_flops = algo_flops_per_px(Q, C, "coefficients") * pix
-        dom_name = "flr_coefficients (walk_kernel<8,3,W_COEFFS>)"
+        dom_name = "flr_coefficients (walk_pair_kernel<8,3,W_COEFFS>)"
         second_ms = round(float(np.mean(per - first)), 5)
     else:
         dom_ms = float(np.mean(per))

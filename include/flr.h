@@ -263,7 +263,7 @@ typedef struct {
   int32_t height, width;              /* output grid, and the guides' */
   int32_t noisy_height, noisy_width;  /* the noisy input's grid */
   int32_t tile_rows;                  /* rows per workgroup of the coefficient walk; 0 = planned */
-  int32_t apply_rows;                 /* rows per workgroup of the averaging (at most 17); 0 =
+  int32_t apply_rows;                 /* rows per workgroup of the averaging (at most 4); 0 =
                                          as tile_rows (flr_denoise's choice: same tiles, same
                                          results bit for bit) */
   const float* guides;                /* [Q][height][width] */

@@ -108,7 +108,9 @@ flr_status flr_net_forward_trace(int32_t height, int32_t width, const float* gui
                                  size_t trace_bytes, void* stream);
 
 /* Workspace bytes of flr_net_backward for a height x width frame: the
- * forward's activations plus FP32 gradient tensors (about 1.3 KB per pixel).
+ * forward's activations, FP32 gradient tensors and partial weight gradients
+ * (1.25 KB per pixel at 1080p, 1.44 at 256 x 256, 2.25 at 64 x 64, where the
+ * partials weigh most).
  * 0 for invalid sizes. */
 size_t flr_net_backward_workspace_bytes(int32_t height, int32_t width);
 
@@ -131,10 +133,7 @@ size_t flr_net_backward_workspace_bytes(int32_t height, int32_t width);
  * gradients are sums over all pixels, added in a fixed order (repeatable
  * bit for bit). Errors as flr_net_forward, FLR_ERR_MODE for accumulate not
  * 0 or 1, FLR_ERR_ALIAS when grad_params or the workspace overlaps an input
- * or each other. Tuning: the data gradients take 16 input channels per
- * thread on layers of at least FLR_DGRAD_WIDE_PX pixels (environment
- * variable, read at each call; default 2^18) and 8 below; the result is
- * bit-identical either way. */
+ * or each other. */
 flr_status flr_net_backward(int32_t height, int32_t width, const float* guides,
                             const float* noisy, const float* params, const void* packed,
                             const float* grad_out, float* grad_params, int32_t accumulate,

@@ -7,9 +7,9 @@ of the frame's size) instead of taken from the launch planner's cost model:
   which every segment repeats, against filling 256 compute units in whole
   waves of workgroups (candidates: the planner's choice and ceil(H / n) for
   n = 1..16 segments);
-* the averaging tile height (rows per workgroup, at most 17): the 2r halo
+* the averaging tile height (rows per workgroup, at most 4): the 2r halo
   rows every tile re-reads against the number of tiles (candidates: the
-  walk's segment length, which is flr_denoise's choice, and 4, 8, 12, 17);
+  walk's segment length, which is flr_denoise's choice, and 2, 4);
 * in a batch, one segment length for every plain frame's walk (each
   frame's own choice, or a longer one: a batch fills the GPU whatever its
   frames' segment counts, so fewer warm-up rows can win; whole batch timed);
@@ -90,7 +90,7 @@ def candidate_rows(H: int) -> list[int]:
 
 def candidate_apply_rows() -> list[int]:
     """0 (the walk's segment length, as flr_denoise) and fixed heights."""
-    return [0, 4, 8, 12, 17]
+    return [0, 2, 4]
 
 
 def _time(fn, reps: int) -> float:

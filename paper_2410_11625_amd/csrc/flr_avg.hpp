@@ -23,8 +23,8 @@
 // 30 planes of 8.3 MB, five times each, in 135 us = 9.2 TB/s). Measured
 // against one workgroup per tile and all channels, 17 rows, one column per
 // lane, planes in turn: 256 x 256, Q = 12 144 -> 17 us; 540p, Q = 8 121 ->
-// 38 us; 720p, Q = 12 177 -> 83 us; 1080p, Q = 8 149 -> 135 us; 540p, r = 16,
-// Q = 6, C = 1 86 -> 35 us. Staging a tile's rows of a plane in LDS for four
+// 37 us; 720p, Q = 12 177 -> 83 us; 1080p, Q = 8 149 -> 135 us; 540p, r = 16,
+// Q = 6, C = 1 86 -> 27 us. Staging a tile's rows of a plane in LDS for four
 // wavefronts (16 rows, each fetched twice) took 176 us at 1080p: its barriers
 // leave too few loads in flight.
 #pragma once

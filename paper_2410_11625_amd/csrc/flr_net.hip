@@ -20,8 +20,9 @@
 // epilogue instructions beside few matrix instructions. Measured against
 // 8-byte staging with per-chunk clamps, a separate pass for the input and the
 // 64- and 96-channel layers reading operands from L2, 64 pixels per wave at
-// every size: 1080p 802 -> 608 us; 256 x 256 137 -> 75 us (its half and quarter
-// grids left most CUs idle).
+// every size: 1080p 802 -> 608 us (569 with the decoder's upsampled half staged
+// at its own resolution); 256 x 256 137 -> 75 us (its half and quarter grids
+// left most CUs idle).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
