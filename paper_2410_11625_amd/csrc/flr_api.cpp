@@ -834,8 +834,8 @@ flr_status flr_batch_plan(const flr_params* p, const flr_frame* frames, int32_t 
     const LaunchArgs& a = apply[i];
     const LaunchArgs& w = walk_sorted[inv[i]];
     largs[nl] = a;
-    stage(flr::BI_AVG, nl++, flr::avg_workgroups(a.tiles_x * a.n_seg, C), 0, walk_ctr[inv[i]], w.tiles_x, -1,
-          w.seg_rows, w.n_seg);
+    stage(flr::BI_AVG, nl++, flr::avg_items(a.tiles_x * a.n_seg), 0, walk_ctr[inv[i]], w.tiles_x,
+          -1, w.seg_rows, w.n_seg);
   }
   for (int j = 0; j < nj; ++j) {
     const LaunchArgs& a = up[j];

@@ -1249,8 +1249,13 @@ __global__ void __launch_bounds__(kThreads, 1) batch_kernel(LaunchArgs ain) {
         bool ok = true;
         if (S.kind == BI_AVG) {
           const LaunchArgs& f = P->largs[S.arg];
-          const int y0 = b / f.nc % f.n_seg * f.seg_rows;
-          const int y1 = min(y0 + f.seg_rows, f.H);
+          // the item's tiles run down a strip; one that goes on in the next
+          // strip waits for the frame's whole height
+          const int t0 = b * kAvgItemTiles;
+          const int t1 = min(t0 + kAvgItemTiles, f.tiles_x * f.n_seg) - 1;
+          const bool one = t0 / f.n_seg == t1 / f.n_seg;
+          const int y0 = one ? t0 % f.n_seg * f.seg_rows : 0;
+          const int y1 = one ? min((t1 % f.n_seg + 1) * f.seg_rows, f.H) : f.H;
           const int s0 = max(y0 - f.r, 0) / S.seg_rows;
           const int s1 = min((min(y1 + f.r, f.H) - 1) / S.seg_rows, S.nseg - 1);
           for (int sg = s0; sg <= s1 && ok; ++sg)
@@ -1282,9 +1287,15 @@ __global__ void __launch_bounds__(kThreads, 1) batch_kernel(LaunchArgs ain) {
       case BI_JMEAN:
         box_tile_any<BOX_MEAN64, WIDE>(P->bargs[S.arg], b % S.nx, b / S.nx);
         break;
-      case BI_AVG:
-        avg_group<AV>(P->largs[S.arg], b);
+      case BI_AVG: {
+        const LaunchArgs& f = P->largs[S.arg];
+        const int g1 = min((b + 1) * kAvgItemTiles, f.tiles_x * f.n_seg) * f.nc;
+        for (int g = b * kAvgItemTiles * f.nc; g < g1; ++g) {
+          avg_group<AV>(f, g);
+          __syncthreads();  // the group is done with LDS
+        }
         break;
+      }
       default:
         up_apply_item<Q, C>(P->largs[S.arg], b);
         break;
