@@ -14,44 +14,50 @@ constexpr int kLrTile = 16;
 struct LrBlurArgs {
   const double* src;
   double* dst;
-  int Hl, Wl, R, tiles_x;
+  int Hl, Wl, tiles_x;
   double taps[2 * kMaxLowresRadius + 1];
 };
 
-__global__ void __launch_bounds__(256) lr_blur_kernel(LrBlurArgs a) {
-  constexpr int SMAX = kLrTile + 2 * kMaxLowresRadius;
-  __shared__ double tile[SMAX * SMAX];
-  __shared__ double mid[SMAX * kLrTile];
+// What bounds it: the tile's loads, its halo read from L2 (2.25 loads per output
+// at radius 4). The radius is a template parameter so that every tap's LDS read
+// is in flight at once (with a loop over a runtime radius each waited for the
+// one before) and positions need no division: 23.0 -> 13.9 us at 1080p, 8 x 8
+// blocks, 72 planes. Tiles of 32 and 64 rows took 13.8 and 14.0.
+template <int R>
+__global__ void __launch_bounds__(kThreads) lr_blur_kernel(LrBlurArgs a) {
+  constexpr int SX = kLrTile + 2 * R, SY = kLrTile + 2 * R;
+  constexpr int NL = (SX * SY + kThreads - 1) / kThreads;
+  __shared__ double tile[SX * SY];
+  __shared__ double mid[SY * kLrTile];
   const int tid = threadIdx.x;
-  const int R = a.R, S = kLrTile + 2 * R;
   const int bx = blockIdx.x % a.tiles_x, by = blockIdx.x / a.tiles_x;
   const int64_t pll = (int64_t)a.Hl * a.Wl;
   const double* src = a.src + (int64_t)blockIdx.y * pll;
   const int I0 = by * kLrTile - R, J0 = bx * kLrTile - R;
-  // at most four items per lane (S <= 32); loads from clamped positions,
-  // issued together, zero outside the grid
-  double v[4];
-  bool in[4];
+  // loads from clamped positions, issued together, zero outside the grid
+  double v[NL];
+  bool in[NL];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < NL; ++u) {
     const int t = tid + u * kThreads;
-    const int ii = t / S, jj = t - (t / S) * S;
+    const int ii = t / SX, jj = t - (t / SX) * SX;
     const int I = I0 + ii, J = J0 + jj;
-    in[u] = t < S * S && I >= 0 && I < a.Hl && J >= 0 && J < a.Wl;
+    in[u] = t < SX * SY && I >= 0 && I < a.Hl && J >= 0 && J < a.Wl;
     const int Ic = I < 0 ? 0 : (I >= a.Hl ? a.Hl - 1 : I);
     const int Jc = J < 0 ? 0 : (J >= a.Wl ? a.Wl - 1 : J);
     v[u] = src[(int64_t)Ic * a.Wl + Jc];
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < NL; ++u) {
     const int t = tid + u * kThreads;
-    if (t < S * S) tile[t] = in[u] ? v[u] : 0.0;
+    if (t < SX * SY) tile[t] = in[u] ? v[u] : 0.0;
   }
   __syncthreads();
-  for (int t = tid; t < S * kLrTile; t += kThreads) {
+  for (int t = tid; t < SY * kLrTile; t += kThreads) {
     const int ii = t / kLrTile, jj = t - (t / kLrTile) * kLrTile;
     double s = 0.0;
-    for (int d = -R; d <= R; ++d) s = fma(a.taps[d + R], tile[ii * S + jj + R + d], s);
+#pragma unroll
+    for (int d = 0; d <= 2 * R; ++d) s = fma(a.taps[d], tile[ii * SX + jj + d], s);
     mid[t] = s;
   }
   __syncthreads();
@@ -59,9 +65,18 @@ __global__ void __launch_bounds__(256) lr_blur_kernel(LrBlurArgs a) {
   const int I = by * kLrTile + ii, J = bx * kLrTile + jj;
   if (I < a.Hl && J < a.Wl) {
     double s = 0.0;
-    for (int d = -R; d <= R; ++d) s = fma(a.taps[d + R], mid[(ii + R + d) * kLrTile + jj], s);
+#pragma unroll
+    for (int d = 0; d <= 2 * R; ++d) s = fma(a.taps[d], mid[(ii + d) * kLrTile + jj], s);
     a.dst[(int64_t)blockIdx.y * pll + (int64_t)I * a.Wl + J] = s;
   }
+}
+
+template <int R>
+hipError_t launch_blur(const LrBlurArgs& a, int rad, int blocks, int planes, hipStream_t s) {
+  if constexpr (R < kMaxLowresRadius)
+    if (rad > R) return launch_blur<R + 1>(a, rad, blocks, planes, s);
+  hipLaunchKernelGGL(lr_blur_kernel<R>, dim3(blocks, planes), dim3(kThreads), 0, s, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_lr_blur(const double* src, double* dst, int planes, int Hl, int Wl, int R,
@@ -73,12 +88,10 @@ hipError_t launch_lr_blur(const double* src, double* dst, int planes, int Hl, in
   a.dst = dst;
   a.Hl = Hl;
   a.Wl = Wl;
-  a.R = R;
   a.tiles_x = (Wl + kLrTile - 1) / kLrTile;
   const int tiles_y = (Hl + kLrTile - 1) / kLrTile;
   for (int k = 0; k < 2 * kMaxLowresRadius + 1; ++k) a.taps[k] = k <= 2 * R ? taps[k] : 0.0;
-  hipLaunchKernelGGL(lr_blur_kernel, dim3(a.tiles_x * tiles_y, planes), dim3(kThreads), 0, s, a);
-  return hipGetLastError();
+  return launch_blur<0>(a, R, a.tiles_x * tiles_y, planes, s);
 }
 
 }  // namespace flr
