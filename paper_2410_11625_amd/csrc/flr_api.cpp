@@ -744,7 +744,7 @@ flr_status flr_batch_plan(const flr_params* p, const flr_frame* frames, int32_t 
       a.Wl = f.noisy_width;
       a.up = frame_up(f);
       up[nj] = a;
-      ws_up[nj + 1] = ws_up[nj] + flr::up_items(f.height, f.width, Q, C);
+      ws_up[nj + 1] = ws_up[nj] + flr::up_items(f.height, f.width);
       out_plan->joint_guides[nj] = f.guides_low;
       out_plan->joint_noisy[nj] = f.noisy;
       out_plan->joint_sums[nj] = reinterpret_cast<double*>(ws + L.coef[i]);
@@ -840,7 +840,7 @@ flr_status flr_batch_plan(const flr_params* p, const flr_frame* frames, int32_t 
   for (int j = 0; j < nj; ++j) {
     const LaunchArgs& a = up[j];
     largs[nl] = a;
-    stage(flr::BI_UP, nl++, flr::up_items(a.H, a.W, Q, C), 0, jctr[j] + 2, jmean_items[j], -1, 0,
+    stage(flr::BI_UP, nl++, flr::up_items(a.H, a.W), 0, jctr[j] + 2, jmean_items[j], -1, 0,
           0);
   }
   flr::BatchPlanDev pd = {};

@@ -1426,7 +1426,7 @@ hipError_t launch_qc(int kind, const LaunchArgs& a, hipStream_t s) {
       return hipErrorInvalidValue;
     case K_UP_APPLY_BATCH:
       return launch_with_lds(up_apply_kernel<Q, C, true>, a.batch_blocks,
-                             lr_apply_lds_bytes(Q, C, 2, up_rows(Q, C)), a, s);
+                             lr_apply_lds_bytes(Q, C, 2, 1), a, s);
     case K_BATCH_PERSISTENT:
       if constexpr (!split_walk(Q, C)) {
         const size_t l = batch_lds_bytes(Q, C);

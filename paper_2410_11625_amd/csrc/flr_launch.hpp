@@ -226,23 +226,21 @@ struct LaunchArgs {
 __host__ __device__ constexpr size_t lr_apply_lds_bytes(int Q, int C, int block, int rows) {
   return (size_t)rows * (Q + 1) * C * ((kThreads - 1) / block + 3) * sizeof(double);
 }
-// Rows per workgroup of the staged interpolation: the most of 8, 4, 2, 1
-// whose staging fits in 64 KiB; 0 when none does (one lane per pixel then).
+// Rows per workgroup of the staged interpolation: the most of 8, 4, 2 whose
+// staging fits in 32 KiB (five or more workgroups per CU: a workgroup stages,
+// then computes, and others fill either half's waits), else one row where
+// that fits in 64 KiB; 0 when it does not (one lane per pixel then). Measured at
+// 1080p, Q = 8, C = 3, 8 x 8 blocks: 8 rows in 59 KB 44.5 us, 4 in 29 KB 32.3, 2
+// in 15 KB 33.2.
 inline int lr_apply_rows(int Q, int C, int block) {
-  for (int rows = 8; rows >= 1; rows /= 2)
-    if (lr_apply_lds_bytes(Q, C, block, rows) <= 65536) return rows;
-  return 0;
+  for (int rows = 8; rows > 1; rows /= 2)
+    if (lr_apply_lds_bytes(Q, C, block, rows) <= 32768) return rows;
+  return lr_apply_lds_bytes(Q, C, block, 1) <= 65536 ? 1 : 0;
 }
 
-// Rows of an upsampling tile: the staging of two rows at 2 x (the finest
-// models) fits in 64 KiB up to (Q + 1) C = 31, one row otherwise.
-__host__ __device__ constexpr int up_rows(int Q, int C) {
-  return lr_apply_lds_bytes(Q, C, 2, 2) <= 65536 ? 2 : 1;
-}
-inline int up_items(int H, int W, int Q, int C) {
-  const int rows = up_rows(Q, C);
-  return ((W + kThreads - 1) / kThreads) * ((H + rows - 1) / rows);
-}
+// Upsampling tiles have one row: staged at 2 x it takes 28 KB at Q = 8, C = 3
+// (two rows, 57 KB: 114 against 88 us at 1080p).
+inline int up_items(int H, int W) { return ((W + kThreads - 1) / kThreads) * H; }
 
 // The downsampled-moment variant's low-resolution planes: the pixel count
 // n then the num_sums(Q, C) anchored product sums (FP64, [planes][Hl][Wl]);
@@ -493,7 +491,7 @@ inline void plan_walk(int kind, int H, int W, int Q, int C, int r, int tile_rows
 // averaging kernel's (its box items use the ring where it fits in that).
 inline size_t batch_lds_bytes(int Q, int C) {
   const size_t w = walk_lds_bytes(K_COEFFS, Q, C), v = avg_lds_bytes(kAvgTileRows);
-  const size_t u = lr_apply_lds_bytes(Q, C, 2, up_rows(Q, C)), m = w > v ? w : v;
+  const size_t u = lr_apply_lds_bytes(Q, C, 2, 1), m = w > v ? w : v;
   return u > m ? u : m;
 }
 

@@ -236,10 +236,10 @@ __device__ __forceinline__ void lr_axis(int k, int block, int n_low, int* k0, in
 //
 // What bounds it: LDS reads (two columns of every model per pixel) and, with
 // 2 x upsampling, staging 131 columns for 256 pixels. Measured at 1080p, Q = 8,
-// C = 3: 8 x 8 blocks 57 -> 44 us against dividing out the row and position of
-// every staged item; 2 x upsampling 131 -> 114 us against four loads of every
-// model per pixel.
-template <int Q, int C>
+// C = 3: 8 x 8 blocks 57 -> 32 us against dividing out the row and position of
+// every staged item, in 59 KB of LDS; 2 x upsampling 131 -> 88 us against four
+// loads of every model per pixel.
+template <int Q, int C, int NU>
 __device__ __forceinline__ void lr_apply_tile(const LaunchArgs& a, const int bx, const int by,
                                               const int block, const int TR, const float* cg,
                                               const float* cy, const int64_t cplane) {
@@ -258,31 +258,31 @@ __device__ __forceinline__ void lr_apply_tile(const LaunchArgs& a, const int bx,
   lr_axis(xl, block, a.Wl, &d1, &c_hi, &dt);
   const int nc = c_hi - c_lo + 1;
   const int total = FC * nc;
-  // rows two at a time: their four loads of an item are in flight together,
-  // two items per lane
-  for (int rr = 0; rr < TR; rr += 2) {
-    int r0[2], r1[2];
-    double w[2];
+  // rows NU at a time, 4 / NU items per lane: eight loads in flight together
+  constexpr int NJ = 4 / NU;
+  for (int rr = 0; rr < TR; rr += NU) {
+    int r0[NU], r1[NU];
+    double w[NU];
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < NU; ++u)
       lr_axis(min(Y0 + rr + u, a.H - 1), block, a.Hl, &r0[u], &r1[u], &w[u]);
-    for (int t0 = tid; t0 < total; t0 += 2 * kThreads) {
-      double v0[2][2], v1[2][2];
+    for (int t0 = tid; t0 < total; t0 += NJ * kThreads) {
+      double v0[NJ][NU], v1[NJ][NU];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < NJ; ++j) {
         const int t = min(t0 + j * kThreads, total - 1);
         const int k = t / nc, cc = t - k * nc;
         const double* m = a.fin + k * pll + c_lo + cc;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < NU; ++u) {
           v0[j][u] = m[(int64_t)r0[u] * a.Wl];
           v1[j][u] = m[(int64_t)r1[u] * a.Wl];
         }
       }
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < NU; ++u)
           if (t0 + j * kThreads < total && rr + u < TR)
             st[(rr + u) * total + t0 + j * kThreads] = v0[j][u] * (T(1) - w[u]) + v1[j][u] * w[u];
     }
@@ -330,8 +330,8 @@ __device__ __forceinline__ void lr_apply_tile(const LaunchArgs& a, const int bx,
 }
 template <int Q, int C>
 __global__ void __launch_bounds__(256) lr_apply_staged_kernel(LaunchArgs a) {
-  lr_apply_tile<Q, C>(a, blockIdx.x, blockIdx.y, a.block, a.lr_rows, a.guides, a.noisy,
-                      (int64_t)a.H * a.W);
+  lr_apply_tile<Q, C, 2>(a, blockIdx.x, blockIdx.y, a.block, a.lr_rows, a.guides, a.noisy,
+                         (int64_t)a.H * a.W);
 }
 
 // Joint denoising and upsampling (Sec. 3.2): anchored FP64 models (b~ | a,
@@ -339,14 +339,12 @@ __global__ void __launch_bounds__(256) lr_apply_staged_kernel(LaunchArgs a) {
 // a.up times coarser than the output, bilinearly interpolated at each output
 // pixel (half-pixel centres, clamped) and applied to the full-resolution
 // guides with the anchors of the fit (pixel (0, 0) of the low-resolution
-// guides and of the noisy input). Batched over frames; an item is a tile of
-// up_rows(Q, C) rows by kThreads columns, down each strip of columns.
+// guides and of the noisy input). Batched over frames; an item is a row of
+// kThreads columns, down each strip of columns.
 template <int Q, int C>
 __device__ __forceinline__ void up_apply_item(const LaunchArgs a, const int bid) {
-  constexpr int TR = up_rows(Q, C);
-  const int ny = (a.H + TR - 1) / TR;
-  lr_apply_tile<Q, C>(a, bid / ny, bid % ny, a.up, TR, a.guides_low, a.noisy,
-                      (int64_t)a.Hl * a.Wl);
+  lr_apply_tile<Q, C, 1>(a, bid / a.H, bid % a.H, a.up, 1, a.guides_low, a.noisy,
+                         (int64_t)a.Hl * a.Wl);
 }
 template <int Q, int C, bool BATCH>
 __global__ void __launch_bounds__(256) up_apply_kernel(LaunchArgs ain) {

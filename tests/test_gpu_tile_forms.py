@@ -11,8 +11,8 @@
   the condition and by the sum over at most 11 guides of magnitude 3 (4e-5).
 * Batched averaging with frames of two- and of four-row tiles in one launch:
   bit for bit the single frames, by both schedules.
-* Model interpolation staged in 8, 4, 2, 1 or no rows, and upsampling tiles
-  of two rows or one: FP64 up to the output, so 1e-6 (see the bilinear
+* Model interpolation staged in 8, 4, 2, 1 or no rows, and upsampling tiles:
+  FP64 up to the output, so 1e-6 (see the bilinear
   models' own tests).
 """
 import numpy as np
@@ -78,7 +78,6 @@ def test_interpolation_rows(Q, C, block):
     assert _rel(got, want) <= 1e-6
 
 
-# (Q + 1) C = 31 at most stages two rows
 @pytest.mark.parametrize("Q,C", [(8, 3), (7, 4)])
 @pytest.mark.parametrize("up,H,W", [(2, 62, 258), (4, 44, 516), (8, 24, 264)])
 def test_upsampling_rows(Q, C, up, H, W):
