@@ -159,6 +159,25 @@ __device__ __forceinline__ void split3(float x, uint16_t (&h)[3]) {
   h[2] = (uint16_t)(__float_as_uint(r2) >> 16);
 }
 
+// D = A B + C of 16 x 16 x 4 FP32 (lane l: A row l % 16, k = l / 16; B k =
+// l / 16, column l % 16; C, D as the BF16 instruction). One of a and b holds
+// BF16 values (A32: b does).
+template <bool A32>
+__device__ __forceinline__ f32x4_t mfma_f32(float a, float b, f32x4_t c) {
+#if __has_builtin(__builtin_amdgcn_mfma_f32_16x16x4f32)
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+#else  // hosts that emulate the BF16 instruction only: the same products in three parts
+  uint16_t h[3];
+  split3(A32 ? a : b, h);
+  const bf16x4_t v = pack4((uint16_t)(__float_as_uint(A32 ? b : a) >> 16), 0, 0, 0);
+  for (int s = 2; s >= 0; --s) {
+    const bf16x4_t part = pack4(h[s], 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A32 ? part : v, A32 ? v : part, c, 0, 0, 0);
+  }
+  return c;
+#endif
+}
+
 struct DgradArgs {
   DzSrc dz;
   const bf16x4_t* w;  // the layer's data-gradient fragments
@@ -169,17 +188,20 @@ struct DgradArgs {
 };
 
 // Data gradient of one layer (CIN channels of dx from COUT of dz, both
-// multiples of 16; kernel KS, stride ST) as an implicit GEMM on the BF16
-// matrix cores: D (c x pixels) += W^T (c x o) dz (o x pixels). The weights are
-// BF16 as they are; dz is FP32 and is split exactly into three BF16 parts
-// when it is staged, three products each, accumulated in FP32: the error is
-// that of FP32 sums. (The FP32 matrix instruction runs at a sixteenth of the
-// BF16 rate: three BF16 products are the cheaper way to FP32.)
+// multiples of 16; kernel KS, stride ST) as an implicit GEMM on the FP32
+// matrix cores: D (c x pixels) += W^T (c x o) dz (o x pixels). The weights'
+// BF16 values are widened in registers. (Three BF16 products of dz split
+// exactly into three parts take a third of the matrix time, but the BF16
+// instruction's sums lean to minus infinity, by about 0.05 * 2^-24 of the
+// accumulator each: over a frame that bias adds up where the gradients
+// cancel. Relative rms error of in3's weights under a loss gradient of random
+// signs, in 2^-24: three BF16 products 429 at 256 x 256 and 1847 at 1080p,
+// FP32 15 and 27; the whole call at 256 x 256 320 -> 343 us.)
 //
 // A workgroup of four waves computes CBG 16-channel blocks of dx for four
 // rows (stride 2: four coarse rows, both row and both column parities) of
 // 16 NT pixels; per 16 output channels it stages the dz tile with its halo in
-// LDS (three planes of HWC BF16, zero outside the grid) and runs the taps.
+// LDS (HWC FP32, zero outside the grid) and runs the taps.
 template <int CIN, int COUT, int KS, int ST, int CBG, int NT>
 __global__ void __launch_bounds__(256) dgrad_kernel(DgradArgs a) {
   constexpr int NCB = CIN / 16, NOB = COUT / 16;
@@ -187,7 +209,7 @@ __global__ void __launch_bounds__(256) dgrad_kernel(DgradArgs a) {
   constexpr int LO = KS == 3 && ST == 1 ? 1 : 0;         // of which before it
   constexpr int SR = 4 + HALO, SP = 16 * NT + HALO;
   constexpr int NPAR = ST * ST, NCG = NCB / CBG;
-  bf16x4_t* st = reinterpret_cast<bf16x4_t*>(flr::lds);  // [3][SR][SP][4]
+  float4* st = reinterpret_cast<float4*>(flr::lds);  // [SR][SP][4]
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, kq = lane >> 4;
   const int x0 = blockIdx.x / NCG * 16 * NT, y0 = blockIdx.y * 4, cb0 = blockIdx.x % NCG * CBG;
   f32x4_t acc[NPAR][NT][CBG];
@@ -216,15 +238,9 @@ __global__ void __launch_bounds__(256) dgrad_kernel(DgradArgs a) {
 #pragma unroll
       for (int u = 0; u < B; ++u) {
         const int i = b0 + u * 256 + tid;
-        const float v[4] = {d[u].x, d[u].y, d[u].z, d[u].w};
-        uint16_t h[4][3];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) split3(ok[u] ? v[j] : 0.f, h[j]);
-        if (i < NIT) {
-#pragma unroll
-          for (int s = 0; s < 3; ++s)
-            st[s * NIT + i] = pack4(h[0][s], h[1][s], h[2][s], h[3][s]);
-        }
+        if (i < NIT)
+          st[i] = float4{ok[u] ? d[u].x : 0.f, ok[u] ? d[u].y : 0.f, ok[u] ? d[u].z : 0.f,
+                         ok[u] ? d[u].w : 0.f};
       }
     }
     __syncthreads();
@@ -238,21 +254,22 @@ __global__ void __launch_bounds__(256) dgrad_kernel(DgradArgs a) {
         const int par = ST == 1 ? 0 : ((u + 1) & 1) * 2 + ((v + 1) & 1);
         const int dy = KS == 1 ? 0 : (ST == 1 ? 2 - u : (u == 0 ? 1 : 0));
         const int dx = KS == 1 ? 0 : (ST == 1 ? 2 - v : (v == 0 ? 1 : 0));
-        bf16x4_t av[CBG];
+        float av[CBG][4];  // lane: output channels 4 kq + j, as dz below
 #pragma unroll
-        for (int cb = 0; cb < CBG; ++cb)
-          av[cb] = a.w[((tap * NOB + ob) * NCB + cb0 + cb) * 64 + lane];
+        for (int cb = 0; cb < CBG; ++cb) {
+          const bf16x4_t w = a.w[((tap * NOB + ob) * NCB + cb0 + cb) * 64 + lane];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) av[cb][j] = bf2f((uint16_t)w[j]);
+        }
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          const int i = ((wv + dy) * SP + t * 16 + (lane & 15) + dx) * 4 + kq;
-          const bf16x4_t b0 = st[i], b1 = st[NIT + i], b2 = st[2 * NIT + i];
+          const float4 z = st[((wv + dy) * SP + t * 16 + (lane & 15) + dx) * 4 + kq];
+          const float b[4] = {z.x, z.y, z.z, z.w};
 #pragma unroll
-          for (int cb = 0; cb < CBG; ++cb) {
-            f32x4_t c = acc[par][t][cb];
-            c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[cb], b2, c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[cb], b1, c, 0, 0, 0);
-            acc[par][t][cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[cb], b0, c, 0, 0, 0);
-          }
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int cb = 0; cb < CBG; ++cb)
+              acc[par][t][cb] = mfma_f32<false>(av[cb][j], b[j], acc[par][t][cb]);
         }
       }
     }
@@ -283,7 +300,7 @@ __global__ void __launch_bounds__(256) dgrad_kernel(DgradArgs a) {
 template <int KS, int ST, int NT>
 constexpr size_t dgrad_lds_bytes() {
   constexpr int halo = KS == 1 ? 0 : (ST == 1 ? 2 : 1);
-  return (size_t)3 * (4 + halo) * (16 * NT + halo) * 4 * sizeof(bf16x4_t);
+  return (size_t)(4 + halo) * (16 * NT + halo) * 4 * sizeof(float4);
 }
 
 // Input of a layer as the backward reads it: one HWC BF16 tensor, or
@@ -315,21 +332,6 @@ struct WgradArgs {
   int rfirst[13];     // first element of each layer in the reduction
   int accumulate;
 };
-
-// D = A B + C of 16 x 16 x 4 FP32 (lane l: A row l % 16, k = l / 16; B k =
-// l / 16, column l % 16; C, D as the BF16 instruction). b holds a BF16 value.
-__device__ __forceinline__ f32x4_t mfma_f32(float a, float b, f32x4_t c) {
-#if __has_builtin(__builtin_amdgcn_mfma_f32_16x16x4f32)
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-#else  // hosts that emulate the BF16 instruction only: the same products in three parts
-  uint16_t h[3];
-  split3(a, h);
-  const bf16x4_t bv = pack4((uint16_t)(__float_as_uint(b) >> 16), 0, 0, 0);
-  for (int s = 2; s >= 0; --s)
-    c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pack4(h[s], 0, 0, 0), bv, c, 0, 0, 0);
-  return c;
-#endif
-}
 
 // Weight gradients as GEMMs over pixels on the matrix cores: D (o x c) += dz
 // (o x pixels) x (pixels x c), one accumulator per tap. A workgroup stages a
@@ -410,13 +412,13 @@ __device__ __forceinline__ void wgrad_tile(const WgradLayer& a, const int wg) {
 #pragma unroll 4
     for (int s = 0; s < 16; ++s) {
       const float z = zr[s * 64];
-      if (cb == 0) bacc = mfma_f32(z, one, bacc);
+      if (cb == 0) bacc = mfma_f32<true>(z, one, bacc);
 #pragma unroll
       for (int u = 0; u < KS; ++u)
 #pragma unroll
         for (int v = 0; v < KS; ++v) {
           const float x = bf2f(xr[(u * XP + 4 * s * ST + v) * 16]);
-          acc[u * KS + v] = mfma_f32(z, x, acc[u * KS + v]);
+          acc[u * KS + v] = mfma_f32<true>(z, x, acc[u * KS + v]);
         }
     }
   }
