@@ -130,3 +130,12 @@ def _errors(H, W, layers):
 def test_net_backward_rounding_does_not_lean(H, W):
     errs = _errors(H, W, 12)
     assert len(errs) == 24 and max(errs.values()) <= TOL, errs
+
+
+def test_weight_gradient_chains_stay_short():
+    """Sums over a large frame: the last two layers, whose dz carries next to
+    no error of its own. One chain of a chunk's 3264 products would give 23
+    units, chains of 128 give 5 and their second level of 26 sums 2; twice
+    that."""
+    errs = _errors(1080, 1920, 2)
+    assert len(errs) == 4 and max(errs.values()) <= 14, errs
