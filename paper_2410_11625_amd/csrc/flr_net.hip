@@ -26,6 +26,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+#include <stdlib.h>
 
 #include "flr.h"
 #include "flr_net.h"
@@ -772,8 +773,19 @@ inline void bwd_layout(const Grids& g, size_t off[B_COUNT + 1]) {
 
 // Data gradient of a layer. Workgroups take two 16-channel blocks of dx
 // (the staged tile serves both) and 64 pixels of four rows; on grids that
-// would leave most CUs idle 32 pixels (kDgNarrowGroups workgroups of 64).
+// would leave most CUs idle 32 pixels (kDgNarrowGroups workgroups of 64). A
+// dx's sums are the same either way. FLR_DGRAD_WIDE_PX in the environment, when
+// it holds a number, sets the line in pixels of dx instead (a tuning knob).
 constexpr int kDgNarrowGroups = 256;
+inline int64_t dgrad_wide_px() {
+  const char* e = getenv("FLR_DGRAD_WIDE_PX");
+  if (e && *e) {
+    char* end = nullptr;
+    const long long v = strtoll(e, &end, 10);
+    if (end && *end == 0 && v >= 0) return v;
+  }
+  return -1;
+}
 template <int CIN, int COUT, int KS, int ST, int CBG, int NT>
 hipError_t launch_dgrad_nt(const DgradArgs& a, hipStream_t s) {
   // tiles of dx pixels (stride 2: of the coarse grid covering dx)
@@ -784,15 +796,17 @@ hipError_t launch_dgrad_nt(const DgradArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 template <int CIN, int COUT, int KS, int ST>
-hipError_t launch_dgrad(const DgradArgs& a, hipStream_t s) {
+hipError_t launch_dgrad(const DgradArgs& a, int64_t wide_px, hipStream_t s) {
   constexpr int CBG = CIN % 32 == 0 ? 2 : 1;
   const int Ht = (a.Hi + ST - 1) / ST, Wt = (a.Wi + ST - 1) / ST;
-  const int wide = (Wt + 63) / 64 * ((Ht + 3) / 4) * (CIN / 16 / CBG);
+  const bool wide = wide_px >= 0 ? (int64_t)a.Hi * a.Wi >= wide_px
+                                 : (Wt + 63) / 64 * ((Ht + 3) / 4) * (CIN / 16 / CBG) >=
+                                       kDgNarrowGroups;
   if constexpr (ST == 1) {
-    if (wide >= kDgNarrowGroups) return launch_dgrad_nt<CIN, COUT, KS, ST, CBG, 4>(a, s);
+    if (wide) return launch_dgrad_nt<CIN, COUT, KS, ST, CBG, 4>(a, s);
     return launch_dgrad_nt<CIN, COUT, KS, ST, CBG, 2>(a, s);
   } else {  // four parities' sums per pixel: 32 pixels, or 16
-    if (wide >= kDgNarrowGroups) return launch_dgrad_nt<CIN, COUT, KS, ST, CBG, 2>(a, s);
+    if (wide) return launch_dgrad_nt<CIN, COUT, KS, ST, CBG, 2>(a, s);
     return launch_dgrad_nt<CIN, COUT, KS, ST, CBG, 1>(a, s);
   }
 }
@@ -854,6 +868,7 @@ flr_status run_backward(const Grids& g, const float* guides, const float* noisy,
       BwdSrc{e2, e1, 64, 64, 32, g.Wq}, plain(t3, 32), BwdSrc{d1, e0, 32, 32, 16, g.Wh},
       plain(t4, 16), plain(t5, 16), plain(t6, 16)};
   bool ok = true;
+  const int64_t wide_px = dgrad_wide_px();
   auto D = [&](auto kernel, int li, float* dx, const float* add = nullptr, int add_cs = 0,
                int add_off = 0) {
     DgradArgs a = {};
@@ -867,7 +882,7 @@ flr_status run_backward(const Grids& g, const float* guides, const float* noisy,
     a.add = add;
     a.add_cs = add_cs;
     a.add_off = add_off;
-    ok = ok && kernel(a, s) == hipSuccess;
+    ok = ok && kernel(a, wide_px, s) == hipSuccess;
   };
   // from out3 back to in1, as in the forward reversed
   D(launch_dgrad<16, 16, 3, 1>, 10, fbuf(B_GT5));
