@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import fcntl
+import glob
 import json
 import os
 import subprocess
@@ -53,7 +54,6 @@ def sanitizer_env() -> dict:
     asan = subprocess.run([SAN_CXX, "-print-file-name=libclang_rt.asan-x86_64.so"],
                           stdout=subprocess.PIPE, text=True, check=True).stdout.strip()
     if not os.path.isabs(asan):
-        import glob
         asan = sorted(glob.glob(os.path.join(os.path.dirname(os.path.dirname(SAN_CXX)), "lib",
                                              "clang", "*", "lib", "linux",
                                              "libclang_rt.asan-x86_64.so")))[-1]
@@ -66,17 +66,21 @@ def sanitizer_env() -> dict:
     return env
 
 
+UNITS = [os.path.join(HERE, "emu.cpp")] + [os.path.join(CSRC, f) for f in (
+    "flr_api.cpp", "flr_net.hip", "flr_adjoint.hip", "flr_lowres.hip")]
+
+
+def dependencies() -> list:
+    """Files whose change calls for a new build: the compiled units, the HIP
+    stand-in and every header that they may include."""
+    return UNITS + [os.path.join(HERE, "hip", "hip_runtime.h")] + \
+        sorted(glob.glob(os.path.join(CSRC, "*.hpp"))) + \
+        sorted(glob.glob(os.path.join(INCLUDE, "*.h")))
+
+
 def build(force: bool = False) -> str:
-    srcs = [os.path.join(HERE, "emu.cpp"), os.path.join(CSRC, "flr_api.cpp")]
-    net_src = os.path.join(CSRC, "flr_net.hip")
-    adj_src = os.path.join(CSRC, "flr_adjoint.hip")
-    lr_src = os.path.join(CSRC, "flr_lowres.hip")
-    deps = srcs + [net_src, adj_src, lr_src, os.path.join(HERE, "hip", "hip_runtime.h"),
-                   os.path.join(CSRC, "flr_device.hpp"), os.path.join(CSRC, "flr_launch.hpp"),
-                   os.path.join(CSRC, "flr_adjoint.hpp"), os.path.join(CSRC, "flr_lowres.hpp"),
-                   os.path.join(CSRC, "flr_net_bwd.hpp"), os.path.join(CSRC, "flr_box.hpp"),
-                   os.path.join(CSRC, "flr_prefix.hpp"),
-                   os.path.join(INCLUDE, "flr.h"), os.path.join(INCLUDE, "flr_net.h")]
+    deps = dependencies()
+
     def fresh():
         return os.path.exists(SO) and \
             os.path.getmtime(SO) >= max(os.path.getmtime(d) for d in deps)
@@ -99,15 +103,14 @@ def build(force: bool = False) -> str:
         flags = [cxx, "-std=c++20", *opt, "-pthread", *tls, "-fPIC", *defs,
                  *(SAN_FLAGS if SANITIZE else []), *EXTRA, f"-I{HERE}", f"-I{INCLUDE}",
                  f"-I{CSRC}"]
-        units = srcs + [net_src, adj_src, lr_src]
-        objs = [f"{tmp}.{i}.o" for i in range(len(units))]
+        objs = [f"{tmp}.{i}.o" for i in range(len(UNITS))]
 
         def compile_unit(i):
-            subprocess.run([*flags, "-x", "c++", "-c", units[i], "-o", objs[i]], check=True)
+            subprocess.run([*flags, "-x", "c++", "-c", UNITS[i], "-o", objs[i]], check=True)
 
         import concurrent.futures as cf
-        with cf.ThreadPoolExecutor(max_workers=len(units)) as ex:
-            list(ex.map(compile_unit, range(len(units))))
+        with cf.ThreadPoolExecutor(max_workers=len(UNITS)) as ex:
+            list(ex.map(compile_unit, range(len(UNITS))))
         link = [cxx, "-shared", "-pthread", *(SAN_FLAGS if SANITIZE else []), *objs, "-o", tmp]
         subprocess.run(link, check=True)
         for o in objs:
