@@ -73,12 +73,17 @@ def algo_hbm_bytes_per_px(Q: int, C: int) -> int:
     return 4 * (Q + C) + 4 * C
 
 
+# the sources of the kernels that the counters were taken on
+COUNTED_SOURCES = ("flr_adjoint.hip", "flr_avg.hpp", "flr_device.hpp", "flr_launch.hpp",
+                   "flr_prefix.hpp", "flr_q08.hip")
+
+
 def kernel_source_digest() -> str:
     """Digest of the sources that define the two-pass kernels and their
     launch (the counters are void once any of them changes)."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2410_11625_amd", "csrc")
-    for f in ("flr_avg.hpp", "flr_device.hpp", "flr_launch.hpp", "flr_prefix.hpp", "flr_q08.hip"):
+    for f in COUNTED_SOURCES:
         h.update(open(os.path.join(csrc, f), "rb").read())
     return h.hexdigest()[:16]
 
