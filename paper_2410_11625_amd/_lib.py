@@ -103,6 +103,7 @@ class FlrBatch(ctypes.Structure):
         ("joint_mean", ctypes.c_void_p * FLR_BATCH_MAX),
         ("joint_height", ctypes.c_int32 * FLR_BATCH_MAX),
         ("joint_width", ctypes.c_int32 * FLR_BATCH_MAX),
+        ("avg_rows", ctypes.c_int32),
     ]
 
 

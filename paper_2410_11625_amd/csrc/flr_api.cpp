@@ -885,12 +885,9 @@ flr_status flr_batch_plan(const flr_params* p, const flr_frame* frames, int32_t 
           hipSuccess)
     return FLR_ERR_HIP;
   out_plan->params = *p;
-  // a batch has no tile_rows of its own (its frames do): the plan keeps its
-  // tallest averaging tile there
-  out_plan->params.tile_rows = 0;
+  out_plan->avg_rows = 0;
   for (int i = 0; i < np; ++i)
-    if (apply[i].seg_rows > out_plan->params.tile_rows)
-      out_plan->params.tile_rows = apply[i].seg_rows;
+    if (apply[i].seg_rows > out_plan->avg_rows) out_plan->avg_rows = apply[i].seg_rows;
   out_plan->num_frames = n;
   out_plan->num_joint = nj;
   out_plan->coeff_blocks = ws_walk[nw];
@@ -939,9 +936,7 @@ flr_status flr_batch_run(const flr_batch* b, void* stream) {
     a.frames = static_cast<const LaunchArgs*>(b->apply_table);
     a.wg_start = starts + (n + 1);
     a.batch_blocks = b->apply_blocks;
-    // the tallest averaging tile of the plan (flr_batch_plan)
-    a.seg_rows = p->tile_rows > 0 && p->tile_rows < flr::kAvgTileRows ? p->tile_rows
-                                                                      : flr::kAvgTileRows;
+    a.seg_rows = b->avg_rows;
     if ((st = dispatch(Q, C, flr::K_APPLY_AVG_BATCH, a, stream)) != FLR_OK) return st;
   }
   if (nj > 0) {

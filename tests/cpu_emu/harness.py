@@ -333,6 +333,7 @@ class Emu:
                                     ctypes.byref(plan)), "flr_batch_plan")
         if persistent_blocks is not None:
             plan.persistent_blocks = persistent_blocks
+        self.batch_plan = plan
         for _ in range(runs):
             for o in outs:
                 o[...] = np.nan
@@ -485,6 +486,13 @@ def run_case(spec: dict) -> dict:
             net_ref.net_forward(fr["guides"], fr["noisy"], wts, cache=cache)
             grads = net_adjoint.net_backward(cache, G.astype(np.float32).astype(np.float64))
             return net_grad_errors(got, grads, wts)
+        if kind == "batch_plan":
+            frames = [make_config(1, seed=3, h=h, w=w) for h, w in spec["sizes"]]
+            p = params(1, 1, Q, C, r, 1e-3, 0, 0.0, 1, 2, tile_rows=spec["tile_rows"])
+            emu.batch([dict(guides=f["guides"][:Q], noisy=f["noisy"][:C]) for f in frames], p,
+                      persistent_blocks=0)
+            return {"tile_rows": p.tile_rows, "plan_tile_rows": emu.batch_plan.params.tile_rows,
+                    "avg_rows": emu.batch_plan.avg_rows}
         if kind == "batch":
             from oracle import flr_lowres
             # plain frames of uneven sizes and one joint frame (noisy input and
