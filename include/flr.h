@@ -297,7 +297,8 @@ typedef struct {
   double* joint_models[FLR_BATCH_MAX];      /* device: the fitted models */
   double* joint_mean[FLR_BATCH_MAX];        /* device: ... window-averaged */
   int32_t joint_height[FLR_BATCH_MAX], joint_width[FLR_BATCH_MAX];
-  int32_t avg_rows;                   /* rows of the plain frames' tallest averaging tile */
+  int32_t avg_rows, avg_width;        /* rows of the plain frames' tallest averaging tile,
+                                         width of the narrowest frame */
 } flr_batch;
 
 /* Workspace bytes of a batch (0 if invalid): the launch tables, the

@@ -104,6 +104,7 @@ class FlrBatch(ctypes.Structure):
         ("joint_height", ctypes.c_int32 * FLR_BATCH_MAX),
         ("joint_width", ctypes.c_int32 * FLR_BATCH_MAX),
         ("avg_rows", ctypes.c_int32),
+        ("avg_width", ctypes.c_int32),
     ]
 
 

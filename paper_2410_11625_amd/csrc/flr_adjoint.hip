@@ -157,27 +157,27 @@ hipError_t launch_mean_planes64(const double* src, double* dst, int planes, int 
 
 // The coefficient average (it needs no per-(Q, C) code, so it is built here
 // once, beside the other window sums).
-template <int RAD, int TH, bool BATCH>
+// Frames of a batch may differ in tile height and width: TH is the tallest,
+// NARROW set where one is narrower than four columns.
+template <int RAD, int TH, bool BATCH, bool NARROW>
 __global__ void __launch_bounds__(kThreads, 2) apply_avg_kernel(LaunchArgs ain) {
   int bid = blockIdx.x;
   const LaunchArgs a = BATCH ? batch_frame(ain, &bid) : ain;
   const int n = a.tiles_x * a.n_seg * a.nc;
   const int t = avg_group_xcd(bid, n);
   if (t >= n) return;  // padding
-  // frames of a batch may differ in tile height: TH is the tallest
-  if (BATCH && TH > 2 && a.W < 4)
-    avg_group_th<2, RAD>(a, t);
-  else
-    avg_group_th<TH, RAD>(a, t);
+  avg_group_th<TH, RAD, NARROW>(a, t);
 }
 
-template <int RAD, int TH>
+template <int RAD, int TH, bool NARROW>
 static void avg_launch(const LaunchArgs& a, bool batch, int blocks, hipStream_t s) {
   const size_t l = avg_lds_bytes(TH);
   if (batch)
-    hipLaunchKernelGGL((apply_avg_kernel<RAD, TH, true>), dim3(blocks), dim3(kThreads), l, s, a);
+    hipLaunchKernelGGL((apply_avg_kernel<RAD, TH, true, NARROW>), dim3(blocks), dim3(kThreads), l,
+                       s, a);
   else
-    hipLaunchKernelGGL((apply_avg_kernel<RAD, TH, false>), dim3(blocks), dim3(kThreads), l, s, a);
+    hipLaunchKernelGGL((apply_avg_kernel<RAD, TH, false, NARROW>), dim3(blocks), dim3(kThreads), l,
+                       s, a);
 }
 
 // The kernel of the tile height: one for both heights would take the taller
@@ -185,16 +185,16 @@ static void avg_launch(const LaunchArgs& a, bool batch, int blocks, hipStream_t 
 template <int RAD>
 static void avg_dispatch(const LaunchArgs& a, bool batch, int blocks, hipStream_t s) {
   if (a.seg_rows > 2)
-    avg_launch<RAD, 4>(a, batch, blocks, s);
+    a.W < 4 ? avg_launch<RAD, 4, true>(a, batch, blocks, s)
+            : avg_launch<RAD, 4, false>(a, batch, blocks, s);
   else
-    avg_launch<RAD, 2>(a, batch, blocks, s);
+    a.W < 4 ? avg_launch<RAD, 2, true>(a, batch, blocks, s)
+            : avg_launch<RAD, 2, false>(a, batch, blocks, s);
 }
 
 hipError_t launch_avg(const LaunchArgs& a, bool batch, hipStream_t s) {
   if (a.r < 0 || a.r > 32) return hipErrorInvalidValue;
-  // taller tiles load four columns at a time (plan_avg)
-  if (a.seg_rows < 1 || a.seg_rows > kAvgTileRows ||
-      (!batch && (a.nc < 1 || (a.seg_rows > 2 && a.W < 4))))
+  if (a.seg_rows < 1 || a.seg_rows > kAvgTileRows || (!batch && a.nc < 1))
     return hipErrorInvalidValue;
   const int blocks = batch ? a.batch_blocks : avg_groups(a.tiles_x * a.n_seg, a.nc);
   switch (avg_variant(a.r)) {

@@ -885,9 +885,11 @@ flr_status flr_batch_plan(const flr_params* p, const flr_frame* frames, int32_t 
           hipSuccess)
     return FLR_ERR_HIP;
   out_plan->params = *p;
-  out_plan->avg_rows = 0;
-  for (int i = 0; i < np; ++i)
+  out_plan->avg_rows = out_plan->avg_width = 0;
+  for (int i = 0; i < np; ++i) {
     if (apply[i].seg_rows > out_plan->avg_rows) out_plan->avg_rows = apply[i].seg_rows;
+    if (i == 0 || apply[i].W < out_plan->avg_width) out_plan->avg_width = apply[i].W;
+  }
   out_plan->num_frames = n;
   out_plan->num_joint = nj;
   out_plan->coeff_blocks = ws_walk[nw];
@@ -937,6 +939,7 @@ flr_status flr_batch_run(const flr_batch* b, void* stream) {
     a.wg_start = starts + (n + 1);
     a.batch_blocks = b->apply_blocks;
     a.seg_rows = b->avg_rows;
+    a.W = b->avg_width;
     if ((st = dispatch(Q, C, flr::K_APPLY_AVG_BATCH, a, stream)) != FLR_OK) return st;
   }
   if (nj > 0) {

@@ -401,8 +401,9 @@ __device__ __forceinline__ void avg_tile(const LaunchArgs& a, const int c, const
 // Workgroup t of a frame: one channel of one tile. Channels run fastest, then
 // down a strip, so that a tile's channels (which read the same guides) and
 // vertically adjacent tiles (which share 2r rows of every plane) follow each
-// other.
-template <int TH, int RAD>
+// other. NARROW: the image may be narrower than four columns (a kernel of its
+// own: its loads would take the four-row form at r = 8 from 163 to 252 registers).
+template <int TH, int RAD, bool NARROW>
 __device__ __forceinline__ void avg_group_th(const LaunchArgs& a, const int t) {
   extern __shared__ float lds[];
   double* base = reinterpret_cast<double*>(lds);
@@ -415,9 +416,9 @@ __device__ __forceinline__ void avg_group_th(const LaunchArgs& a, const int t) {
                     Y0 + TH - 1 + a.r >= a.H;
   if (!edge)
     avg_tile<TH, RAD, 0>(a, c, X0, Y0, yend, base, wv);
-  else if (TH > 2 || a.W >= 4)
+  else if (!NARROW || a.W >= 4)
     avg_tile<TH, RAD, 1>(a, c, X0, Y0, yend, base, wv);
-  else if constexpr (TH == 2)  // plan_avg: narrow images take tiles of two rows
+  else
     avg_tile<TH, RAD, 2>(a, c, X0, Y0, yend, base, wv);
 }
 
@@ -425,9 +426,9 @@ __device__ __forceinline__ void avg_group_th(const LaunchArgs& a, const int t) {
 template <int RAD>
 __device__ __forceinline__ void avg_group(const LaunchArgs& a, const int t) {
   if (a.seg_rows > 2)
-    avg_group_th<4, RAD>(a, t);
+    avg_group_th<4, RAD, true>(a, t);
   else
-    avg_group_th<2, RAD>(a, t);
+    avg_group_th<2, RAD, true>(a, t);
 }
 
 // Workgroup of a frame for workgroup b of its launch range. Workgroups are

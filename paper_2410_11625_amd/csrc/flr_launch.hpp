@@ -362,7 +362,6 @@ inline void plan_avg(int H, int W, int r, int C, int tile_rows, int* tiles_x, in
     t = tile_rows < kAvgTileRows ? tile_rows : kAvgTileRows;
   else if ((int64_t)*tiles_x * ceil_div(H, tall) * C >= kAvgMinGroups)
     t = tall;
-  if (W < 4 && t > 2) t = 2;
   *seg_rows = t < H ? t : H;
   *n_seg = ceil_div(H, *seg_rows);
 }
