@@ -163,7 +163,7 @@ template <int RAD, int TH, bool BATCH, bool NARROW>
 __global__ void __launch_bounds__(kThreads, 2) apply_avg_kernel(LaunchArgs ain) {
   int bid = blockIdx.x;
   const LaunchArgs a = BATCH ? batch_frame(ain, &bid) : ain;
-  const int n = a.tiles_x * a.n_seg * a.nc;
+  const int n = avg_workgroups(a.tiles_x * a.n_seg, a.nc, a.avg_solo);
   const int t = avg_group_xcd(bid, n);
   if (t >= n) return;  // padding
   avg_group_th<TH, RAD, NARROW>(a, t);
@@ -196,7 +196,7 @@ hipError_t launch_avg(const LaunchArgs& a, bool batch, hipStream_t s) {
   if (a.r < 0 || a.r > 32) return hipErrorInvalidValue;
   if (a.seg_rows < 1 || a.seg_rows > kAvgTileRows || (!batch && a.nc < 1))
     return hipErrorInvalidValue;
-  const int blocks = batch ? a.batch_blocks : avg_groups(a.tiles_x * a.n_seg, a.nc);
+  const int blocks = batch ? a.batch_blocks : avg_groups(a.tiles_x * a.n_seg, a.nc, a.avg_solo);
   switch (avg_variant(a.r)) {
     case AVG_R8: avg_dispatch<AVG_R8>(a, batch, blocks, s); break;
     case AVG_R64: avg_dispatch<AVG_R64>(a, batch, blocks, s); break;

@@ -48,8 +48,8 @@ LaunchArgs base_args(const flr_params* p) {
 
 void plan(const flr_params* p, int kind, LaunchArgs* a) {
   if (kind == flr::K_APPLY_AVG) {
-    flr::plan_avg(p->height, p->width, p->radius, p->num_channels, p->tile_rows, &a->tiles_x,
-                  &a->n_seg, &a->seg_rows);
+    flr::plan_avg(p->height, p->width, p->radius, p->num_guides, p->num_channels, a->coef_lo,
+                  p->tile_rows, &a->tiles_x, &a->n_seg, &a->seg_rows, &a->avg_solo);
     return;
   }
   const int Q = p->num_guides, C = p->num_channels, r = p->radius;
@@ -734,7 +734,7 @@ flr_status flr_batch_plan(const flr_params* p, const flr_frame* frames, int32_t 
       a.coef_lo = 1;
       plan(&q, flr::K_APPLY_AVG, &a);
       apply[np] = a;
-      ws_apply[np + 1] = ws_apply[np] + flr::avg_groups(a.tiles_x * a.n_seg, C);
+      ws_apply[np + 1] = ws_apply[np] + flr::avg_groups(a.tiles_x * a.n_seg, C, a.avg_solo);
       ++np;
     } else {
       a.fin = reinterpret_cast<const double*>(ws + L.mean[i]);

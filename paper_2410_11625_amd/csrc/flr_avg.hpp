@@ -305,8 +305,9 @@ struct AvgLane {
 
 // One channel of a tile of TH rows. The workgroup's wavefronts take every
 // fourth plane each (the chain of planes is what a small frame waits for) and
-// add their sums in LDS at the end.
-template <int TH, int RAD, int EDGE>
+// add their sums in LDS at the end; SOLO: this wavefront takes every plane
+// alone (no barrier), the workgroup's others have tiles of their own.
+template <int TH, int RAD, int EDGE, bool SOLO>
 __device__ __forceinline__ void avg_tile(const LaunchArgs& a, const int c, const int X0,
                                          const int Y0, const int yend, double* base,
                                          const int wv) {
@@ -319,7 +320,7 @@ __device__ __forceinline__ void avg_tile(const LaunchArgs& a, const int c, const
   for (int k = 0; k < TH; ++k)
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[k][i] = 0.0;
-  for (int f = wv; f < L.np; f += kAvgWaves) {
+  for (int f = SOLO ? 0 : wv; f < L.np; f += SOLO ? 1 : kAvgWaves) {
     const __amdgpu_buffer_rsrc_t p = L.plane(f);
     const __amdgpu_buffer_rsrc_t gp = L.guide_plane(f);
     // all loads of the plane first: rows of the first window, then the rows
@@ -377,6 +378,10 @@ __device__ __forceinline__ void avg_tile(const LaunchArgs& a, const int c, const
       L.template rows_out<RB, TH>(k0, vs, g, L.is_guide(f), acc);
     }
   }
+  if constexpr (SOLO) {
+    L.template store<TH>(a.out + (int64_t)c * L.pl, Y0, yend, acc);
+    return;
+  }
   __syncthreads();  // every wavefront is done with its exchange rows
   double* red = base + (threadIdx.x & 63);
 #pragma unroll
@@ -398,28 +403,40 @@ __device__ __forceinline__ void avg_tile(const LaunchArgs& a, const int c, const
   }
 }
 
-// Workgroup t of a frame: one channel of one tile. Channels run fastest, then
+// Unit u of a frame: one channel of one tile. Channels run fastest, then
 // down a strip, so that a tile's channels (which read the same guides) and
 // vertically adjacent tiles (which share 2r rows of every plane) follow each
 // other. NARROW: the image may be narrower than four columns (a kernel of its
 // own: its loads would take the four-row form at r = 8 from 163 to 252 registers).
-template <int TH, int RAD, bool NARROW>
-__device__ __forceinline__ void avg_group_th(const LaunchArgs& a, const int t) {
-  extern __shared__ float lds[];
-  double* base = reinterpret_cast<double*>(lds);
-  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int tile = t / a.nc, c = t - tile * a.nc;
+template <int TH, int RAD, bool NARROW, bool SOLO>
+__device__ __forceinline__ void avg_unit(const LaunchArgs& a, const int u, double* base,
+                                         const int wv) {
+  const int tile = u / a.nc, c = u - tile * a.nc;
   const int sx = tile / a.n_seg, sy = tile - sx * a.n_seg;
   const int X0 = avg_col0(sx, a.r), Y0 = sy * a.seg_rows;
   const int yend = min(Y0 + a.seg_rows, a.H);
   const bool edge = X0 - a.r < 0 || X0 - a.r + 256 > a.W || Y0 - a.r < 0 ||
                     Y0 + TH - 1 + a.r >= a.H;
   if (!edge)
-    avg_tile<TH, RAD, 0>(a, c, X0, Y0, yend, base, wv);
+    avg_tile<TH, RAD, 0, SOLO>(a, c, X0, Y0, yend, base, wv);
   else if (!NARROW || a.W >= 4)
-    avg_tile<TH, RAD, 1>(a, c, X0, Y0, yend, base, wv);
+    avg_tile<TH, RAD, 1, SOLO>(a, c, X0, Y0, yend, base, wv);
   else
-    avg_tile<TH, RAD, 2>(a, c, X0, Y0, yend, base, wv);
+    avg_tile<TH, RAD, 2, SOLO>(a, c, X0, Y0, yend, base, wv);
+}
+
+// Workgroup t of a frame: a unit, or one for each wavefront (avg_solo).
+template <int TH, int RAD, bool NARROW>
+__device__ __forceinline__ void avg_group_th(const LaunchArgs& a, const int t) {
+  extern __shared__ float lds[];
+  double* base = reinterpret_cast<double*>(lds);
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (a.avg_solo) {
+    const int u = t * kAvgWaves + wv;
+    if (u < a.tiles_x * a.n_seg * a.nc) avg_unit<TH, RAD, NARROW, true>(a, u, base, wv);
+  } else {
+    avg_unit<TH, RAD, NARROW, false>(a, t, base, wv);
+  }
 }
 
 // Workgroup t with the frame's tile height.

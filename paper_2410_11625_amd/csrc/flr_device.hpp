@@ -1289,8 +1289,9 @@ __global__ void __launch_bounds__(kThreads, 1) batch_kernel(LaunchArgs ain) {
         break;
       case BI_AVG: {
         const LaunchArgs& f = P->largs[S.arg];
-        const int g1 = min((b + 1) * kAvgItemTiles, f.tiles_x * f.n_seg) * f.nc;
-        for (int g = b * kAvgItemTiles * f.nc; g < g1; ++g) {
+        const int t1 = min((b + 1) * kAvgItemTiles, f.tiles_x * f.n_seg);
+        const int g1 = avg_workgroups(t1, f.nc, f.avg_solo);
+        for (int g = avg_workgroups(b * kAvgItemTiles, f.nc, f.avg_solo); g < g1; ++g) {
           avg_group<AV>(f, g);
           __syncthreads();  // the group is done with LDS
         }

@@ -181,7 +181,8 @@ struct LaunchArgs {
   float* out;            // moments / coefficients / output image
   void* ring;            // K_FUSED1 workspace (ring_t elements)
   int H, W, r;
-  int nq, nc;  // guides and channels
+  int nq, nc;    // guides and channels
+  int avg_solo;  // averaging: a tile and channel per wavefront (plan_avg)
   int seg_rows, tiles_x, n_seg;
   int hchunk_m, hchunk_a;  // horizontal-pass chunk lengths (moments, averaging)
   float eps, eps_mul;
@@ -337,9 +338,13 @@ constexpr int kXcds = 8;
 // each: an item costs a queue step and its wait, a tile of four rows alone is
 // too little work for one (16 frames, 35 Mpixel: 16.7 -> 13.5 ms).
 constexpr int kAvgItemTiles = 4;
+static_assert(kAvgItemTiles % kAvgWaves == 0, "an item holds whole workgroups of plan_avg_solo");
 inline int avg_items(int tiles) { return (tiles + kAvgItemTiles - 1) / kAvgItemTiles; }
-inline int avg_groups(int tiles, int C) {
-  return (tiles * C + kXcds - 1) / kXcds * kXcds;
+__host__ __device__ constexpr int avg_workgroups(int tiles, int C, int solo) {
+  return solo ? (tiles * C + kAvgWaves - 1) / kAvgWaves : tiles * C;
+}
+inline int avg_groups(int tiles, int C, int solo) {
+  return (avg_workgroups(tiles, C, solo) + kXcds - 1) / kXcds * kXcds;
 }
 
 // Rows of coefficient halo a walker recomputes above and below its segment.
@@ -353,8 +358,21 @@ inline int row_halo(int kind, int r) { return kind == K_FUSED1 ? r : 0; }
 // r = 16, 540p, C = 1 35 / 27; 1080p, C = 3 261 / 181. (Eight rows: 242
 // registers, two wavefronts per SIMD; 1080p, Q = 8 132, r = 16 221.)
 constexpr int kAvgMinGroups = 600;
-inline void plan_avg(int H, int W, int r, int C, int tile_rows, int* tiles_x, int* n_seg,
-                     int* seg_rows) {
+// A wavefront takes a tile's planes (np of them) alone where four would share
+// too few: with 2, 3 or 5 planes some idle through a quarter to half of the
+// tile, and the closing sum costs two barriers. It takes several tiles per
+// wavefront slot of the chip to make up for the longer chain. Measured, shared /
+// alone: r = 8, 1080p, 2 planes, C = 1 (2160 tiles) 17.3 / 13.2 us; 4K, C = 3 154
+// / 107; 3 planes, 1080p, C = 3 45 / 38; 5 planes, 1080p, C = 3 (6480 tiles) 65.5 /
+// 58.1, C = 1 26.5 / 27.7; 7 planes, 1080p, C = 3 within 3 %; other radii hold fewer
+// registers and more wavefronts: 2 planes, 4K, r = 16, C = 3 0.77, 3 planes
+// 0.89 to 1.19.
+inline int plan_avg_solo(int r, int np, int64_t units) {
+  if (r == 8) return (np <= 3 && units >= 2048) || (np <= 6 && units >= 6144);
+  return np == 2 && units >= 3072;
+}
+inline void plan_avg(int H, int W, int r, int Q, int C, bool coef_lo, int tile_rows, int* tiles_x,
+                     int* n_seg, int* seg_rows, int* solo) {
   *tiles_x = ceil_div(W - avg_col0(0, r), avg_cols(r));
   constexpr int tall = kAvgTileRows;
   int t = 2;
@@ -364,6 +382,7 @@ inline void plan_avg(int H, int W, int r, int C, int tile_rows, int* tiles_x, in
     t = tall;
   *seg_rows = t < H ? t : H;
   *n_seg = ceil_div(H, *seg_rows);
+  *solo = plan_avg_solo(r, Q + 1 + (coef_lo ? 1 : 0), (int64_t)*tiles_x * *n_seg * C);
 }
 
 // Chunk length for the LDS horizontal pass over `rows` channel rows and
