@@ -12,7 +12,7 @@ namespace flr {
 // segment of rows. Four 64-wide wavefronts.
 constexpr int kThreads = 256;
 // MI355X compute units; the automatic segment choice aims for whole waves of
-// workgroups over this many CUs (the walker kernels run one workgroup per CU).
+// workgroups over this many CUs (workgroups_per_cu of a walker on each).
 constexpr int kCUs = 256;
 // Numeric types. Products of the FP32 inputs are summed in sum_t; central
 // moments, intercepts, the coefficient average and the reconstruction run in
@@ -456,22 +456,37 @@ inline size_t walk_lds_bytes(int kind, int Q, int C, int ns_walk = -1) {
   return L.a + L.b + L.va;
 }
 
-// Workgroups of a walker kernel that share a CU (by LDS; registers allow four).
+// Vector registers of a walker of ns moment channels in one LDS group: its
+// vertical sums, two registers each, and what a mode holds beside them (the
+// built kernels': W_MOMENTS 68 at 4 channels, 176 at 19, 276 at 34; W_COEFFS and
+// W_FUSED0 56, 138 and 212).
+__host__ __device__ constexpr int walk_registers(int kind, int ns) {
+  return kind == K_MOMENTS ? 54 + (13 * ns + 1) / 2 : 44 + 5 * ns;
+}
+// Workgroups of a walker kernel that share a CU: by LDS, and by the 512
+// registers of a SIMD lane, on which each has one wave. Counting LDS alone
+// planned two workgroups of 276 registers as if both ran at once: moments at
+// Q = 6, C = 1, 540p, r = 24 94.7 us, counted as one 67.6.
 inline int workgroups_per_cu(int kind, int Q, int C) {
   if (kind == K_FUSED1) return 1;
-  const int n = (int)(kLdsBytes / walk_lds_bytes(kind, Q, C));
+  const int lds = (int)(kLdsBytes / walk_lds_bytes(kind, Q, C));
+  const int regs = 512 / walk_registers(kind, num_sums(Q, C));
+  const int n = lds < regs ? lds : regs;
   return n < 1 ? 1 : (n > 4 ? 4 : n);
 }
 // Time of a row step with k workgroups on a CU, against one alone. Measured
 // at 1080p, Q = 4, C = 1: one workgroup per CU 2.24 us per row, two 2.8, four
-// 5 (one wave per SIMD leaves most issue slots empty, four fill them).
+// (three of them at a time) 5: one wave per SIMD leaves most issue slots empty.
 inline double shared_step(int k) { return k <= 1 ? 1.0 : 0.15 + 0.55 * k; }
 
 // Pick tiles and segments. With tile_rows > 0 the caller fixes the segment
 // length; otherwise minimise the rounds of workgroups, each the rows walked
 // per segment at the speed of the workgroups that then share a CU. Measured,
 // coefficients at 1080p, Q = 4, C = 1: segments of 34 rows (one workgroup per
-// CU) 88.7 us, of 17 (two) 62.8, of 9 (four) 68.9; Q = 6, C = 1 130 / 96.5.
+// CU) 88.7 us, of 17 (two) 62.8, of 9 (four) 68.9; Q = 6, C = 1 130 / 96.5. The
+// same line serves the moments and the fused walk without averaging: 14 pairs
+// of guides and channels, six sizes, r = 2, 8 and 24, none slower than with one
+// workgroup per CU.
 // K_MOMENTS, K_FUSED0 and K_COEFFS have no coefficient-row halo.
 inline void plan_walk(int kind, int H, int W, int Q, int C, int r, int tile_rows, int* tiles_x,
                       int* n_seg, int* seg_rows) {
