@@ -1135,11 +1135,16 @@ __device__ __forceinline__ void walk_pair_tile(const LaunchArgs a, const int bid
   }
 }
 
-// Whether a walk runs as walk_pair_kernel: both LDS groups in use.
+// Whether a walk runs as walk_pair_kernel: both LDS groups in use, and a system
+// that the solving waves can hold in their 256 registers (Q = 9, C = 2, 74 values,
+// spills 56 of them and is 2 % faster paired at 1080p, r = 8, 17 % at r = 32; Q = 10,
+// C = 1, 76 values, spills 129: 472 us paired, 266 not).
+constexpr int kPairSolve = 74;
 template <int Q, int C, int MODE, int PCNT = -1>
 constexpr bool paired_walk() {
   constexpr int ns = PCNT < 0 ? num_sums(Q, C) : Q + C + PCNT;
-  return (MODE == W_COEFFS || MODE == W_MOMENTS) && group_count(ns, sizeof(sum_t)) == 2;
+  return group_count(ns, sizeof(sum_t)) == 2 &&
+         (MODE == W_MOMENTS || (MODE == W_COEFFS && num_sums(Q, C) <= kPairSolve));
 }
 
 template <int Q, int C, int MODE, bool WIDE, int POFF = 0, int PCNT = -1, bool BATCH = false>

@@ -81,3 +81,10 @@ int main() {
             assert n * ((regs + 7) // 8 * 8) <= 512, (name, regs, n)
             checked += n > 1
     assert checked >= 50
+
+
+def test_paired_walkers_hold_their_systems(kernels):
+    """Where the solving waves spill much of a pixel's system, the unpaired
+    walker is the faster one (measured: 56 registers are worth it, 129 not)."""
+    pairs = {n: spill for n, (_, spill) in kernels.items() if "walk_pair_kernel<" in n}
+    assert pairs and max(pairs.values()) <= 64, max(pairs, key=pairs.get)
