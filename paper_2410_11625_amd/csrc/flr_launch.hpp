@@ -240,8 +240,17 @@ inline int lr_apply_rows(int Q, int C, int block) {
 }
 
 // Upsampling tiles have one row: staged at 2 x it takes 28 KB at Q = 8, C = 3
-// (two rows, 57 KB: 114 against 88 us at 1080p).
-inline int up_items(int H, int W) { return ((W + kThreads - 1) / kThreads) * H; }
+// (two rows, 57 KB: 114 against 88 us at 1080p). Frames of up to half a
+// workgroup's columns take as many rows as fit in it side by side, in no more
+// LDS (the staged columns of a row are at most half its pixels).
+__host__ __device__ constexpr int up_rows(int W) {
+  int rows = 1;
+  while (2 * rows * W <= kThreads) rows *= 2;
+  return rows;
+}
+inline int up_items(int H, int W) {
+  return ((W + kThreads - 1) / kThreads) * ((H + up_rows(W) - 1) / up_rows(W));
+}
 
 // The downsampled-moment variant's low-resolution planes: the pixel count
 // n then the num_sums(Q, C) anchored product sums (FP64, [planes][Hl][Wl]);

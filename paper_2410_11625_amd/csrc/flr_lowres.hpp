@@ -233,13 +233,16 @@ __device__ __forceinline__ void lr_axis(int k, int block, int n_low, int* k0, in
 // uniform, so an item is a model and a column, for all rows), then each lane
 // sums both staged columns' models and interpolates between the two sums.
 // Models FP64 (b~ | a) at a.fin; cg, cy: the anchors, a plane apart by cplane.
+// SIDE: the image is narrower than a workgroup, all TR rows go side by side,
+// kThreads / TR lanes each (with a row step known only at run time every
+// caller's tiles were slower, 85 -> 93 us at 1080p, 8 x 8 blocks).
 //
 // What bounds it: LDS reads (two columns of every model per pixel) and, with
 // 2 x upsampling, staging 131 columns for 256 pixels. Measured at 1080p, Q = 8,
 // C = 3: 8 x 8 blocks 57 -> 32 us against dividing out the row and position of
 // every staged item, in 59 KB of LDS; 2 x upsampling 131 -> 88 us against four
 // loads of every model per pixel.
-template <int Q, int C, int NU>
+template <int Q, int C, int NU, bool SIDE>
 __device__ __forceinline__ void lr_apply_tile(const LaunchArgs& a, const int bx, const int by,
                                               const int block, const int TR, const float* cg,
                                               const float* cy, const int64_t cplane) {
@@ -288,7 +291,8 @@ __device__ __forceinline__ void lr_apply_tile(const LaunchArgs& a, const int bx,
     }
   }
   __syncthreads();
-  const int x = X0 + tid;
+  const int cols = SIDE ? kThreads / TR : kThreads;
+  const int x = X0 + (SIDE ? tid % cols : tid);
   if (x >= a.W) return;
   int c0, c1;
   double tc;
@@ -306,14 +310,15 @@ __device__ __forceinline__ void lr_apply_tile(const LaunchArgs& a, const int bx,
 #pragma unroll
     for (int q = 0; q < Q; ++q) gn[q] = a.guides[q * pl + idx];
   };
-  fetch(0);
-  for (int rr = 0; rr < TR; ++rr) {
+  const int first = SIDE ? tid / cols : 0;
+  fetch(first);
+  for (int rr = first; SIDE ? rr == first : rr < TR; ++rr) {
     const int y = Y0 + rr;
     if (y >= a.H) break;
     T g[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) g[q] = (T)gn[q] - anc_g[q];
-    if (rr + 1 < TR) fetch(rr + 1);  // the next row's guides are on their way meanwhile
+    if (!SIDE && rr + 1 < TR) fetch(rr + 1);  // the next row's guides are on their way meanwhile
     const double* p0 = st + rr * total + c0;
     const double* p1 = st + rr * total + c1;
 #pragma unroll
@@ -330,8 +335,8 @@ __device__ __forceinline__ void lr_apply_tile(const LaunchArgs& a, const int bx,
 }
 template <int Q, int C>
 __global__ void __launch_bounds__(256) lr_apply_staged_kernel(LaunchArgs a) {
-  lr_apply_tile<Q, C, 2>(a, blockIdx.x, blockIdx.y, a.block, a.lr_rows, a.guides, a.noisy,
-                         (int64_t)a.H * a.W);
+  lr_apply_tile<Q, C, 2, false>(a, blockIdx.x, blockIdx.y, a.block, a.lr_rows, a.guides, a.noisy,
+                                (int64_t)a.H * a.W);
 }
 
 // Joint denoising and upsampling (Sec. 3.2): anchored FP64 models (b~ | a,
@@ -339,12 +344,16 @@ __global__ void __launch_bounds__(256) lr_apply_staged_kernel(LaunchArgs a) {
 // a.up times coarser than the output, bilinearly interpolated at each output
 // pixel (half-pixel centres, clamped) and applied to the full-resolution
 // guides with the anchors of the fit (pixel (0, 0) of the low-resolution
-// guides and of the noisy input). Batched over frames; an item is a row of
-// kThreads columns, down each strip of columns.
+// guides and of the noisy input). Batched over frames; an item is up_rows(W) rows
+// of kThreads columns, down each strip of columns.
 template <int Q, int C>
 __device__ __forceinline__ void up_apply_item(const LaunchArgs a, const int bid) {
-  lr_apply_tile<Q, C, 1>(a, bid / a.H, bid % a.H, a.up, 1, a.guides_low, a.noisy,
-                         (int64_t)a.Hl * a.Wl);
+  const int64_t pll = (int64_t)a.Hl * a.Wl;
+  const int rows = up_rows(a.W);  // uniform
+  if (rows == 1)
+    lr_apply_tile<Q, C, 1, false>(a, bid / a.H, bid % a.H, a.up, 1, a.guides_low, a.noisy, pll);
+  else
+    lr_apply_tile<Q, C, 2, true>(a, 0, bid, a.up, rows, a.guides_low, a.noisy, pll);
 }
 template <int Q, int C, bool BATCH>
 __global__ void __launch_bounds__(256) up_apply_kernel(LaunchArgs ain) {
