@@ -406,9 +406,10 @@ __device__ __forceinline__ void avg_tile(const LaunchArgs& a, const int c, const
 // Unit u of a frame: one channel of one tile. Channels run fastest, then
 // down a strip, so that a tile's channels (which read the same guides) and
 // vertically adjacent tiles (which share 2r rows of every plane) follow each
-// other. NARROW: the image may be narrower than four columns (a kernel of its
-// own: its loads would take the four-row form at r = 8 from 163 to 252 registers).
-template <int TH, int RAD, bool NARROW, bool SOLO>
+// other. NARROW: the image may be (1) or is (2) narrower than four columns (a
+// kernel of its own: its loads would take the four-row form at r = 8 from 163 to
+// 252 registers).
+template <int TH, int RAD, int NARROW, bool SOLO>
 __device__ __forceinline__ void avg_unit(const LaunchArgs& a, const int u, double* base,
                                          const int wv) {
   const int tile = u / a.nc, c = u - tile * a.nc;
@@ -417,7 +418,9 @@ __device__ __forceinline__ void avg_unit(const LaunchArgs& a, const int u, doubl
   const int yend = min(Y0 + a.seg_rows, a.H);
   const bool edge = X0 - a.r < 0 || X0 - a.r + 256 > a.W || Y0 - a.r < 0 ||
                     Y0 + TH - 1 + a.r >= a.H;
-  if (!edge)
+  if constexpr (NARROW == 2)
+    avg_tile<TH, RAD, 2, SOLO>(a, c, X0, Y0, yend, base, wv);
+  else if (!edge)
     avg_tile<TH, RAD, 0, SOLO>(a, c, X0, Y0, yend, base, wv);
   else if (!NARROW || a.W >= 4)
     avg_tile<TH, RAD, 1, SOLO>(a, c, X0, Y0, yend, base, wv);
@@ -426,7 +429,7 @@ __device__ __forceinline__ void avg_unit(const LaunchArgs& a, const int u, doubl
 }
 
 // Workgroup t of a frame: a unit, or one for each wavefront (avg_solo).
-template <int TH, int RAD, bool NARROW>
+template <int TH, int RAD, int NARROW>
 __device__ __forceinline__ void avg_group_th(const LaunchArgs& a, const int t) {
   extern __shared__ float lds[];
   double* base = reinterpret_cast<double*>(lds);
@@ -439,13 +442,13 @@ __device__ __forceinline__ void avg_group_th(const LaunchArgs& a, const int t) {
   }
 }
 
-// Workgroup t with the frame's tile height.
+// Workgroup t with the frame's tile height and width.
 template <int RAD>
 __device__ __forceinline__ void avg_group(const LaunchArgs& a, const int t) {
-  if (a.seg_rows > 2)
-    avg_group_th<4, RAD, true>(a, t);
+  if (a.W < 4)
+    a.seg_rows > 2 ? avg_group_th<4, RAD, 2>(a, t) : avg_group_th<2, RAD, 2>(a, t);
   else
-    avg_group_th<2, RAD, true>(a, t);
+    a.seg_rows > 2 ? avg_group_th<4, RAD, 0>(a, t) : avg_group_th<2, RAD, 0>(a, t);
 }
 
 // Workgroup of a frame for workgroup b of its launch range. Workgroups are
