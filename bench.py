@@ -541,10 +541,9 @@ def time_path(flr, torch, np, sets, nsets, dev, stream, path, steps, warmup):
     the FP64 (= unpacked FP32) vector peak, and the whole frame's
     algorithmic HBM bytes over the frame time against the HBM peak."""
     p = flr.make_params(H, W, Q, C, R, eps=EPS, average=True, fused=path)
-    # one byte less than the two kernels' coefficient image keeps the fused
-    # path on its one kernel
-    ws = torch.empty(max(flr.workspace_bytes(p) - (path == "fused"), 1), dtype=torch.uint8,
-                     device=dev)
+    # the smaller workspace keeps the fused path on its one kernel
+    need = flr.min_workspace_bytes(p) if path == "fused" else flr.workspace_bytes(p)
+    ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
     # the two-pass path's coefficient image: intercepts as hi + lo pairs
     coeffs = torch.empty((flr.num_coeff_planes(Q, C) + C, H, W), dtype=torch.float32, device=dev)
 

@@ -106,7 +106,7 @@ typedef enum {
                             whose coefficients pass through a per-workgroup ring in
                             the workspace, r coefficient rows recomputed at each
                             workgroup's top and bottom (slower, and on large frames
-                            a smaller workspace) */
+                            a smaller workspace: flr_denoise_min_workspace_bytes) */
   FLR_PATH_TWO_PASS = 2  /* with averaging: one kernel for moments and solve writing the
                             coefficient image to the workspace, then the averaging and
                             reconstruction of flr_apply; the image holds each intercept
@@ -167,9 +167,16 @@ size_t flr_num_coeff_planes(int32_t num_guides, int32_t num_channels);
  * image of M planes, of which the first slice's are written, then the
  * coefficient image at the next 256-byte boundary);
  * without averaging: 0 (STAGES aside). Depends on the launch geometry only.
- * FLR_PATH_FUSED also takes a smaller workspace that holds its ring: per
- * workgroup 2r+1 rows of (Q+1)*C*256 floats. */
+ */
 size_t flr_denoise_workspace_bytes(const flr_params* p);
+
+/* The least workspace flr_denoise takes for these parameters (0 if invalid).
+ * Less than flr_denoise_workspace_bytes for FLR_PATH_FUSED with averaging where
+ * the one-kernel form's ring is smaller than the coefficient image: per
+ * workgroup 2r+1 rows of (Q+1)*C*256 floats (r = 8, Q = 8, C = 3: 118 MB instead of
+ * 249 at 1080p, 348 MB instead of 8 GB at 8192 x 8192; not where the form's LDS
+ * does not hold Q and C). With a workspace between the two that form runs. */
+size_t flr_denoise_min_workspace_bytes(const flr_params* p);
 
 /* Window moments (Sec. 3.2). Reads guides, noisy; writes moments [M][H][W]. */
 flr_status flr_moments(const flr_params* p, const float* guides, const float* noisy,

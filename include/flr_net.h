@@ -143,7 +143,9 @@ flr_status flr_net_backward(int32_t height, int32_t width, const float* guides,
                             void* workspace, size_t workspace_bytes, void* stream);
 
 /* Workspace bytes of flr_flnr_denoise for params p (p->num_guides must be
- * FLR_NET_IN_GUIDES + FLR_NET_OUT = 12 and p->num_channels 3). */
+ * FLR_NET_IN_GUIDES + FLR_NET_OUT = 12 and p->num_channels 3): those of
+ * flr_denoise, up to the next 256, and of flr_net_forward. As flr_denoise it
+ * also takes less (flr_denoise_min_workspace_bytes in place of the first). */
 size_t flr_flnr_workspace_bytes(const flr_params* p);
 
 /* FLNR: the network, then FLR over the 12 guides (Sec. 3.3 with the

@@ -29,8 +29,8 @@ STATUS_NAMES = {
 
 # Every symbol include/flr.h declares.
 EXPORTED = ("flr_num_moment_planes", "flr_num_coeff_planes", "flr_denoise_workspace_bytes",
-            "flr_moments", "flr_solve", "flr_coefficients", "flr_apply", "flr_denoise",
-            "flr_status_str", "flr_validate_params", "flr_denoise_backward_workspace_bytes",
+            "flr_denoise_min_workspace_bytes", "flr_moments", "flr_solve", "flr_coefficients", "flr_apply",
+            "flr_denoise", "flr_status_str", "flr_validate_params", "flr_denoise_backward_workspace_bytes",
             "flr_denoise_backward", "flr_lowres_workspace_bytes", "flr_denoise_lowres",
             "flr_batch_workspace_bytes", "flr_batch_plan", "flr_batch_run", "flr_batch_failed",
             # include/flr_net.h
@@ -136,6 +136,8 @@ def lib() -> ctypes.CDLL:
     L.flr_num_coeff_planes.restype = ctypes.c_size_t
     L.flr_denoise_workspace_bytes.argtypes = [P]
     L.flr_denoise_workspace_bytes.restype = ctypes.c_size_t
+    L.flr_denoise_min_workspace_bytes.argtypes = [P]
+    L.flr_denoise_min_workspace_bytes.restype = ctypes.c_size_t
     L.flr_validate_params.argtypes = [P]
     L.flr_validate_params.restype = ctypes.c_int
     L.flr_moments.argtypes = [P, vp, vp, vp, vp]

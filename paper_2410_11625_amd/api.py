@@ -88,6 +88,23 @@ def workspace_bytes(p: FlrParams) -> int:
     return int(lib().flr_denoise_workspace_bytes(ctypes.byref(p)))
 
 
+def min_workspace_bytes(p: FlrParams) -> int:
+    """The least workspace ``denoise`` takes: less than ``workspace_bytes`` where
+    the fused path's one-kernel form needs less memory (and takes longer)."""
+    return int(lib().flr_denoise_min_workspace_bytes(ctypes.byref(p)))
+
+
+def _workspace(need: int, least: int, device) -> torch.Tensor:
+    """A workspace of ``need`` bytes, or of ``least`` where the device has no
+    room for that."""
+    try:
+        return torch.empty(need, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        if least >= need:
+            raise
+    return torch.empty(least, dtype=torch.uint8, device=device)
+
+
 def moments(guides: torch.Tensor, noisy: torch.Tensor, radius: int, *, raw: bool = False,
             tile_rows: int = 0, out: torch.Tensor | None = None) -> torch.Tensor:
     """Window moments (central, or raw sums with ``raw``) as [M,H,W]."""
@@ -170,10 +187,12 @@ def denoise(noisy: torch.Tensor, guides: torch.Tensor, radius: int = 8, eps: flo
             fused=True, tile_rows: int = 0, out: torch.Tensor | None = None,
             workspace: torch.Tensor | None = None,
             eps_device: torch.Tensor | None = None) -> torch.Tensor:
-    """The whole FLR path -> [C,H,W]. ``fused``: True (one kernel), False
-    (three stages) or a path name from ``PATHS``. ``workspace`` is a uint8
-    device tensor of at least ``workspace_bytes`` bytes; it is allocated when
-    omitted. ``eps_device``: see make_params."""
+    """The whole FLR path -> [C,H,W]. ``fused``: True (the fused path: with
+    averaging two kernels, or one in a smaller workspace), False (three
+    stages) or a path name from ``PATHS``. ``workspace`` is a uint8 device
+    tensor of ``workspace_bytes`` bytes, or at least ``min_workspace_bytes``;
+    when omitted it is allocated, of the smaller size where the device has no
+    room for the other. ``eps_device``: see make_params."""
     _need(guides, "guides")
     _need(noisy, "noisy")
     Q, H, W = guides.shape
@@ -186,7 +205,7 @@ def denoise(noisy: torch.Tensor, guides: torch.Tensor, radius: int = 8, eps: flo
     if need == 0 and lib().flr_validate_params(ctypes.byref(p)) != 0:
         check(lib().flr_validate_params(ctypes.byref(p)), "flr_denoise")
     if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=guides.device)
+        workspace = _workspace(need, min_workspace_bytes(p), guides.device)
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
     if out is None:
@@ -541,7 +560,9 @@ def flnr_denoise(noisy: torch.Tensor, guides12: torch.Tensor, packed: torch.Tens
         check(lib().flr_validate_params(ctypes.byref(p)), "flr_flnr_denoise")
         raise ValueError("FLNR needs 12 guide planes and 3 noisy channels")
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=guides12.device)
+        least = (min_workspace_bytes(p) + 255) // 256 * 256 + \
+            int(lib().flr_net_workspace_bytes(H, W))
+        workspace = _workspace(need, least, guides12.device)
     if out is None:
         out = torch.empty((C, H, W), dtype=torch.float32, device=guides12.device)
     _need(out, "out")
@@ -818,6 +839,6 @@ class FLNRTrainer:
 
 
 __all__ = ["FLRError", "PATHS", "make_params", "num_moment_planes", "num_coeff_planes",
-           "workspace_bytes", "moments", "solve", "coefficients", "apply", "denoise",
+           "workspace_bytes", "min_workspace_bytes", "moments", "solve", "coefficients", "apply", "denoise",
            "net_num_params", "net_pack", "net_forward", "net_backward", "flnr_workspace_bytes",
            "flnr_denoise", "l1_loss_grad", "adamw_step", "reg_adam_step", "FLNRTrainer"]

@@ -93,6 +93,12 @@ size_t ring_bytes(const flr_params* p) {
          flr::ring_bytes_per_block(p->num_guides, p->num_channels, p->radius);
 }
 
+// Whether the one-kernel form's LDS holds these channel counts.
+bool one_kernel(const flr_params* p) {
+  return flr::walk_lds_bytes(flr::K_FUSED1, p->num_guides, p->num_channels) <=
+         (size_t)flr::kLdsBytes;
+}
+
 // Unfused workspace: the moment image, then the coefficient image at the
 // next 256-byte boundary.
 // Bytes of a coefficient image: (Q + 1) C planes, plus C with the intercept
@@ -340,6 +346,13 @@ size_t flr_denoise_workspace_bytes(const flr_params* p) {
   return two_pass_bytes(p);
 }
 
+size_t flr_denoise_min_workspace_bytes(const flr_params* p) {
+  const size_t need = flr_denoise_workspace_bytes(p);
+  if (need == 0 || p->fused != FLR_PATH_FUSED || !p->average_coeffs || !one_kernel(p)) return need;
+  const size_t ring = ring_bytes(p);
+  return ring < need ? ring : need;
+}
+
 flr_status flr_moments(const flr_params* p, const float* guides, const float* noisy,
                        float* moments, void* stream) {
   flr_status st = flr_validate_params(p);
@@ -438,7 +451,8 @@ flr_status flr_denoise(const flr_params* p_in, const float* guides, const float*
   size_t need = flr_denoise_workspace_bytes(p);
   // FLR_PATH_FUSED with averaging runs as the two-pass path where the
   // workspace holds its coefficient image (and overlaps nothing there); a
-  // workspace that only holds the one-kernel form's ring gets that form.
+  // workspace that only holds the one-kernel form's ring gets that form
+  // (flr_denoise_min_workspace_bytes), where LDS holds its channels.
   // Measured, one kernel / two: 64 x 96, Q = 4, C = 1 51 / 14 us; 256 x 256,
   // Q = 4, C = 1 59 / 19; 717 x 1283, Q = 6, C = 3, r = 5 238 / 155; 1080p,
   // Q = 3, C = 1, r = 3 119 / 94; 1080p, Q = 8, C = 3 654 / 397: one kernel's
@@ -449,7 +463,10 @@ flr_status flr_denoise(const flr_params* p_in, const float* guides, const float*
     const size_t gb = p->num_guides * pb, nb = p->num_channels * pb;
     two_pass = workspace && workspace_bytes >= need && !overlaps(workspace, need, guides, gb) &&
                !overlaps(workspace, need, noisy, nb) && !overlaps(workspace, need, out, ob);
-    if (!two_pass) need = ring_bytes(p);
+    if (!two_pass) {
+      two_pass = !one_kernel(p);
+      if (!two_pass) need = ring_bytes(p);
+    }
   }
   if (need > 0) {
     if (!workspace || workspace_bytes < need) return FLR_ERR_WORKSPACE;

@@ -1074,10 +1074,14 @@ flr_status flr_flnr_denoise(const flr_params* p, float* guides12, const float* n
     return FLR_ERR_CHANNELS;
   if (p->flags & FLR_FLAG_RAW_MOMENTS) return FLR_ERR_MODE;
   if (!guides12 || !noisy || !packed || !out) return FLR_ERR_NULL;
-  const size_t need = flr_flnr_workspace_bytes(p);
-  if (!workspace || workspace_bytes < need) return FLR_ERR_WORKSPACE;
+  // the regression's part, then the network's: the fused path also takes a
+  // workspace that only holds its smaller form
   const size_t pl = (size_t)p->height * p->width;
-  const size_t fw = align256(flr_denoise_workspace_bytes(p));
+  const size_t nw = flr_net_workspace_bytes(p->height, p->width);
+  size_t fw = align256(flr_denoise_workspace_bytes(p));
+  if (workspace_bytes < fw + nw) fw = align256(flr_denoise_min_workspace_bytes(p));
+  const size_t need = fw + nw;
+  if (!workspace || workspace_bytes < need) return FLR_ERR_WORKSPACE;
   char* ws = static_cast<char*>(workspace);
   st = flr_net_forward(p->height, p->width, guides12, noisy, packed,
                        guides12 + FLR_NET_IN_GUIDES * pl, ws + fw, need - fw, stream);
