@@ -94,15 +94,15 @@ def min_workspace_bytes(p: FlrParams) -> int:
     return int(lib().flr_denoise_min_workspace_bytes(ctypes.byref(p)))
 
 
-def _workspace(need: int, least: int, device) -> torch.Tensor:
-    """A workspace of ``need`` bytes, or of ``least`` where the device has no
+def _workspace(need: int, least, device) -> torch.Tensor:
+    """A workspace of ``need`` bytes, or of ``least()`` where the device has no
     room for that."""
     try:
         return torch.empty(need, dtype=torch.uint8, device=device)
     except torch.OutOfMemoryError:
-        if least >= need:
+        if least() >= need:
             raise
-    return torch.empty(least, dtype=torch.uint8, device=device)
+    return torch.empty(least(), dtype=torch.uint8, device=device)
 
 
 def moments(guides: torch.Tensor, noisy: torch.Tensor, radius: int, *, raw: bool = False,
@@ -205,7 +205,7 @@ def denoise(noisy: torch.Tensor, guides: torch.Tensor, radius: int = 8, eps: flo
     if need == 0 and lib().flr_validate_params(ctypes.byref(p)) != 0:
         check(lib().flr_validate_params(ctypes.byref(p)), "flr_denoise")
     if workspace is None and need > 0:
-        workspace = _workspace(need, min_workspace_bytes(p), guides.device)
+        workspace = _workspace(need, lambda: min_workspace_bytes(p), guides.device)
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
     if out is None:
@@ -560,9 +560,8 @@ def flnr_denoise(noisy: torch.Tensor, guides12: torch.Tensor, packed: torch.Tens
         check(lib().flr_validate_params(ctypes.byref(p)), "flr_flnr_denoise")
         raise ValueError("FLNR needs 12 guide planes and 3 noisy channels")
     if workspace is None:
-        least = (min_workspace_bytes(p) + 255) // 256 * 256 + \
-            int(lib().flr_net_workspace_bytes(H, W))
-        workspace = _workspace(need, least, guides12.device)
+        workspace = _workspace(need, lambda: (min_workspace_bytes(p) + 255) // 256 * 256 +
+                               int(lib().flr_net_workspace_bytes(H, W)), guides12.device)
     if out is None:
         out = torch.empty((C, H, W), dtype=torch.float32, device=guides12.device)
     _need(out, "out")
