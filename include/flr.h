@@ -100,13 +100,13 @@ typedef enum { FLR_REG_RIDGE = 0, FLR_REG_PAPER = 1 } flr_reg_mode;
 typedef enum {
   FLR_PATH_STAGES = 0,   /* flr_moments -> flr_solve -> flr_apply, images in the workspace */
   FLR_PATH_FUSED = 1,    /* without averaging: one kernel for moments, solve and
-                            reconstruction; with averaging: as TWO_PASS where the
-                            workspace holds its coefficient image (what
-                            flr_denoise_workspace_bytes asks for), else one kernel
-                            whose coefficients pass through a per-workgroup ring in
-                            the workspace, r coefficient rows recomputed at each
-                            workgroup's top and bottom (slower, and on large frames
-                            a smaller workspace: flr_denoise_min_workspace_bytes) */
+                            reconstruction; with averaging the faster of two forms:
+                            as TWO_PASS, or (small frames with windows of up to 3 x 3)
+                            one kernel whose coefficients pass through a per-workgroup
+                            ring in the workspace, r coefficient rows recomputed at
+                            each workgroup's top and bottom; a workspace that only
+                            holds what the other form needs gets that one
+                            (flr_denoise_min_workspace_bytes) */
   FLR_PATH_TWO_PASS = 2  /* with averaging: one kernel for moments and solve writing the
                             coefficient image to the workspace, then the averaging and
                             reconstruction of flr_apply; the image holds each intercept
@@ -161,21 +161,22 @@ size_t flr_num_coeff_planes(int32_t num_guides, int32_t num_channels);
 /* Workspace bytes flr_denoise needs for these parameters (0 if invalid):
  * FLR_PATH_STAGES: the moment and coefficient images, (M + F*C)*H*W floats
  * (the coefficient image starts at the next 256-byte boundary);
- * FLR_PATH_FUSED, FLR_PATH_TWO_PASS with averaging: the coefficient image with intercept
+ * FLR_PATH_TWO_PASS with averaging: the coefficient image with intercept
  * pairs, (F + 1)*C*H*W floats (F = Q + 1; when Q + C + Q(Q+1)/2 + Q*C
  * exceeds 78 moment channels the walk is split in two: first a moment
  * image of M planes, of which the first slice's are written, then the
  * coefficient image at the next 256-byte boundary);
- * without averaging: 0 (STAGES aside). Depends on the launch geometry only.
- */
+ * FLR_PATH_FUSED with averaging: what its faster form needs, that image or a
+ * ring (below);
+ * without averaging: 0 (STAGES aside). Depends on the launch geometry only. */
 size_t flr_denoise_workspace_bytes(const flr_params* p);
 
 /* The least workspace flr_denoise takes for these parameters (0 if invalid).
  * Less than flr_denoise_workspace_bytes for FLR_PATH_FUSED with averaging where
- * the one-kernel form's ring is smaller than the coefficient image: per
- * workgroup 2r+1 rows of (Q+1)*C*256 floats (r = 8, Q = 8, C = 3: 118 MB instead of
- * 249 at 1080p, 348 MB instead of 8 GB at 8192 x 8192; not where the form's LDS
- * does not hold Q and C). With a workspace between the two that form runs. */
+ * the form that is not preferred needs less. The two-pass form needs the
+ * coefficient image, the one-kernel form 2r+1 rows of (Q+1)*C*256 floats per
+ * workgroup (r = 8, Q = 8, C = 3: 118 MB against the image's 249 at 1080p, 348 MB
+ * against 8 GB at 8192 x 8192; not for Q and C that its LDS does not hold). */
 size_t flr_denoise_min_workspace_bytes(const flr_params* p);
 
 /* Window moments (Sec. 3.2). Reads guides, noisy; writes moments [M][H][W]. */

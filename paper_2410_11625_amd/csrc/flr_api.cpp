@@ -99,6 +99,21 @@ bool one_kernel(const flr_params* p) {
          (size_t)flr::kLdsBytes;
 }
 
+// Whether the fused path with averaging prefers the one-kernel form: windows of
+// one pixel, and of 3 x 3 over few channels, on frames whose segments are a row
+// or two. Its 2r + 1 rows a segment then take no longer than a second launch.
+// Measured back to back, one kernel / two: r = 0, 64 x 96, Q = 4, C = 1 6.0 /
+// 10.4 us, 256 x 256, Q = 6, C = 3 13.1 / 15.9; r = 1, 64 x 96, Q = 1 to 3, C = 1
+// 5.9 / 7.2, 7.8 / 7.9, 9.3 / 9.9, Q = 4 (19 channels) 11.4 / 10.9, 256 x 256,
+// Q = 2 10.5 / 9.6; r = 2, Q = 1 8.2 / 7.5.
+bool prefer_one_kernel(const flr_params* p) {
+  if (p->radius > 1 || !one_kernel(p)) return false;
+  const int64_t rows = (int64_t)p->height *
+                       flr::ceil_div(p->width, flr::strip_out_cols(flr::K_FUSED1, p->radius));
+  if (p->radius == 0) return rows <= 2 * flr::kCUs;
+  return rows <= flr::kCUs && flr::num_sums(p->num_guides, p->num_channels) <= 13;
+}
+
 // Unfused workspace: the moment image, then the coefficient image at the
 // next 256-byte boundary.
 // Bytes of a coefficient image: (Q + 1) C planes, plus C with the intercept
@@ -341,16 +356,16 @@ size_t flr_denoise_workspace_bytes(const flr_params* p) {
   if (p->fused == FLR_PATH_STAGES)
     return unfused_coeff_offset(p) + flr_num_coeff_planes(p->num_guides, p->num_channels) * pb;
   if (!p->average_coeffs) return 0;
-  // the two-pass path and, as the faster form wherever it was measured, the
-  // fused path (flr_denoise)
+  // the two-pass path and, as mostly the faster form, the fused path
+  if (p->fused == FLR_PATH_FUSED && prefer_one_kernel(p)) return ring_bytes(p);
   return two_pass_bytes(p);
 }
 
 size_t flr_denoise_min_workspace_bytes(const flr_params* p) {
   const size_t need = flr_denoise_workspace_bytes(p);
   if (need == 0 || p->fused != FLR_PATH_FUSED || !p->average_coeffs || !one_kernel(p)) return need;
-  const size_t ring = ring_bytes(p);
-  return ring < need ? ring : need;
+  const size_t ring = ring_bytes(p), image = two_pass_bytes(p);
+  return ring < image ? ring : image;
 }
 
 flr_status flr_moments(const flr_params* p, const float* guides, const float* noisy,
@@ -448,24 +463,30 @@ flr_status flr_denoise(const flr_params* p_in, const float* guides, const float*
   if (overlaps(out, ob, guides, p->num_guides * pb) ||
       overlaps(out, ob, noisy, p->num_channels * pb))
     return FLR_ERR_ALIAS;
-  size_t need = flr_denoise_workspace_bytes(p);
-  // FLR_PATH_FUSED with averaging runs as the two-pass path where the
-  // workspace holds its coefficient image (and overlaps nothing there); a
-  // workspace that only holds the one-kernel form's ring gets that form
-  // (flr_denoise_min_workspace_bytes), where LDS holds its channels.
-  // Measured, one kernel / two: 64 x 96, Q = 4, C = 1 51 / 14 us; 256 x 256,
-  // Q = 4, C = 1 59 / 19; 717 x 1283, Q = 6, C = 3, r = 5 238 / 155; 1080p,
+  size_t need = p->fused == FLR_PATH_FUSED ? 0 : flr_denoise_workspace_bytes(p);
+  // FLR_PATH_FUSED with averaging has two forms: as the two-pass path, or one
+  // kernel with its ring (where LDS holds its channels). The preferred one runs
+  // where the workspace holds what it needs (and overlaps nothing there), else
+  // the other. Measured, one kernel / two: 64 x 96, Q = 4, C = 1 51 / 14 us; 256 x
+  // 256, Q = 4, C = 1 59 / 19; 717 x 1283, Q = 6, C = 3, r = 5 238 / 155; 1080p,
   // Q = 3, C = 1, r = 3 119 / 94; 1080p, Q = 8, C = 3 654 / 397: one kernel's
   // ring leaves L2, its segments recompute 2r coefficient rows each, and small
   // frames give it a few long segments.
   bool two_pass = p->fused == FLR_PATH_TWO_PASS && p->average_coeffs;
   if (p->fused == FLR_PATH_FUSED && p->average_coeffs) {
-    const size_t gb = p->num_guides * pb, nb = p->num_channels * pb;
-    two_pass = workspace && workspace_bytes >= need && !overlaps(workspace, need, guides, gb) &&
-               !overlaps(workspace, need, noisy, nb) && !overlaps(workspace, need, out, ob);
-    if (!two_pass) {
-      two_pass = !one_kernel(p);
-      if (!two_pass) need = ring_bytes(p);
+    auto holds = [&](size_t bytes) {
+      return workspace && workspace_bytes >= bytes &&
+             !overlaps(workspace, bytes, guides, p->num_guides * pb) &&
+             !overlaps(workspace, bytes, noisy, p->num_channels * pb) &&
+             !overlaps(workspace, bytes, out, ob);
+    };
+    const bool prefer_one = prefer_one_kernel(p);
+    const size_t image = two_pass_bytes(p);
+    two_pass = !one_kernel(p) || (!prefer_one && holds(image));
+    need = two_pass ? image : ring_bytes(p);
+    if (prefer_one && !holds(need) && holds(image)) {
+      two_pass = true;
+      need = image;
     }
   }
   if (need > 0) {

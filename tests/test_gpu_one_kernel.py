@@ -30,13 +30,14 @@ def _one_kernel(y, g, r, rows=0, **kw):
     Q, H, W = g.shape
     p = flr.make_params(H, W, Q, y.shape[0], r, tile_rows=rows, fused="fused", **kw)
     least = flr.min_workspace_bytes(p)
-    assert least < flr.workspace_bytes(p)  # the one kernel runs
+    image = flr.workspace_bytes(flr.make_params(H, W, Q, y.shape[0], r, fused="two_pass"))
+    assert least < image  # the one kernel runs
     ws = torch.empty(least, dtype=torch.uint8, device=g.device)
     return flr.denoise(y, g, r, fused="fused", workspace=ws, tile_rows=rows, **kw)
 
 
 def _rel(got, want):
-    rms = np.sqrt(np.mean(np.square(want, dtype=np.float64)))
+    rms = max(np.sqrt(np.mean(np.square(want, dtype=np.float64))), 1e-30)  # an all-zero frame
     return float((np.abs(got - want) / np.maximum(np.abs(want), 1e-3 * rms)).max())
 
 
@@ -89,3 +90,22 @@ def test_smaller_workspace_where_memory_is_short(monkeypatch):
     assert len(refused) == 3
     assert _rel(one.cpu().numpy(), two.cpu().numpy()) <= 2e-4
     assert _rel(small.cpu().numpy(), flnr.cpu().numpy()) <= 2e-4
+
+
+@pytest.mark.parametrize("H,W,Q,C,r", [(1, 1, 1, 1, 0), (7, 9, 2, 1, 1), (64, 96, 3, 1, 1),
+                                       (200, 160, 1, 3, 1), (90, 300, 6, 3, 0)])
+def test_small_windows_in_either_form(H, W, Q, C, r):
+    """Small windows on small frames run as one kernel in the workspace that
+    they ask for, and as the two-pass path in one that only holds its image."""
+    guides, noisy, g, y = _frame(H, W, Q, C)
+    p = flr.make_params(H, W, Q, C, r, fused="fused")
+    image = flr.workspace_bytes(flr.make_params(H, W, Q, C, r, fused="two_pass"))
+    need = flr.workspace_bytes(p)
+    assert need > image
+    one = flr.denoise(y, g, r, fused="fused")
+    ws = torch.empty(need, dtype=torch.uint8, device=g.device)
+    assert torch.equal(one, flr.denoise(y, g, r, fused="fused", workspace=ws))
+    two = flr.denoise(y, g, r, fused="fused", workspace=ws[:image])
+    assert torch.equal(two, flr.denoise(y, g, r, fused="two_pass"))
+    want = flr_ref.flr_reference(noisy, guides, r, float(np.float32(1e-3)), "ridge")
+    assert _rel(one.cpu().numpy(), want) <= 1e-4 and _rel(two.cpu().numpy(), want) <= 1e-4

@@ -64,3 +64,15 @@ def test_flnr_takes_the_smaller_form(L):
     assert L.flr_flnr_denoise(ctypes.byref(p), g, y, k, o, ws, small - 1, None) == 8
     # enough: past the size check, on to the next one (here: a misaligned input)
     assert L.flr_flnr_denoise(ctypes.byref(p), g + 4, y, k, o, ws, small, None) == 7
+
+
+def test_small_windows_on_small_frames_ask_for_the_ring(L):
+    """One kernel: 2r + 1 rows of (Q+1) C 256 floats for each of the frame's
+    rows; the coefficient image, where it is smaller, is still enough."""
+    for H, W, Q, C, r in ((64, 96, 3, 1, 1), (64, 96, 6, 3, 0), (200, 160, 1, 3, 1)):
+        need, least = _sizes(L, _p(H, W, Q, C, r))
+        assert need == H * (2 * r + 1) * (Q + 1) * C * 1024
+        assert least == min(need, (Q + 2) * C * H * W * 4)
+    for H, W, Q, C, r in ((64, 96, 4, 1, 1), (64, 96, 1, 1, 2), (600, 96, 1, 1, 1)):
+        need, _ = _sizes(L, _p(H, W, Q, C, r))
+        assert need == (Q + 2) * C * H * W * 4
