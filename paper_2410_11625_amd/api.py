@@ -638,7 +638,8 @@ class FLNRTrainer:
     gives dL/d(guides) and the network backward accumulates dL/d(weights);
     then one AdamW step updates the FP32 master weights. ``params`` (FP32
     device vector) is updated in place. Buffers are allocated once per crop
-    size and reused.
+    size and reused; those of crops that run side by side (``step``) stay within
+    ``SIDE_BYTES``.
 
     FLR's regularisers live on the device (``reg``: eps, eps_mul) and every
     FLR call reads them from there. With ``learn_eps`` they are learned with
@@ -668,7 +669,9 @@ class FLNRTrainer:
         self.reg_state = torch.zeros(6, dtype=torch.float64, device=dev)
         self.learn_eps, self.eps_lr = learn_eps, eps_lr
         self.last_dreg = None
-        self._bufs = {}
+        self._bufs, self._bytes = {}, {}  # (H, W): a crop's buffers, their bytes
+        self._side = {}  # (H, W, slot): those of further streams, last used last
+        self._pinned, self._held = set(), []  # of _side, and tensors, that captured steps replay
         self._streams = []
         self._crop_grads = None
 
@@ -716,30 +719,67 @@ class FLNRTrainer:
         self.learn_eps = state.get("learn_eps", False)
         self.eps_lr = state.get("eps_lr", self.eps_lr)
 
-    def _buffers(self, H, W, dev, slot=0):
-        key = (H, W, slot)
-        if key not in self._bufs:
-            p = make_params(H, W, 12, 3, self.radius, mode=self.mode, fused="two_pass")
-            b = dict(
-                g12=torch.empty((12, H, W), dtype=torch.float32, device=dev),
-                out=torch.empty((3, H, W), dtype=torch.float32, device=dev),
-                G=torch.empty((3, H, W), dtype=torch.float32, device=dev),
-                dy=torch.empty((3, H, W), dtype=torch.float32, device=dev),
-                dg=torch.empty((12, H, W), dtype=torch.float32, device=dev),
-                ws_fwd=torch.empty(max(workspace_bytes(p), 1), dtype=torch.uint8, device=dev),
-                ws_bwd=torch.empty(max(backward_workspace_bytes(p), 1), dtype=torch.uint8,
-                                   device=dev),
-                ws_net=torch.empty(max(int(lib().flr_net_backward_workspace_bytes(H, W)), 1),
-                                   dtype=torch.uint8, device=dev),
-                ws_l1=torch.empty(max(int(lib().flr_l1_workspace_bytes(3 * H * W)), 1),
-                                  dtype=torch.uint8, device=dev))
-            self._bufs[key] = b
-        return self._bufs[key]
+    def _new_buffers(self, H, W, dev) -> dict:
+        p = make_params(H, W, 12, 3, self.radius, mode=self.mode, fused="two_pass")
+        return dict(
+            g12=torch.empty((12, H, W), dtype=torch.float32, device=dev),
+            out=torch.empty((3, H, W), dtype=torch.float32, device=dev),
+            G=torch.empty((3, H, W), dtype=torch.float32, device=dev),
+            dy=torch.empty((3, H, W), dtype=torch.float32, device=dev),
+            dg=torch.empty((12, H, W), dtype=torch.float32, device=dev),
+            ws_fwd=torch.empty(max(workspace_bytes(p), 1), dtype=torch.uint8, device=dev),
+            ws_bwd=torch.empty(max(backward_workspace_bytes(p), 1), dtype=torch.uint8, device=dev),
+            ws_net=torch.empty(max(int(lib().flr_net_backward_workspace_bytes(H, W)), 1),
+                               dtype=torch.uint8, device=dev),
+            ws_l1=torch.empty(max(int(lib().flr_l1_workspace_bytes(3 * H * W)), 1),
+                              dtype=torch.uint8, device=dev))
 
-    # Crops of up to this many pixels leave most of the chip idle in most of
-    # their launches, so several run side by side, each on its own stream
-    # with its own buffers (about 0.4 GB per stream at 256 x 256).
-    SIDE_PIXELS, SIDE_STREAMS = 1 << 18, 4
+    def _buffers(self, H, W, dev) -> dict:
+        if (H, W) not in self._bufs:
+            b = self._bufs[H, W] = self._new_buffers(H, W, dev)
+            self._bytes[H, W] = sum(t.numel() * t.element_size() for t in b.values())
+        return self._bufs[H, W]
+
+    def _side_buffers(self, crops, side, dev):
+        """Buffers of each crop on `side` streams, or None where the further
+        streams' would not fit in SIDE_BYTES. The first stream has the sets that
+        stay with the trainer; of the others the least recently used go, but
+        none that a captured step replays."""
+        first = [self._buffers(*c["noisy"].shape[1:], dev) for c in crops]
+        keys = [(*c["noisy"].shape[1:], k % side) for k, c in enumerate(crops)]
+        need = {k for k in keys if k[2]}
+        kept = {k for k in self._side if k in need or k in self._pinned}
+
+        def nbytes(sets):
+            return sum(self._bytes[k[:2]] for k in sets)
+
+        if nbytes(need | kept) > self.SIDE_BYTES:
+            return None
+        over = nbytes(need | set(self._side)) - self.SIDE_BYTES
+        for k in [k for k in self._side if k not in kept]:
+            if over > 0:
+                over -= nbytes([k])
+                del self._side[k]
+        out = []
+        for b, k in zip(first, keys):
+            if k[2] == 0:
+                out.append(b)
+                continue
+            b = self._side.pop(k, None) or self._new_buffers(*k[:2], dev)
+            self._side[k] = b
+            out.append(b)
+        if torch.cuda.is_current_stream_capturing():
+            self._pinned |= need
+        return out
+
+    # Crops of up to SIDE_PIXELS pixels leave much of the chip idle in most of
+    # their launches, so up to SIDE_STREAMS run side by side, each on its own
+    # stream with its own buffers (0.34 GB at 256 x 256, 1.3 at 512 x 512; at most
+    # SIDE_BYTES beside one set per crop size). 8 crops, in turn / on four
+    # streams: 128 x 128 3.9 / 2.4 ms, 256 x 256 6.0 / 3.8, 384 x 384 9.8 / 6.9,
+    # 512 x 512 14.7 / 11.7; 4 of 600 x 600 9.7 / 8.0, of 720 x 1280 21.8 / 19.2 for
+    # 14 GB more.
+    SIDE_PIXELS, SIDE_STREAMS, SIDE_BYTES = 1 << 18, 4, 4 << 30
 
     def _side_streams(self, crops) -> int:
         """Streams for a batch: 1 where crops are large or few, or where one
@@ -790,15 +830,21 @@ class FLNRTrainer:
         host. Small crops run side by side on streams of the trainer's own,
         which start after the current stream's work and which it waits for;
         their weight gradients are added in crop order, so the result is that
-        of the crops one after the other, bit for bit (8 crops of 256 x 256:
-        5.9 ms one after the other, 4.0 ms on four streams)."""
+        of the crops one after the other, bit for bit. What the further
+        streams' buffers may take is bounded (``SIDE_BYTES``, with
+        ``SIDE_PIXELS`` and ``SIDE_STREAMS`` the trainer's own to set;
+        ``SIDE_STREAMS = 1`` runs every batch in turn, in the least memory)."""
         dev = self.params.device
         packed = net_pack(self.params)
         losses = torch.empty(len(crops), dtype=torch.float64, device=dev)
         dregs = torch.empty((len(crops), 2), dtype=torch.float64, device=dev)
         total = sum(c["noisy"].numel() for c in crops)
         side = self._side_streams(crops)
-        if side == 1:
+        bufs = None
+        while side > 1 and bufs is None:
+            bufs = self._side_buffers(crops, side, dev)
+            side -= bufs is None
+        if bufs is None:
             for k, c in enumerate(crops):
                 _, H, W = c["noisy"].shape
                 self._crop(c, self._buffers(H, W, dev), packed, total, losses[k:k + 1], dregs[k],
@@ -808,9 +854,8 @@ class FLNRTrainer:
             row = (n + 3) // 4 * 4  # 16-byte aligned gradient rows
             if self._crop_grads is None or self._crop_grads.shape[0] < len(crops):
                 self._crop_grads = torch.empty((len(crops), row), dtype=torch.float32, device=dev)
-            # every buffer a crop needs, allocated on the current stream
-            bufs = [self._buffers(c["noisy"].shape[1], c["noisy"].shape[2], dev, k % side)
-                    for k, c in enumerate(crops)]
+            if torch.cuda.is_current_stream_capturing():
+                self._held.append(self._crop_grads)
             main = torch.cuda.current_stream(dev)
             while len(self._streams) < side:
                 self._streams.append(torch.cuda.Stream(device=dev))
