@@ -17,19 +17,22 @@ of the frame's size) instead of taken from the launch planner's cost model:
   stage's tiles, or one launch per stage (whole batch timed both ways).
 
 Results are kept in memory and in a JSON file (``FLR_AUTOTUNE_CACHE``, by
-default ``~/.cache/flr_autotune.json``) keyed by the device architecture
-and the frame's (H, W, Q, C, r), or for a batch schedule by the
-architecture and the batch's frame list; a later process reuses them
-without measuring again.
+default ``~/.cache/flr_autotune.json``) keyed by the device architecture,
+the built library (other kernels have other best schedules) and the frame's
+(H, W, Q, C, r), or for a batch schedule the batch's frame list; a later
+process reuses them without measuring again.
 """
 from __future__ import annotations
 
+import functools
+import hashlib
 import json
 import math
 import os
 
 import torch
 
+from . import _lib
 from .api import Batch, apply, coefficients
 
 _MEM: dict = {}
@@ -76,8 +79,20 @@ def arch(device=None) -> str:
     return str(getattr(torch.cuda.get_device_properties(dev), "gcnArchName", "unknown"))
 
 
+@functools.lru_cache(maxsize=4)
+def _digest(path: str, mtime_ns: int) -> str:
+    with open(path, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:12]
+
+
+def _target(device=None) -> str:
+    """What a measurement holds for: the architecture and the built library."""
+    path = _lib.LIB_PATH
+    return f"{arch(device)}|{_digest(path, os.stat(path).st_mtime_ns)}"
+
+
 def frame_key(H: int, W: int, Q: int, C: int, radius: int, device=None) -> str:
-    return f"{arch(device)}|frame|{H}x{W}|Q{Q}|C{C}|r{radius}"
+    return f"{_target(device)}|frame|{H}x{W}|Q{Q}|C{C}|r{radius}"
 
 
 def candidate_rows(H: int) -> list[int]:
@@ -180,7 +195,7 @@ def tune_batch_rows(frames: list, radius: int = 8, eps: float = 1e-3, reps: int 
     Q = frames[0]["guides"].shape[0]
     C = frames[0]["noisy"].shape[0]
     dev = frames[0]["noisy"].device
-    key = f"{arch(dev)}|batchrows|Q{Q}|C{C}|r{radius}|{_batch_desc(frames)}"
+    key = f"{_target(dev)}|batchrows|Q{Q}|C{C}|r{radius}|{_batch_desc(frames)}"
 
     def with_rows(rows):
         if rows == 0:
@@ -207,7 +222,7 @@ def tune_batch(frames: list, radius: int = 8, eps: float = 1e-3, reps: int = 5) 
     Q = frames[0]["guides"].shape[0]
     C = frames[0]["noisy"].shape[0]
     dev = frames[0]["noisy"].device
-    key = f"{arch(dev)}|batch|Q{Q}|C{C}|r{radius}|{desc}"
+    key = f"{_target(dev)}|batch|Q{Q}|C{C}|r{radius}|{desc}"
     hit = _lookup(key)
     if hit is not None:
         return hit
