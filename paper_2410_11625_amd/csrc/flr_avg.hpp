@@ -5,9 +5,10 @@
 // Sec. 3.1: each pixel's output uses the mean of the coefficients of the
 // windows that contain it,
 //   out_c = (sum b_c + sum_q g_q * sum a_qc) / n.
-// One workgroup owns one channel of a tile of output rows by avg_cols(r)
-// output columns; that channel's planes (b, a_q, and with a.coef_lo the
-// intercepts' lo parts) are taken one at a time. Lane l of a wavefront holds
+// One workgroup (with few planes and many tiles one wavefront, plan_avg_solo)
+// owns one channel of a tile of output rows by avg_cols(r) output columns; that
+// channel's planes (b, a_q, and with a.coef_lo the intercepts' lo parts) are
+// taken one at a time. Lane l of a wavefront holds
 // four adjacent columns X0 - r + 4 l .. + 3: vertical window sums slide down
 // each column in FP64 registers, an exclusive prefix of the lanes' totals
 // (segments of 16 columns for r <= 8, 64 columns otherwise; DPP moves) turns a

@@ -24,12 +24,12 @@
 // sums in a fixed order, so the result does not depend on scheduling.
 //
 // What bounds it: at a training crop's sizes the chain of data gradients (ten
-// launches of 6 to 22 us, most of them with fewer workgroups than the chip has
-// room for) and the weight gradients' FP32 matrix instructions. Measured at
+// launches of 5 to 36 us, most of them with fewer workgroups than the chip has
+// room for) and the FP32 matrix instructions of both gradients. Measured at
 // 256 x 256 against FP32 vector kernels (one thread per pixel and 8 channels of
 // dx, one wave per 4 x 8 channels of a weight gradient's taps, 48 launches):
-// data gradients 435 -> 152 us, weight gradients and their sums 480 -> 98 us,
-// the whole call 962 -> 318 us, 75 us of it the recomputed forward.
+// data gradients 435 -> 161 us, weight gradients and their sums 480 -> 102 us,
+// the whole call 963 -> 342 us, 72 us of it the recomputed forward.
 
 namespace flrnet {
 
